@@ -16,7 +16,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libwdc.so")
-SOURCES = ["wdc.cpp", "gemm.hip", "attention.hip", "elementwise.hip", "surrogate.hip"]
+SOURCES = ["wdc.cpp", "gemm.hip", "gemm_f32.hip", "attention.hip", "elementwise.hip", "surrogate.hip"]
 
 HIPCC = os.environ.get("HIPCC", shutil.which("hipcc") or "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -152,6 +152,10 @@ struct GemmArgs {
 
 // dtype: 0 float32, 1 bfloat16
 hipError_t launch_gemm(int dtype, const GemmArgs &g, hipStream_t s);
+// float32 products on the matrix cores: whether the shape and alignment allow
+// it, and the launch (any epilogue but EPI_QKV)
+bool gemm_f32_mfma(const GemmArgs &g);
+hipError_t launch_gemm_f32(const GemmArgs &g, hipStream_t s);
 // Whether launch_gemm runs this product (epi EPI_STORE shape) on the 256 x 256
 // kernels, the only ones with the EPI_QKV epilogue.
 bool gemm_qkv_fusable(int dtype, const GemmArgs &g);

@@ -14,8 +14,9 @@
 // round would be thin run their last rows as a second launch of 128 x 128 tiles;
 // products too small to fill one dispatch round of 256 x 256 tiles run on
 // 128 x 128 tiles throughout (128 x 64 when even those would not fill it).
-// float32 path (tiny fp32 workload, and shapes the MFMA tiles do not cover):
-// a plain LDS-tiled FMA kernel.
+// float32 products run on the matrix cores too (gemm_f32.hip). Shapes that
+// neither covers (K not a multiple of 32 or 64, unaligned operands): a plain
+// LDS-tiled FMA kernel.
 #include "common.h"
 
 namespace wdc {
@@ -886,6 +887,7 @@ hipError_t launch_gemm(int dtype, const GemmArgs &g_in, hipStream_t s) {
     // narrow outputs (the output head: n = 64 latent values per token)
     if (g.n % 64 == 0) return launch_mfma<128, 64, 2, 2>(g, s);
   }
+  if (dtype == 0 && gemm_f32_mfma(g)) return launch_gemm_f32(g, s);
   dim3 grid((unsigned)((g.n + 63) / 64), (unsigned)((g.m + 63) / 64), g.batch > 1 ? g.batch : 1), block(256);
   if (dtype == 1)
     hipLaunchKernelGGL(k_gemm_simple<bf16_t>, grid, block, 0, s, g);
