@@ -235,19 +235,50 @@ hipError_t launch_qkv_prep(int dtype, const QKVPrepArgs &a, hipStream_t s);
 hipError_t launch_qkv_pad(int dtype, void *q, void *k, void *v, int heads, int hd, int64_t n, int64_t n_pad,
                           hipStream_t s);
 
-// y[i] = sum_j W[i, j] * act(x[j]) + b[i] (+ y[i] if accumulate); act = SiLU if silu_in.
-hipError_t launch_gemv(int dtype, const void *w, const void *b, const float *x, float *y, int n, int k, int silu_in,
-                       int accumulate, hipStream_t s);
-// sinusoidal timestep features (256) of 1000 t, computed in double
-hipError_t launch_timestep_features(double t, float *out, hipStream_t s);
+// Modulation vectors y_b = W SiLU(x_b) + bias of several weights at once. A
+// section is count weights [rows, k] (and biases) of the model dtype, stride
+// bytes apart; entry e of it goes to y + b * ys + yoff + e * ystep. rows % 32 == 0.
+struct ModSec {
+  const void *w, *b;
+  int64_t stride, yoff, ystep;
+  int rows, count;
+};
+struct ModArgs {
+  ModSec sec[5];
+  int nsec;
+  const float *x;         // [nb, k]
+  float *y;
+  int64_t ys;
+  int k, nb;
+};
+hipError_t launch_mod(int dtype, const ModArgs &a, hipStream_t s);
+
+constexpr int kMaxBatch = 64;   // most samples of one batched forward
+struct SamplePtrs {
+  const void *p[kMaxBatch];
+};
+
+// Conditioning vectors of nb samples at one time t: tmp = SiLU(fc1
+// sinusoid(1000 t) + b1) (256 features computed in float64, [n] scratch), y_b
+// [nb, n] = fc2 tmp + b[0] + w[1] cond_b + b[1] + w[2] cam_b + b[2] (the last two where
+// their dim is not 0).
+struct CondArgs {
+  const void *w1, *b1;
+  const void *w[3], *b[3];
+  const void *cond[kMaxBatch], *cam[kMaxBatch];
+  double t;
+  float *tmp, *y;
+  int n, cond_dim, cam_dim, nb;
+};
+hipError_t launch_cond(int dtype, const CondArgs &a, hipStream_t s);
 // convert a model-dtype vector to float32
 hipError_t launch_to_f32(int dtype, const void *src, float *dst, int64_t n, hipStream_t s);
-// z [C,F,H,W] f32 -> patches [Nv, C*pt*ph*pw] model dtype
-hipError_t launch_patchify(int dtype, const float *z, void *out, int c, int f, int h, int w, int pt, int ph, int pw,
-                           hipStream_t s);
-// tokens [Nv, P] f32 -> v [C,F,H,W] f32
-hipError_t launch_unpatchify(const float *tok, float *v, int c, int f, int h, int w, int pt, int ph, int pw,
-                             hipStream_t s);
+// nb latents [C,F,H,W] f32 -> patches [nb, Nv, C*pt*ph*pw] model dtype
+hipError_t launch_patchify(int dtype, const SamplePtrs &z, int nb, void *out, int c, int f, int h, int w, int pt, int ph,
+                           int pw, hipStream_t s);
+// tokens [nb, Nv, P] f32 -> nb velocities [C,F,H,W] f32
+hipError_t launch_unpatchify(const float *tok, const SamplePtrs &v, int nb, int c, int f, int h, int w, int pt, int ph,
+                             int pw, hipStream_t s);
 hipError_t launch_fill_normal(int dtype, void *dst, int64_t n, uint64_t seed, uint64_t offset, float std,
                               hipStream_t s);
 hipError_t launch_copy_rows_f32(const float *src, int64_t lds, float *dst, int64_t ldd, int64_t rows, int64_t cols,

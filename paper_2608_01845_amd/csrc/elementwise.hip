@@ -1,6 +1,6 @@
 // Memory-bound kernels of the denoiser: LayerNorm + adaLN modulation, q/k/v
 // preparation (per-head RMSNorm, 3D rotary embedding, attention layouts),
-// conditioning GEMVs, patch (un)folding and seeded initialisation.
+// conditioning products, patch (un)folding and seeded initialisation.
 #include "common.h"
 
 namespace wdc {
@@ -282,66 +282,165 @@ __global__ void k_qkv_pad(T *q, T *k, T *v, int heads, int hd, int64_t n, int64_
   }
 }
 
-// ---------------------------------------------------------------- GEMV (conditioning)
-// One wavefront per output row; 16-byte loads along the input dimension.
-template <typename T>
-__global__ __launch_bounds__(256) void k_gemv(const T *__restrict__ w, const T *__restrict__ b,
-                                             const float *__restrict__ x, float *__restrict__ y, int n, int k,
-                                             int silu_in, int accumulate) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= n) return;
-  const T *wr = w + (int64_t)row * k;
-  float acc = 0.f;
-  for (int j = lane; j < k; j += 64) {
-    float xv = x[j];
-    if (silu_in) xv = silu(xv);
-    acc += ld<T>(wr + j) * xv;
-  }
-  acc = warp_sum(acc);
-  if (lane == 0) {
-    float out = acc + (b ? ld<T>(b + row) : 0.f);
-    y[row] = accumulate ? y[row] + out : out;
-  }
-}
+// ---------------------------------------------------------------- conditioning products
+// Matrix-vector products of the conditioning path, bound by the weight stream
+// (each weight is read once for up to four samples). The input vectors are
+// staged in LDS once per block, activation applied there: computing SiLU in
+// every wave cost more than its weights' loads (a 18,432 x 3,072 modulation
+// 57 us, 2.0 TB/s; 35 us here). Sums run in one fixed order (explicit fused
+// multiply-adds, lane by lane, then the butterfly), so a sample's result does
+// not depend on how many share the launch.
+// CH input elements per sample are in LDS at a time; a chunk's weights are
+// requested before the barriers of its staging, so they travel under it.
 
-// 16-byte vectorised bf16 variant for k % 512 == 0
-__global__ __launch_bounds__(256) void k_gemv_bf16_v(const bf16_t *__restrict__ w, const bf16_t *__restrict__ b,
-                                                    const float *__restrict__ x, float *__restrict__ y, int n, int k,
-                                                    int silu_in, int accumulate) {
+// acc[r][b] += the lane's part of sum_j w[r][j] x_b[j]; fill(b, j) gives x_b[j]
+template <typename T, int R, int NB, int CH, class Fill>
+__device__ __forceinline__ void gv_dot(const T *const (&w)[R], int k, bool vec, float *xs, const Fill &fill,
+                                       float (&acc)[R][NB]) {
+  constexpr int V = 16 / sizeof(T), IT = CH / (64 * V);
+  static_assert(IT >= 1 && CH % (64 * V) == 0, "whole 16-byte loads of a wave");
   const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= n) return;
-  const uint4 *wr = (const uint4 *)(w + (int64_t)row * k);
-  float acc = 0.f;
-  for (int j = lane; j < k / 8; j += 64) {
-    uint4 pk = wr[j];
-    const float *xp = x + j * 8;
-    uint32_t u[4] = {pk.x, pk.y, pk.z, pk.w};
+  for (int c0 = 0; c0 < k; c0 += CH) {
+    const int n = min(CH, k - c0);
+    uint4 u[IT][R];
+    if (vec)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float x0 = xp[2 * e], x1 = xp[2 * e + 1];
-      if (silu_in) {
-        x0 = silu(x0);
-        x1 = silu(x1);
+      for (int it = 0; it < IT; ++it) {
+        const int j = (it * 64 + lane) * V;
+#pragma unroll
+        for (int r = 0; r < R; ++r) u[it][r] = j < n ? *(const uint4 *)(w[r] + c0 + j) : make_uint4(0, 0, 0, 0);
       }
-      acc += __uint_as_float(u[e] << 16) * x0 + __uint_as_float(u[e] & 0xffff0000u) * x1;
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      for (int i = threadIdx.x; i < n; i += 256) xs[b * CH + i] = fill(b, c0 + i);
+    __syncthreads();
+    if (vec) {
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int j = (it * 64 + lane) * V;
+        if (j >= n) break;
+        float x[NB][V];
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int e = 0; e < V; e += 4) *(float4 *)&x[b][e] = *(const float4 *)&xs[b * CH + j + e];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const uint32_t uu[4] = {u[it][r].x, u[it][r].y, u[it][r].z, u[it][r].w};
+#pragma unroll
+          for (int e = 0; e < V; ++e) {
+            const float wv = sizeof(T) == 4 ? __uint_as_float(uu[e % 4])
+                                            : __uint_as_float(e & 1 ? uu[e / 2] & 0xffff0000u : uu[e / 2] << 16);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[r][b] = fmaf(wv, x[b][e], acc[r][b]);
+          }
+        }
+      }
+    } else {
+      for (int j = lane; j < n; j += 64)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const float wv = ld<T>(w[r] + c0 + j);
+#pragma unroll
+          for (int b = 0; b < NB; ++b) acc[r][b] = fmaf(wv, xs[b * CH + j], acc[r][b]);
+        }
     }
   }
-  acc = warp_sum(acc);
-  if (lane == 0) {
-    float out = acc + (b ? bf2f(b[row]) : 0.f);
-    y[row] = accumulate ? y[row] + out : out;
-  }
 }
 
-__global__ void k_timestep(double t, float *out) {
-  int j = threadIdx.x;
-  if (j >= 128) return;
-  double f = exp(-log(10000.0) * (double)j / 128.0);
-  double arg = 1000.0 * t * f;
-  out[j] = (float)cos(arg);
-  out[128 + j] = (float)sin(arg);
+template <typename T>
+__device__ __forceinline__ bool gv_vec(const void *w, int k) {
+  return k % (16 / (int)sizeof(T)) == 0 && (uintptr_t)w % 16 == 0;
+}
+
+// Modulation vectors of the listed weights for NB samples: y_b[i] = W[i, :] SiLU(x_b) + bias[i]
+// R rows per wave: 8 where the rows are many and long (each staged input then
+// serves 32 of them: 18,432 x 3,072 35 us against 42 with 2), else 2 (51,200 x
+// 1,024: 26 us against 28 with 8)
+template <typename T, int NB, int R>
+__global__ __launch_bounds__(256) void k_mod(ModArgs a) {
+  constexpr int CH = 1024;
+  __shared__ __attribute__((aligned(16))) float xs[NB * CH];
+  // the block's rows lie in one entry of one section (rows % 32 == 0)
+  int64_t row = (int64_t)blockIdx.x * 4 * R;
+  int s = 0;
+  while (s + 1 < a.nsec && row >= (int64_t)a.sec[s].rows * a.sec[s].count) {
+    row -= (int64_t)a.sec[s].rows * a.sec[s].count;
+    ++s;
+  }
+  const ModSec sec = a.sec[s];
+  const int64_t entry = row / sec.rows;
+  const int r0 = (int)(row - entry * sec.rows) + R * (threadIdx.x >> 6), b0 = blockIdx.y * NB;
+  const T *w0 = (const T *)((const char *)sec.w + entry * sec.stride);
+  const T *bias = (const T *)((const char *)sec.b + entry * sec.stride);
+  const T *w[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) w[r] = w0 + (int64_t)(r0 + r) * a.k;
+  float acc[R][NB] = {};
+  gv_dot<T, R, NB, CH>(w, a.k, gv_vec<T>(sec.w, a.k) && sec.stride % 16 == 0, xs,
+                   [&](int b, int j) { return silu(a.x[(int64_t)min(b0 + b, a.nb - 1) * a.k + j]); }, acc);
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const float v = warp_sum(acc[r][b]);
+      if ((threadIdx.x & 63) == 0 && b0 + b < a.nb)
+        a.y[(b0 + b) * a.ys + sec.yoff + entry * sec.ystep + r0 + r] = v + ld<T>(bias + r0 + r);
+    }
+}
+
+// y = SiLU(fc1 * sinusoid(1000 t) + bias): 128 frequencies 1e4^(-j/128), cosines then
+// sines, in float64 by every block (a separate launch cost more)
+template <typename T>
+__global__ __launch_bounds__(256) void k_cond1(const T *w, const T *bias, double t, float *y, int n) {
+  __shared__ __attribute__((aligned(16))) float xs[512];
+  __shared__ float feat[256];
+  const int j = threadIdx.x & 127;
+  const double arg = 1000.0 * t * exp(-log(10000.0) * (double)j / 128.0);
+  feat[threadIdx.x] = threadIdx.x < 128 ? (float)cos(arg) : (float)sin(arg);
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const T *wr[1] = {w + (int64_t)min(row, n - 1) * 256};
+  float acc[1][1] = {};
+  gv_dot<T, 1, 1, 512>(wr, 256, true, xs, [&](int, int i) { return feat[i]; }, acc);
+  const float v = warp_sum(acc[0][0]);
+  if ((threadIdx.x & 63) == 0 && row < n) y[row] = silu(v + ld<T>(bias + row));
+}
+
+// out_b = fc2 tmp + bias2 (+ Wc cond_b + bias_c) (+ Wm cam_b + bias_m): the
+// three products of the conditioning vector in one launch, one row per wave so
+// that 3,072 rows keep 3,072 waves loading
+template <typename T, int NB>
+__global__ __launch_bounds__(256) void k_cond2(CondArgs a) {
+  constexpr int CH = NB == 1 ? 4096 : 2048;
+  __shared__ __attribute__((aligned(16))) float xs[NB * CH];
+  const int rw = blockIdx.x * 4 + (threadIdx.x >> 6), row = min(rw, a.n - 1), b0 = blockIdx.y * NB;
+  float out[NB] = {};
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    const int k = s == 0 ? a.n : s == 1 ? a.cond_dim : a.cam_dim;
+    if (k == 0) continue;
+    const T *w = (const T *)a.w[s], *bias = (const T *)a.b[s];
+    const T *wr[1] = {w + (int64_t)row * k};
+    float acc[1][NB] = {};
+    if (s == 0) {
+      // the same input for every sample
+      float one[1][1] = {};
+      gv_dot<T, 1, 1, CH>(wr, k, gv_vec<T>(w, k), xs, [&](int, int j) { return a.tmp[j]; }, one);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[0][b] = one[0][0];
+    } else {
+      const void *const *xp = s == 1 ? a.cond : a.cam;
+      gv_dot<T, 1, NB, CH>(wr, k, gv_vec<T>(w, k), xs,
+                       [&](int b, int j) { return ld<T>((const T *)xp[min(b0 + b, a.nb - 1)] + j); }, acc);
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) out[b] += warp_sum(acc[0][b]) + ld<T>(bias + row);
+  }
+  if ((threadIdx.x & 63) == 0 && rw < a.n)
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      if (b0 + b < a.nb) a.y[(int64_t)(b0 + b) * a.n + row] = out[b];
 }
 
 template <typename T>
@@ -351,33 +450,37 @@ __global__ void k_to_f32(const T *src, float *dst, int64_t n) {
 }
 
 // ---------------------------------------------------------------- patches
-template <typename T>
-__global__ void k_patchify(const float *__restrict__ z, T *__restrict__ out, int c, int f, int h, int w, int pt,
-                           int ph, int pw) {
-  const int fp = f / pt, hp = h / ph, wp = w / pw;
-  const int P = c * pt * ph * pw;
-  const int64_t total = (int64_t)fp * hp * wp * P;
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Sample blockIdx.y of the launch; I: index type (32-bit divisions where a
+// sample's elements allow it: 8 samples of 172,032 elements 8.2 us against 10.7).
+template <typename T, typename I>
+__global__ void k_patchify(SamplePtrs zs, T *__restrict__ out, int c, int f, int h, int w, int pt, int ph, int pw) {
+  const float *__restrict__ z = (const float *)zs.p[blockIdx.y];
+  const unsigned hp = h / ph, wp = w / pw, P = c * pt * ph * pw;
+  const I total = (I)(f / pt) * hp * wp * P;
+  const I i = (I)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= total) return;
-  int feat = (int)(i % P);
-  int64_t n = i / P;
-  int wq = (int)(n % wp), hq = (int)((n / wp) % hp), fq = (int)(n / ((int64_t)wp * hp));
-  int jj = feat % pw, ii = (feat / pw) % ph, aa = (feat / (pw * ph)) % pt, cc = feat / (pw * ph * pt);
-  int64_t src = (((int64_t)cc * f + (fq * pt + aa)) * h + (hq * ph + ii)) * w + (wq * pw + jj);
+  out += (int64_t)blockIdx.y * total;
+  const unsigned feat = (unsigned)(i % P);
+  const I n = i / P;
+  const unsigned wq = (unsigned)(n % wp), hq = (unsigned)(n / wp % hp), fq = (unsigned)(n / wp / hp);
+  const unsigned jj = feat % pw, ii = feat / pw % ph, aa = feat / pw / ph % pt, cc = feat / pw / ph / pt;
+  const I src = (((I)cc * f + (fq * pt + aa)) * h + (hq * ph + ii)) * w + (wq * pw + jj);
   st<T>(out + i, z[src]);
 }
 
-__global__ void k_unpatchify(const float *__restrict__ tok, float *__restrict__ v, int c, int f, int h, int w, int pt,
-                             int ph, int pw) {
-  const int64_t total = (int64_t)c * f * h * w;
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+template <typename I>
+__global__ void k_unpatchify(const float *__restrict__ tok, SamplePtrs vs, int c, int f, int h, int w, int pt, int ph,
+                             int pw) {
+  float *__restrict__ v = (float *)vs.p[blockIdx.y];
+  const I total = (I)c * f * h * w;
+  const I i = (I)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= total) return;
-  int x = (int)(i % w), y = (int)((i / w) % h), fr = (int)((i / ((int64_t)w * h)) % f), cc = (int)(i / ((int64_t)w * h * f));
-  const int fp = f / pt, hp = h / ph, wp = w / pw;
-  (void)fp;
-  int64_t n = ((int64_t)(fr / pt) * hp + (y / ph)) * wp + (x / pw);
-  int feat = ((cc * pt + fr % pt) * ph + y % ph) * pw + x % pw;
-  v[i] = tok[n * (int64_t)(c * pt * ph * pw) + feat];
+  tok += (int64_t)blockIdx.y * total;
+  const unsigned x = (unsigned)(i % w), y = (unsigned)(i / w % h), fr = (unsigned)(i / w / h % f), cc = (unsigned)(i / w / h / f);
+  const unsigned hp = h / ph, wp = w / pw;
+  const I n = ((I)(fr / pt) * hp + (y / ph)) * wp + (x / pw);
+  const unsigned feat = ((cc * pt + fr % pt) * ph + y % ph) * pw + x % pw;
+  v[i] = tok[n * (I)(c * pt * ph * pw) + feat];
 }
 
 // ---------------------------------------------------------------- seeded normal fill
@@ -566,27 +669,45 @@ hipError_t launch_qkv_pad(int dtype, void *q, void *k, void *v, int heads, int h
   return hipGetLastError();
 }
 
-hipError_t launch_gemv(int dtype, const void *w, const void *b, const float *x, float *y, int n, int k, int silu_in,
-                       int accumulate, hipStream_t s) {
-  dim3 g(nblk(n, 4)), bl(256);
+// samples of one launch share the weight reads four (or two) at a time
+template <template <typename, int> class Launch, typename A>
+hipError_t by_samples(int dtype, const A &a, hipStream_t s) {
   if (dtype == 1) {
-    if (k % 512 == 0 && ((uintptr_t)w & 15) == 0)
-      hipLaunchKernelGGL(k_gemv_bf16_v, g, bl, 0, s, (const bf16_t *)w, (const bf16_t *)b, x, y, n, k, silu_in,
-                         accumulate);
-    else
-      hipLaunchKernelGGL((k_gemv<bf16_t>), g, bl, 0, s, (const bf16_t *)w, (const bf16_t *)b, x, y, n, k, silu_in,
-                         accumulate);
-  } else {
-    hipLaunchKernelGGL((k_gemv<float>), g, bl, 0, s, (const float *)w, (const float *)b, x, y, n, k, silu_in,
-                       accumulate);
+    if (a.nb > 2) return Launch<bf16_t, 4>::run(a, s);
+    return a.nb == 2 ? Launch<bf16_t, 2>::run(a, s) : Launch<bf16_t, 1>::run(a, s);
   }
-  return hipGetLastError();
+  if (a.nb > 2) return Launch<float, 4>::run(a, s);
+  return a.nb == 2 ? Launch<float, 2>::run(a, s) : Launch<float, 1>::run(a, s);
 }
 
-hipError_t launch_timestep_features(double t, float *out, hipStream_t s) {
-  hipLaunchKernelGGL(k_timestep, dim3(1), dim3(128), 0, s, t, out);
-  return hipGetLastError();
-}
+template <typename T, int NB>
+struct LaunchMod {
+  static hipError_t run(const ModArgs &a, hipStream_t s) {
+    int64_t rows = 0;
+    for (int i = 0; i < a.nsec; ++i) {
+      if (a.sec[i].rows % 32 != 0) return hipErrorInvalidValue;
+      rows += (int64_t)a.sec[i].rows * a.sec[i].count;
+    }
+    const unsigned gy = (unsigned)((a.nb + NB - 1) / NB);
+    if (rows >= 32 * 256 && a.k > 1024)
+      hipLaunchKernelGGL((k_mod<T, NB, 8>), dim3((unsigned)(rows / 32), gy), dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_mod<T, NB, 2>), dim3((unsigned)(rows / 8), gy), dim3(256), 0, s, a);
+    return hipGetLastError();
+  }
+};
+template <typename T, int NB>
+struct LaunchCond {
+  static hipError_t run(const CondArgs &a, hipStream_t s) {
+    const unsigned g = nblk(a.n, 4);
+    hipLaunchKernelGGL(k_cond1<T>, dim3(g), dim3(256), 0, s, (const T *)a.w1, (const T *)a.b1, a.t, a.tmp, a.n);
+    hipLaunchKernelGGL((k_cond2<T, NB>), dim3(g, (unsigned)((a.nb + NB - 1) / NB)), dim3(256), 0, s, a);
+    return hipGetLastError();
+  }
+};
+
+hipError_t launch_mod(int dtype, const ModArgs &a, hipStream_t s) { return by_samples<LaunchMod>(dtype, a, s); }
+hipError_t launch_cond(int dtype, const CondArgs &a, hipStream_t s) { return by_samples<LaunchCond>(dtype, a, s); }
 
 hipError_t launch_to_f32(int dtype, const void *src, float *dst, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
@@ -597,22 +718,30 @@ hipError_t launch_to_f32(int dtype, const void *src, float *dst, int64_t n, hipS
   return hipGetLastError();
 }
 
-hipError_t launch_patchify(int dtype, const float *z, void *out, int c, int f, int h, int w, int pt, int ph, int pw,
-                           hipStream_t s) {
-  int64_t total = (int64_t)c * f * h * w;
-  if (dtype == 1)
-    hipLaunchKernelGGL((k_patchify<bf16_t>), dim3(nblk(total, 256)), dim3(256), 0, s, z, (bf16_t *)out, c, f, h, w,
-                       pt, ph, pw);
+hipError_t launch_patchify(int dtype, const SamplePtrs &z, int nb, void *out, int c, int f, int h, int w, int pt, int ph,
+                           int pw, hipStream_t s) {
+  const int64_t total = (int64_t)c * f * h * w;
+  const dim3 g(nblk(total, 256), nb), b(256);
+  const bool i32 = total < (int64_t(1) << 31);
+  if (dtype == 1 && i32)
+    hipLaunchKernelGGL((k_patchify<bf16_t, uint32_t>), g, b, 0, s, z, (bf16_t *)out, c, f, h, w, pt, ph, pw);
+  else if (dtype == 1)
+    hipLaunchKernelGGL((k_patchify<bf16_t, uint64_t>), g, b, 0, s, z, (bf16_t *)out, c, f, h, w, pt, ph, pw);
+  else if (i32)
+    hipLaunchKernelGGL((k_patchify<float, uint32_t>), g, b, 0, s, z, (float *)out, c, f, h, w, pt, ph, pw);
   else
-    hipLaunchKernelGGL((k_patchify<float>), dim3(nblk(total, 256)), dim3(256), 0, s, z, (float *)out, c, f, h, w, pt,
-                       ph, pw);
+    hipLaunchKernelGGL((k_patchify<float, uint64_t>), g, b, 0, s, z, (float *)out, c, f, h, w, pt, ph, pw);
   return hipGetLastError();
 }
 
-hipError_t launch_unpatchify(const float *tok, float *v, int c, int f, int h, int w, int pt, int ph, int pw,
-                             hipStream_t s) {
-  int64_t total = (int64_t)c * f * h * w;
-  hipLaunchKernelGGL(k_unpatchify, dim3(nblk(total, 256)), dim3(256), 0, s, tok, v, c, f, h, w, pt, ph, pw);
+hipError_t launch_unpatchify(const float *tok, const SamplePtrs &v, int nb, int c, int f, int h, int w, int pt, int ph,
+                             int pw, hipStream_t s) {
+  const int64_t total = (int64_t)c * f * h * w;
+  const dim3 g(nblk(total, 256), nb), b(256);
+  if (total < (int64_t(1) << 31))
+    hipLaunchKernelGGL(k_unpatchify<uint32_t>, g, b, 0, s, tok, v, c, f, h, w, pt, ph, pw);
+  else
+    hipLaunchKernelGGL(k_unpatchify<uint64_t>, g, b, 0, s, tok, v, c, f, h, w, pt, ph, pw);
   return hipGetLastError();
 }
 

@@ -52,7 +52,7 @@ struct wdc_ctx {
   // workspace
   char *ws = nullptr;
   size_t ws_need = 0, ws_bytes = 0;
-  float *x = nullptr, *mod = nullptr, *cemb = nullptr, *tfeat = nullptr, *tmp = nullptr, *cvec = nullptr;
+  float *x = nullptr, *mod = nullptr, *cemb = nullptr, *tmp = nullptr, *cvec = nullptr;
   void *h = nullptr, *qkv = nullptr, *cat = nullptr, *q = nullptr, *k = nullptr, *v = nullptr, *patches = nullptr;
   float *tok = nullptr;
   float2 *rope = nullptr;
@@ -225,11 +225,17 @@ struct Carve {
 };
 
 struct WsLayout {
-  size_t x, h, qkv, cat, q, k, v, mod, cemb, tfeat, tmp, cvec, patches, tok, rope, rv, total;
+  size_t x, h, qkv, cat, q, k, v, mod, cemb, tmp, cvec, patches, tok, rope, rv, total;
 };
 
-// per-sample stride of the modulation vectors (dual blocks use 12 D)
-int64_t mod_stride(const wdc_ctx *c) { return 12 * (int64_t)c->D; }
+// The modulation vectors of every block and of the head, per sample: sequential
+// blocks 6 D floats each, dual blocks 12 D (video then text), single blocks 3 D,
+// the head 2 D (indexed as one more block).
+int64_t mod_off(const wdc_ctx *c, int block) {
+  const int64_t s = std::min(block, c->d.n_seq), d = std::min(std::max(block - c->d.n_seq, 0), c->d.n_dual);
+  return (6 * s + 12 * d + 3 * std::max(block - c->d.n_seq - c->d.n_dual, 0)) * (int64_t)c->D;
+}
+int64_t mod_stride(const wdc_ctx *c) { return mod_off(c, c->d.n_seq + c->d.n_dual + c->d.n_single) + 2 * (int64_t)c->D; }
 
 WsLayout ws_layout(const wdc_ctx *c) {
   WsLayout L;
@@ -247,7 +253,6 @@ WsLayout ws_layout(const wdc_ctx *c) {
   L.v = cv.take(qk);
   L.mod = cv.take(B * mod_stride(c) * 4);
   L.cemb = cv.take(B * D * 4);
-  L.tfeat = cv.take(256 * 4);
   L.tmp = cv.take(D * 4);
   size_t cdim = std::max({(size_t)c->d.cond_dim, (size_t)c->d.cam_dim, (size_t)1});
   L.cvec = cv.take(cdim * 4);
@@ -288,6 +293,21 @@ void release_events(wdc_ctx *c) {
   c->events.clear();
 }
 
+wdc_status need_ws(wdc_ctx *c) {
+  if (!c->ws) {
+    set_err(c, "workspace not bound");
+    return WDC_E_WORKSPACE;
+  }
+  return WDC_OK;
+}
+wdc_status need_w(wdc_ctx *c) {
+  if (!c->w) {
+    set_err(c, "weights not bound");
+    return WDC_E_WORKSPACE;
+  }
+  return WDC_OK;
+}
+
 // ---------------------------------------------------------------- kernel wrappers
 char *elem(wdc_ctx *c, void *base, int64_t off) { return (char *)base + off * c->esz; }
 const char *elem(wdc_ctx *c, const void *base, int64_t off) { return (const char *)base + off * c->esz; }
@@ -326,21 +346,49 @@ wdc_status gemm(wdc_ctx *c, const void *a, int64_t lda, const void *w, const voi
   return WDC_OK;
 }
 
-wdc_status gemv(wdc_ctx *c, const std::string &name, const float *x, float *y, int silu_in, int acc) {
-  const auto &t = c->tensors[c->index.at(name + ".w")];
-  const void *w = W(c, name + ".w"), *b = W(c, name + ".b");
-  if (!w) {
-    set_err(c, "weights not bound");
-    return WDC_E_WORKSPACE;
-  }
-  HIPCHK(c, launch_gemv(c->d.dtype, w, b, x, y, (int)t.shape[0], (int)t.shape[1], silu_in, acc, c->stream));
-  return WDC_OK;
+// Section of the modulation weights "<pre>.<i><post>.ada" of blocks i0 <= i <
+// i0 + count, whose vectors start at yoff and lie ystep apart. Blocks of one
+// kind follow each other in the blob, so their weights are a fixed stride apart.
+ModSec mod_sec(wdc_ctx *c, const std::string &pre, const std::string &post, int i0, int count, int64_t yoff,
+               int64_t ystep) {
+  auto name = [&](int i, const char *t) { return pre + (i < 0 ? "" : std::to_string(i)) + post + ".ada" + t; };
+  ModSec m{};
+  m.w = W(c, name(i0, ".w"));
+  m.b = W(c, name(i0, ".b"));
+  m.rows = (int)c->tensors[c->index.at(name(i0, ".w"))].shape[0];
+  m.count = count;
+  m.stride = count > 1 ? (const char *)W(c, name(i0 + 1, ".w")) - (const char *)m.w : 0;
+  m.yoff = yoff;
+  m.ystep = ystep;
+  return m;
 }
 
-// the modulation GEMV of every sample: y_b = W SiLU(cemb_b) + b, at mod + b * mod_stride + off
-wdc_status mod_gemv(wdc_ctx *c, const std::string &name, int64_t off) {
-  for (int b = 0; b < c->nb; ++b)
-    CHK(gemv(c, name, c->cemb + (int64_t)b * c->D, c->mod + b * mod_stride(c) + off, 1, 0));
+// Modulation vectors of every sample, y_b = W SiLU(cemb_b) + b, of every block
+// and the head (block < 0, one launch) or of one block, into the mod buffer.
+wdc_status modulation(wdc_ctx *c, int block) {
+  CHK(need_w(c));
+  const auto &d = c->d;
+  const int64_t D = c->D;
+  ModArgs a{};
+  auto add = [&](const ModSec &m) { a.sec[a.nsec++] = m; };
+  // blocks [lo, hi) of the kind whose first global index is base
+  auto kind = [&](int base, int count, auto &&f) {
+    const int lo = block < 0 ? 0 : block - base, n = block < 0 ? count : 1;
+    if (count > 0 && n > 0 && lo >= 0 && lo < count) f(lo, n, mod_off(c, base + lo));
+  };
+  kind(0, d.n_seq, [&](int i, int n, int64_t o) { add(mod_sec(c, "seq.", "", i, n, o, 6 * D)); });
+  kind(d.n_seq, d.n_dual, [&](int i, int n, int64_t o) {
+    add(mod_sec(c, "dual.", ".vid", i, n, o, 12 * D));
+    add(mod_sec(c, "dual.", ".txt", i, n, o + 6 * D, 12 * D));
+  });
+  kind(d.n_seq + d.n_dual, d.n_single, [&](int i, int n, int64_t o) { add(mod_sec(c, "single.", "", i, n, o, 3 * D)); });
+  if (block < 0) add(mod_sec(c, "final", "", -1, 1, mod_off(c, d.n_seq + d.n_dual + d.n_single), 0));
+  a.x = c->cemb;
+  a.y = c->mod;
+  a.ys = mod_stride(c);
+  a.k = c->D;
+  a.nb = c->nb;
+  HIPCHK(c, launch_mod(d.dtype, a, c->stream));
   return WDC_OK;
 }
 
@@ -464,15 +512,15 @@ wdc_status ln_mod(wdc_ctx *c, int64_t row0, int64_t rows, const float *shift, co
 }
 
 // ---------------------------------------------------------------- blocks
-// Every block works on all nb samples of the residual stream x [nb, N, D]:
+// Every block works on all nb samples of the residual stream x [nb, N, D], with
+// its modulation vectors in the mod buffer:
 // products that share weights and need no per-sample vector run as one GEMM
 // over all rows; gated residual products run as a batch (one gate per sample).
 wdc_status seq_block(wdc_ctx *c, int i) {
   const int64_t D = c->D, N = c->n, F = c->F, LC = D + F, NB = c->nb, MS = mod_stride(c);
   const std::string pre = "seq." + std::to_string(i);
-  float *m = c->mod;
+  float *m = c->mod + mod_off(c, i);
   const Batch gr{(int)NB, N * LC, N * D, MS};
-  CHK(mod_gemv(c, pre + ".ada", 0));
   CHK(ln_mod(c, 0, N, m, m + D));
   CHK(qkv_project(c, c->h, W(c, pre + ".qkv.w"), W(c, pre + ".qkv.b"), 0, N, false));
   CHK(attention(c, c->cat, LC));
@@ -488,9 +536,7 @@ wdc_status seq_block(wdc_ctx *c, int i) {
 wdc_status dual_block(wdc_ctx *c, int i) {
   const int64_t D = c->D, N = c->n, F = c->F, LC = D + F, NV = c->nv, NT = c->nt, NB = c->nb, MS = mod_stride(c);
   const std::string pre = "dual." + std::to_string(i);
-  float *mv = c->mod, *mt = c->mod + 6 * D;
-  CHK(mod_gemv(c, pre + ".vid.ada", 0));
-  CHK(mod_gemv(c, pre + ".txt.ada", 6 * D));
+  float *mv = c->mod + mod_off(c, c->d.n_seq + i), *mt = mv + 6 * D;
   const struct {
     const char *s;
     int64_t r0, rows;
@@ -518,8 +564,7 @@ wdc_status dual_block(wdc_ctx *c, int i) {
 wdc_status single_block(wdc_ctx *c, int i) {
   const int64_t D = c->D, N = c->n, F = c->F, LC = D + F, NB = c->nb, MS = mod_stride(c);
   const std::string pre = "single." + std::to_string(i);
-  float *m = c->mod;
-  CHK(mod_gemv(c, pre + ".ada", 0));
+  float *m = c->mod + mod_off(c, c->d.n_seq + c->d.n_dual + i);
   CHK(ln_mod(c, 0, N, m, m + D));
   const char *w1 = (const char *)W(c, pre + ".lin1.w"), *b1 = (const char *)W(c, pre + ".lin1.b");
   if (!w1) {
@@ -543,41 +588,36 @@ wdc_status block_forward(wdc_ctx *c, int b) {
   return single_block(c, b);
 }
 
-wdc_status need_ws(wdc_ctx *c) {
-  if (!c->ws) {
-    set_err(c, "workspace not bound");
-    return WDC_E_WORKSPACE;
-  }
-  return WDC_OK;
-}
-wdc_status need_w(wdc_ctx *c) {
-  if (!c->w) {
-    set_err(c, "weights not bound");
-    return WDC_E_WORKSPACE;
-  }
-  return WDC_OK;
-}
-
-wdc_status cond_embed(wdc_ctx *c, double t, const void *cond, const void *cam, float *out) {
-  HIPCHK(c, launch_timestep_features(t, c->tfeat, c->stream));
-  CHK(gemv(c, "t_embed.fc1", c->tfeat, c->tmp, 0, 0));
-  CHK(gemv(c, "t_embed.fc2", c->tmp, out, 1, 0));
-  if (c->d.cond_dim) {
-    if (!cond) {
+// conditioning vectors [nb, D] of nb samples at time t (cond / cam: one pointer per sample, or null)
+wdc_status cond_embed(wdc_ctx *c, int nb, double t, const void *const *cond, const void *const *cam, float *out) {
+  CondArgs a{};
+  for (int b = 0; b < nb; ++b) {
+    a.cond[b] = cond ? cond[b] : nullptr;
+    a.cam[b] = cam ? cam[b] : nullptr;
+    if (c->d.cond_dim && !a.cond[b]) {
       set_err(c, "model has a condition vector but d_cond is NULL");
       return WDC_E_ARG;
     }
-    HIPCHK(c, launch_to_f32(c->d.dtype, cond, c->cvec, c->d.cond_dim, c->stream));
-    CHK(gemv(c, "cond_embed", c->cvec, out, 0, 1));
-  }
-  if (c->d.cam_dim) {
-    if (!cam) {
+    if (c->d.cam_dim && !a.cam[b]) {
       set_err(c, "model has a camera vector but d_cam is NULL");
       return WDC_E_ARG;
     }
-    HIPCHK(c, launch_to_f32(c->d.dtype, cam, c->cvec, c->d.cam_dim, c->stream));
-    CHK(gemv(c, "cam_embed", c->cvec, out, 0, 1));
   }
+  a.w1 = W(c, "t_embed.fc1.w");
+  a.b1 = W(c, "t_embed.fc1.b");
+  const char *names[3] = {"t_embed.fc2", "cond_embed", "cam_embed"};
+  for (int i = 0; i < 3; ++i) {
+    a.w[i] = W(c, std::string(names[i]) + ".w");
+    a.b[i] = W(c, std::string(names[i]) + ".b");
+  }
+  a.t = t;
+  a.tmp = c->tmp;
+  a.y = out;
+  a.n = c->D;
+  a.cond_dim = c->d.cond_dim;
+  a.cam_dim = c->d.cam_dim;
+  a.nb = nb;
+  HIPCHK(c, launch_cond(c->d.dtype, a, c->stream));
   return WDC_OK;
 }
 
@@ -597,11 +637,15 @@ wdc_status dit_forward_batch(wdc_ctx *c, int nb, const float *const *z, double t
   c->nb = nb;
   const int64_t D = c->D, N = c->n, NV = c->nv, P = c->P;
   const auto &d = c->d;
-  for (int b = 0; b < nb; ++b)
-    CHK(cond_embed(c, t, cond ? cond[b] : nullptr, cam ? cam[b] : nullptr, c->cemb + b * D));
-  for (int b = 0; b < nb; ++b)
-    HIPCHK(c, launch_patchify(d.dtype, z[b], elem(c, c->patches, b * NV * P), d.lat_c, d.lat_f, d.lat_h, d.lat_w,
-                              d.patch_t, d.patch_h, d.patch_w, c->stream));
+  CHK(cond_embed(c, nb, t, cond, cam, c->cemb));
+  CHK(modulation(c, -1));
+  SamplePtrs zp{}, vp{};
+  for (int b = 0; b < nb; ++b) {
+    zp.p[b] = z[b];
+    vp.p[b] = vout[b];
+  }
+  HIPCHK(c, launch_patchify(d.dtype, zp, nb, c->patches, d.lat_c, d.lat_f, d.lat_h, d.lat_w, d.patch_t, d.patch_h,
+                            d.patch_w, c->stream));
   CHK(gemm(c, c->patches, P, W(c, "patch_embed.w"), W(c, "patch_embed.b"), c->x, D, NV, D, P, EPI_STORE_F32, nullptr,
            Batch{nb, NV * P, N * D, 0}));
   if (d.text_tokens) {
@@ -615,13 +659,12 @@ wdc_status dit_forward_batch(wdc_ctx *c, int nb, const float *const *z, double t
     }
   }
   for (int b = 0; b < d.n_seq + d.n_dual + d.n_single; ++b) CHK(block_forward(c, b));
-  CHK(mod_gemv(c, "final.ada", 0));
-  CHK(ln_mod(c, 0, NV, c->mod, c->mod + D));
+  const float *fm = c->mod + mod_off(c, d.n_seq + d.n_dual + d.n_single);
+  CHK(ln_mod(c, 0, NV, fm, fm + D));
   CHK(gemm(c, c->h, D, W(c, "final.lin.w"), W(c, "final.lin.b"), c->tok, P, NV, P, D, EPI_STORE_F32, nullptr,
            Batch{nb, N * D, NV * P, 0}));
-  for (int b = 0; b < nb; ++b)
-    HIPCHK(c, launch_unpatchify(c->tok + b * NV * P, vout[b], d.lat_c, d.lat_f, d.lat_h, d.lat_w, d.patch_t,
-                                d.patch_h, d.patch_w, c->stream));
+  HIPCHK(c, launch_unpatchify(c->tok, vp, nb, d.lat_c, d.lat_f, d.lat_h, d.lat_w, d.patch_t, d.patch_h, d.patch_w,
+                              c->stream));
   return WDC_OK;
 }
 
@@ -1136,7 +1179,7 @@ wdc_status wdc_create(const wdc_model_desc *desc, const wdc_params *params, wdc_
     delete c;
     return WDC_E_ARG;
   }
-  if (d.max_batch < 0 || d.max_batch > 64) {
+  if (d.max_batch < 0 || d.max_batch > kMaxBatch) {
     g_create_err = "max_batch out of range (0..64)";
     delete c;
     return WDC_E_ARG;
@@ -1247,7 +1290,6 @@ wdc_status wdc_bind_workspace(wdc_ctx *ctx, void *d_ws, size_t bytes) {
   ctx->v = b + L.v;
   ctx->mod = (float *)(b + L.mod);
   ctx->cemb = (float *)(b + L.cemb);
-  ctx->tfeat = (float *)(b + L.tfeat);
   ctx->tmp = (float *)(b + L.tmp);
   ctx->cvec = (float *)(b + L.cvec);
   ctx->patches = b + L.patches;
@@ -1359,7 +1401,7 @@ wdc_status wdc_cond_embed(wdc_ctx *ctx, double t, const void *d_cond, const void
   if (!ctx || !d_cemb) return WDC_E_ARG;
   CHK(need_ws(ctx));
   CHK(need_w(ctx));
-  return cond_embed(ctx, t, d_cond, d_cam, d_cemb);
+  return cond_embed(ctx, 1, t, &d_cond, &d_cam, d_cemb);
 }
 
 wdc_status wdc_dit_block_forward(wdc_ctx *ctx, int32_t block, float *d_x, const float *d_cemb) {
@@ -1374,7 +1416,8 @@ wdc_status wdc_dit_block_forward(wdc_ctx *ctx, int32_t block, float *d_x, const 
   float *x_saved = ctx->x, *c_saved = ctx->cemb;
   ctx->x = d_x;
   ctx->cemb = const_cast<float *>(d_cemb);
-  wdc_status s = block_forward(ctx, block);
+  wdc_status s = modulation(ctx, block);
+  if (s == WDC_OK) s = block_forward(ctx, block);
   ctx->x = x_saved;
   ctx->cemb = c_saved;
   return s;

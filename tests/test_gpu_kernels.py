@@ -277,3 +277,39 @@ def test_cond_embed_matches_oracle(dtype):
         got = ctx.cond_embed(t, ctx.to_device(inp["cond"]), ctx.to_device(inp["cam"])).cpu().numpy()
         ref = dit.cond_embedding(W, cfg, t, inp["cond"], inp["cam"])
         assert rel_l2(got, ref) <= TOL_F32     # same (bf16-valued) weights, float32 accumulation
+
+
+@pytest.mark.parametrize("dtype,hidden,cond,cam", [
+    ("bf16", 256, 1001, 0), ("bf16", 256, 8, 5000), ("f32", 512, 30, 4100), ("f32", 256, 0, 7), ("bf16", 768, 2056, 96)])
+def test_cond_embed_odd_lengths_match_oracle(dtype, hidden, cond, cam):
+    """Condition and camera lengths below, across and above the staged chunks,
+    odd ones among them (element-wise weight reads)."""
+    torch = torch_cuda()
+    cfg = small_cfg(dtype, hidden=hidden, heads=hidden // 64, cond_dim=cond, cam_dim=cam)
+    ctx = context(cfg)
+    inp = synth.gen_inputs(cfg)
+    got = ctx.cond_embed(0.37, *(ctx.to_device(inp[k]) if k in inp else None for k in ("cond", "cam"))).cpu().numpy()
+    ref = dit.cond_embedding(synth.gen_weights(cfg), cfg, 0.37, inp.get("cond"), inp.get("cam"))
+    err = rel_l2(got, ref)
+    print(dtype, hidden, cond, cam, err)
+    assert err <= 2e-6     # float32 sums of up to 5,000 terms
+
+
+def test_forward_batch_several_blocks_of_each_kind_match_oracle():
+    """Two blocks of every kind, five samples: the modulation vectors of all
+    blocks come from one launch, four samples at a time."""
+    torch = torch_cuda()
+    import paper_2608_01845_amd as wdc
+    cfg = small_cfg("f32", n_seq=2, n_dual=2, n_single=2)
+    ctx = wdc.Context(cfg, max_batch=5)
+    W = synth.gen_weights(cfg)
+    ctx.load_weights(W)
+    B = 5
+    host = [{k: synth.gen_tensor(90 + b, k, v.shape) for k, v in synth.gen_inputs(cfg).items()} for b in range(B)]
+    dev = {k: [ctx.to_device(h[k]) for h in host] for k in host[0]}
+    outs = ctx.forward_batch(dev["z_T"], 0.6, dev["cond"], dev["text"], dev["cam"])
+    for b in range(B):
+        ref = dit.dit_forward(W, cfg, host[b]["z_T"], 0.6, host[b]["cond"], host[b]["text"], host[b]["cam"])
+        err = rel_l2(outs[b].cpu().numpy(), ref)
+        print("sample", b, err)
+        assert err <= TOL_F32
