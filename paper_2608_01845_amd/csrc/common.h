@@ -76,26 +76,14 @@ __device__ __forceinline__ float warp_max(float v) {
   return v;
 }
 
-// Block-wide sum of NV values per thread in a fixed order (deterministic);
-// result valid in thread 0. blockDim.x must be a multiple of 64, <= 1024.
-template <int NV>
-__device__ __forceinline__ void block_sum(float (&v)[NV], float *lds /* >= 16*NV */) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] = warp_sum(v[i]);
-  if (lane == 0)
-#pragma unroll
-    for (int i = 0; i < NV; ++i) lds[w * NV + i] = v[i];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      float s = 0.f;
-      for (int j = 0; j < nw; ++j) s += lds[j * NV + i];
-      v[i] = s;
-    }
-  }
-  __syncthreads();
+// Sum over the wave, in every lane: within rows of 16 lanes by DPP moves, then
+// across rows by the gfx950 lane swaps (no LDS round trips).
+__device__ __forceinline__ float wave_sum_fast(float v) {
+  v = group_sum<16>(v);
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // ------------------------------------------------------------------ GEMM
@@ -292,6 +280,7 @@ struct SegPlan {
   int64_t t;
   int g;       // chunks per channel (8)
   int splits;  // blocks per segment
+  int threads; // threads per block
   int vec;     // 16-byte vector access (set per launch from the buffers' alignment)
   int nseg() const { return c * g; }
   int nblocks() const { return c * g * splits; }
@@ -319,18 +308,8 @@ struct PostArgs {
   int has_anchor, has_zhat;
 };
 hipError_t launch_exact_post(const SegPlan &pl, const PostArgs &a, float *partials, hipStream_t s);
-// sum partials over splits in a fixed order: [nseg, splits, nv] -> [nseg, nv] double
-hipError_t launch_reduce_partials(const SegPlan &pl, const float *partials, int nv, double *out, hipStream_t s);
+// host: sum the blocks' partial sums over splits in a fixed order: [nseg, splits, nv] -> [nseg, nv]
+void reduce_partials(const SegPlan &pl, const float *part, int nv, double *out);
 hipError_t launch_psi(const float *z, const float *v, float dt, float *zn, int64_t n, hipStream_t s);
-
-// Fixed device scratch of the allocation-free surrogate step (one array per
-// device, held until the process ends): per-block partial sums of the
-// statistics kernels at offset 0, their per-segment float64 reductions at
-// kScratchRedOffset. Sized for the largest plan (16 channels x 8 segments x
-// 64 slices, POST_NV values each).
-constexpr size_t kScratchRedOffset = (size_t)16 * 8 * 64 * POST_NV * sizeof(float);
-constexpr size_t kScratchBytes = kScratchRedOffset + (size_t)16 * 8 * POST_NV * sizeof(double);
-// Device address of that array on the current device, looked up once per device.
-hipError_t scratch_address(void **out);
 
 }  // namespace wdc

@@ -5,8 +5,15 @@
 // which is the finest chunking the 256-d summary pools over (coarser chunks
 // nest: floor(4j/T) = floor(floor(8j/T)/2)). Each block streams one slice of
 // one segment, so every per-chunk sum is a plain per-block sum and the grid
-// needs no atomics; partial sums are then combined in a fixed order
-// (deterministic, bit-reproducible run to run).
+// needs no atomics. The blocks write their partial sums (7 to 10 floats each)
+// straight into the state's pinned host memory, and the host, which waits for
+// them anyway, adds the slices of a segment in a fixed order in float64
+// (deterministic, bit-reproducible run to run): no reduction launch and no copy
+// between the kernel and the decision. That needs few blocks: slices are as
+// long as 512 blocks allow (make_seg_plan), with 1,024 threads where a slice
+// would keep 256 threads too long. The candidate step on 16 x 7 x 32 x 48
+// (two such waits): 51 -> 37 us; a rollout step on 16 x 33 x 90 x 160: 74 -> 56
+// us, the combine of four latents at 6.2 TB/s (the 256 MB cache holds most of them).
 //
 // Slices are read as 16-byte vectors when every buffer of the launch is
 // 16-byte aligned: a slice is split into a scalar head (< 4 elements up to
@@ -17,18 +24,10 @@
 // rollout reads each latent once per step (Eq. (2), (5), (6)).
 #include "common.h"
 
-#include <mutex>
-
-// Statistics scratch of the allocation-free surrogate step (layout in common.h).
-// Host code must not pass this name to a kernel: it uses the device address
-// that scratch_address() looks up per device.
-static __device__ __align__(256) unsigned char scratch[wdc::kScratchBytes];
-
 namespace wdc {
 
 namespace {
-constexpr int kThreads = 256;
-constexpr int64_t kSliceElems = 4096;  // target elements per block
+constexpr int kThreads = 1024;   // most threads per block
 
 struct SegRange {
   int64_t a, b;  // flat element range [a, b) of this block
@@ -93,19 +92,28 @@ __device__ __forceinline__ void stream_range(const Op &op, SegRange r, bool vec,
     const int64_t b4 = max(a4, r.b & ~(int64_t)3);
     if (r.a + threadIdx.x < a4) op.template step<1>(r.a + threadIdx.x, acc);
 #pragma unroll 2
-    for (int64_t i = a4 + 4 * (int64_t)threadIdx.x; i < b4; i += 4 * kThreads) op.template step<4>(i, acc);
+    for (int64_t i = a4 + 4 * (int64_t)threadIdx.x; i < b4; i += 4 * (int64_t)blockDim.x) op.template step<4>(i, acc);
     if (b4 + threadIdx.x < r.b) op.template step<1>(b4 + threadIdx.x, acc);
   } else {
-    for (int64_t i = r.a + threadIdx.x; i < r.b; i += kThreads) op.template step<1>(i, acc);
+    for (int64_t i = r.a + threadIdx.x; i < r.b; i += blockDim.x) op.template step<1>(i, acc);
   }
 }
 
+// the block's sums, one store by NV neighbouring lanes (part: pinned host memory)
 template <int NV>
 __device__ __forceinline__ void write_partials(float (&v)[NV], float *lds, float *__restrict__ part) {
-  block_sum<NV>(v, lds);
-  if (threadIdx.x == 0)
+  const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) part[(int64_t)blockIdx.x * NV + i] = v[i];
+  for (int i = 0; i < NV; ++i) v[i] = wave_sum_fast(v[i]);
+  if (lane == 0)
+#pragma unroll
+    for (int i = 0; i < NV; ++i) lds[(threadIdx.x >> 6) * NV + i] = v[i];
+  __syncthreads();
+  if (threadIdx.x < NV) {
+    float s = 0.f;
+    for (int w = 0; w < nw; ++w) s += lds[w * NV + threadIdx.x];
+    part[(int64_t)blockIdx.x * NV + threadIdx.x] = s;
+  }
 }
 
 // pass-1 statistics of z against the anchor za (0 without one):
@@ -141,6 +149,9 @@ __global__ __launch_bounds__(kThreads) void k_stats_pre(SegPlan pl, PreOp op, fl
   write_partials<PRE_NV>(v, lds, part);
 }
 
+// M: number of combined latents, 0 = m (read four at a time, so that their
+// loads travel together)
+template <int M>
 struct ObsOp {
   const float *outs[WDC_MAXB];
   float kappa[WDC_MAXB];
@@ -149,14 +160,30 @@ struct ObsOp {
   float *zhat;
   template <int W>
   __device__ __forceinline__ void step(int64_t i, float (&v)[OBS_NV]) const {
+    const Vf<W> a = za ? ldv<W>(za, i) : zeros<W>();
     Vf<W> acc = zeros<W>();
-    for (int j = 0; j < m; ++j) {
-      const Vf<W> o = ldv<W>(outs[j], i);
+    auto add = [&](int j, const Vf<W> &o) {
 #pragma unroll
       for (int e = 0; e < W; ++e) acc.x[e] += kappa[j] * o.x[e];
+    };
+    if constexpr (M > 0) {
+      Vf<W> o[M];
+#pragma unroll
+      for (int j = 0; j < M; ++j) o[j] = ldv<W>(outs[j], i);
+#pragma unroll
+      for (int j = 0; j < M; ++j) add(j, o[j]);
+    } else {
+      int j = 0;
+      for (; j + 4 <= m; j += 4) {
+        Vf<W> o[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = ldv<W>(outs[j + q], i);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) add(j + q, o[q]);
+      }
+      for (; j < m; ++j) add(j, ldv<W>(outs[j], i));
     }
     stv<W>(zhat, i, acc);
-    const Vf<W> a = za ? ldv<W>(za, i) : zeros<W>();
     float pre[PRE_NV] = {};
     acc_pre<W>(acc, a, pre);
 #pragma unroll
@@ -166,7 +193,8 @@ struct ObsOp {
   }
 };
 
-__global__ __launch_bounds__(kThreads) void k_observe(SegPlan pl, ObsOp op, float *__restrict__ part) {
+template <int M>
+__global__ __launch_bounds__(kThreads) void k_observe(SegPlan pl, ObsOp<M> op, float *__restrict__ part) {
   __shared__ float lds[16 * OBS_NV];
   float v[OBS_NV] = {};
   stream_range<OBS_NV>(op, seg_range(pl.t, pl.g, pl.splits), pl.vec, v);
@@ -216,15 +244,6 @@ __global__ __launch_bounds__(kThreads) void k_exact_post(SegPlan pl, PostOp op, 
   write_partials<POST_NV>(v, lds, part);
 }
 
-__global__ void k_reduce(const float *__restrict__ part, int nseg, int splits, int nv, double *__restrict__ out) {
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= nseg * nv) return;
-  int seg = idx / nv, v = idx % nv;
-  double s = 0.0;
-  for (int sp = 0; sp < splits; ++sp) s += (double)part[((int64_t)seg * splits + sp) * nv + v];
-  out[idx] = s;
-}
-
 template <int W>
 __global__ __launch_bounds__(256) void k_psi(const float *__restrict__ z, const float *__restrict__ v, float dt,
                                              float *__restrict__ zn, int64_t n) {
@@ -245,29 +264,64 @@ __global__ __launch_bounds__(256) void k_psi(const float *__restrict__ z, const 
 bool al16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 }  // namespace
 
+// Slices of about 4,096 elements and 256 threads while at most 4 of them make a
+// segment (512 blocks in all); longer segments in slices of 16,384 elements and
+// 1,024 threads: as many threads in flight, a quarter of the partial sums (16 x
+// 33 x 90 x 160, exact-step epilogue 44 -> 36 us with the wave sums by lane moves).
 SegPlan make_seg_plan(int c, int64_t t, int g) {
   SegPlan p;
   p.c = c;
   p.t = t;
   p.g = g;
   p.vec = 1;
-  int64_t seglen = (t + g - 1) / g;
-  int64_t sp = (seglen + kSliceElems - 1) / kSliceElems;
+  const int64_t seglen = (t + g - 1) / g;
+  int64_t sp = (seglen + 4095) / 4096;
+  p.threads = 256;
+  if (sp > 4) {
+    sp = (seglen + 16383) / 16384;
+    p.threads = kThreads;
+  }
   p.splits = (int)(sp < 1 ? 1 : (sp > 64 ? 64 : sp));
   return p;
+}
+
+void reduce_partials(const SegPlan &pl, const float *part, int nv, double *out) {
+  const int nseg = pl.nseg();
+  for (int seg = 0; seg < nseg; ++seg) {
+    double *o = out + (size_t)seg * nv;
+    for (int v = 0; v < nv; ++v) o[v] = 0.0;
+    for (int sp = 0; sp < pl.splits; ++sp, part += nv)
+      for (int v = 0; v < nv; ++v) o[v] += (double)part[v];
+  }
 }
 
 hipError_t launch_stats_pre(const SegPlan &pl, const float *z, const float *za, float *partials, hipStream_t s) {
   SegPlan p = pl;
   p.vec = al16(z) && al16(za);
-  hipLaunchKernelGGL(k_stats_pre, dim3(p.nblocks()), dim3(kThreads), 0, s, p, PreOp{z, za}, partials);
+  hipLaunchKernelGGL(k_stats_pre, dim3(p.nblocks()), dim3(p.threads), 0, s, p, PreOp{z, za}, partials);
   return hipGetLastError();
 }
+
+namespace {
+template <int M>
+hipError_t run_observe(const SegPlan &p, const ObsOp<0> &o, float *partials, hipStream_t s) {
+  ObsOp<M> op;
+  for (int j = 0; j < WDC_MAXB; ++j) {
+    op.outs[j] = o.outs[j];
+    op.kappa[j] = o.kappa[j];
+  }
+  op.m = o.m;
+  op.za = o.za;
+  op.zhat = o.zhat;
+  hipLaunchKernelGGL(k_observe<M>, dim3(p.nblocks()), dim3(p.threads), 0, s, p, op, partials);
+  return hipGetLastError();
+}
+}  // namespace
 
 hipError_t launch_observe(const SegPlan &pl, const float *const *outs, const float *kappa, int m, const float *za,
                           float *zhat, float *partials, hipStream_t s) {
   if (m < 1 || m > WDC_MAXB) return hipErrorInvalidValue;
-  ObsOp op;
+  ObsOp<0> op;
   bool vec = al16(zhat) && al16(za);
   for (int j = 0; j < WDC_MAXB; ++j) {
     op.outs[j] = j < m ? outs[j] : nullptr;
@@ -279,42 +333,22 @@ hipError_t launch_observe(const SegPlan &pl, const float *const *outs, const flo
   op.zhat = zhat;
   SegPlan p = pl;
   p.vec = vec;
-  hipLaunchKernelGGL(k_observe, dim3(p.nblocks()), dim3(kThreads), 0, s, p, op, partials);
-  return hipGetLastError();
+  // the bank's default capacity and its filling, and the secant's three latents
+  switch (m) {
+    case 1: return run_observe<1>(p, op, partials, s);
+    case 2: return run_observe<2>(p, op, partials, s);
+    case 3: return run_observe<3>(p, op, partials, s);
+    case 4: return run_observe<4>(p, op, partials, s);
+    default: return run_observe<0>(p, op, partials, s);
+  }
 }
 
 hipError_t launch_exact_post(const SegPlan &pl, const PostArgs &a, float *partials, hipStream_t s) {
   SegPlan p = pl;
   p.vec = al16(a.z) && al16(a.v) && al16(a.zn_in) && al16(a.za) && al16(a.zhat) && al16(a.zn_out) &&
           al16(a.bank_slot) && al16(a.anchor_out) && al16(a.in_slot);
-  hipLaunchKernelGGL(k_exact_post, dim3(p.nblocks()), dim3(kThreads), 0, s, p, PostOp{a}, partials);
+  hipLaunchKernelGGL(k_exact_post, dim3(p.nblocks()), dim3(p.threads), 0, s, p, PostOp{a}, partials);
   return hipGetLastError();
-}
-
-hipError_t launch_reduce_partials(const SegPlan &pl, const float *partials, int nv, double *out, hipStream_t s) {
-  int total = pl.nseg() * nv;
-  hipLaunchKernelGGL(k_reduce, dim3((total + 127) / 128), dim3(128), 0, s, partials, pl.nseg(), pl.splits, nv, out);
-  return hipGetLastError();
-}
-
-hipError_t scratch_address(void **out) {
-  constexpr int kMaxDevices = 64;
-  static std::mutex mu;
-  static void *addr[kMaxDevices] = {};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  std::lock_guard<std::mutex> lock(mu);
-  if (!addr[dev]) {
-    void *p = nullptr;
-    e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (e != hipSuccess) return e;
-    if (!p) return hipErrorInvalidSymbol;
-    addr[dev] = p;
-  }
-  *out = addr[dev];
-  return hipSuccess;
 }
 
 hipError_t launch_psi(const float *z, const float *v, float dt, float *zn, int64_t n, hipStream_t s) {

@@ -102,9 +102,9 @@ struct wdc_state {
   double R = 0, eta = 1;
   int n_s = 0;
   float *rz[3] = {nullptr, nullptr, nullptr};  // current latent, candidate, next exact latent of a rollout
-  float *partials = nullptr;
-  double *d_red = nullptr;
-  double *h_red = nullptr;  // pinned host
+  float *h_part = nullptr;    // pinned host: the blocks' partial sums of the last statistics kernel
+  float *partials = nullptr;  // its device address
+  std::vector<double> red;    // their sums per segment
   std::vector<double> n8;   // element count of each fine segment [C*8]
   // pass-1 statistics [nseg, PRE_NV] of the latent the next step starts from,
   // emitted by the kernel that produced it (observation or exact epilogue);
@@ -725,21 +725,11 @@ void summary_tail(const wdc_state *st, double *s) {
   for (int i = 0; i < GCAM; ++i) s[o + 48 + i] = 0.0;  // depth: unavailable
 }
 
-// Device buffers the statistics kernels write: per-block partial sums and
-// their per-segment float64 reductions (the state's own, or the fixed scratch
-// of the allocation-free entry point).
-struct Scratch {
-  float *part;
-  double *red;
-};
-Scratch own_scratch(wdc_state *st) { return Scratch{st->partials, st->d_red}; }
-
-wdc_status fetch(wdc_state *st, int nv, Scratch sc) {
+// waits for the last statistics kernel (nv values per block) and sums its partials per segment
+wdc_status fetch(wdc_state *st, int nv) {
   wdc_ctx *c = st->ctx;
-  HIPCHK(c, launch_reduce_partials(st->plan, sc.part, nv, sc.red, c->stream));
-  HIPCHK(c, hipMemcpyAsync(st->h_red, sc.red, sizeof(double) * st->plan.nseg() * nv, hipMemcpyDeviceToHost,
-                           c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  reduce_partials(st->plan, st->h_part, nv, st->red.data());
   return WDC_OK;
 }
 
@@ -752,9 +742,8 @@ void log_clear(wdc_step_log *l) {
 
 // Pass 1 + candidate (Eq. (2)-(5)) for step k; keeps it pending in the state.
 // pre: pass-1 statistics of z [nseg, PRE_NV] already at hand, else null (computed here).
-// sc: where the statistics kernels put their partial sums.
 wdc_status surrogate_step(wdc_state *st, const float *z, int k, int S, float *zhat, wdc_step_log *log,
-                          const double *pre, Scratch sc) {
+                          const double *pre) {
   wdc_ctx *c = st->ctx;
   const auto &p = c->p;
   const int nseg = st->plan.nseg();
@@ -762,9 +751,9 @@ wdc_status surrogate_step(wdc_state *st, const float *z, int k, int S, float *zh
   if (!pre) {
     const double bytes = (za ? 8.0 : 4.0) * c->E;
     HIPCHK(c, timed(c, WDC_T_STATS, bytes,
-                    [&] { return launch_stats_pre(st->plan, z, za, sc.part, c->stream); }));
-    CHK(fetch(st, PRE_NV, sc));
-    pre = st->h_red;
+                    [&] { return launch_stats_pre(st->plan, z, za, st->partials, c->stream); }));
+    CHK(fetch(st, PRE_NV));
+    pre = st->red.data();
   }
   std::vector<double> sz(nseg), sd(nseg);
   double qz = 0, qd = 0, ad = 0, aa = 0;
@@ -878,12 +867,12 @@ wdc_status surrogate_step(wdc_state *st, const float *z, int k, int S, float *zh
   for (int i : slots) simm = std::min(simm, std::fabs(sims[i] - p.theta_sim));
   const double obytes = (4.0 * m + 4.0 + (za ? 4.0 : 0.0)) * c->E;
   HIPCHK(c, timed(c, WDC_T_OBSERVE, obytes,
-                  [&] { return launch_observe(st->plan, src, coef, m, za, zhat, sc.part, c->stream); }));
-  CHK(fetch(st, OBS_NV, sc));
+                  [&] { return launch_observe(st->plan, src, coef, m, za, zhat, st->partials, c->stream); }));
+  CHK(fetch(st, OBS_NV));
   double nonfinite = 0;
   st->pre_obs.resize((size_t)nseg * PRE_NV);
   for (int i = 0; i < nseg; ++i) {
-    const double *r = st->h_red + i * OBS_NV;
+    const double *r = st->red.data() + i * OBS_NV;
     for (int j = 0; j < PRE_NV; ++j) st->pre_obs[(size_t)i * PRE_NV + j] = r[j];
     nonfinite += r[PRE_NV];
   }
@@ -960,12 +949,12 @@ wdc_status post_exact(wdc_state *st, const float *z, const float *v, float *zn, 
   const double pbytes = 4.0 * c->E * (2 + a.has_anchor + a.has_zhat + (a.v ? 1 : 0) + 2 + (a.in_slot ? 1 : 0));
   HIPCHK(c, timed(c, WDC_T_EXACT_POST, pbytes,
                   [&] { return launch_exact_post(st->plan, a, st->partials, c->stream); }));
-  CHK(fetch(st, POST_NV, own_scratch(st)));
+  CHK(fetch(st, POST_NV));
   std::vector<double> sn(nseg), sdn(nseg), sdx(nseg);
   double qn = 0, qdn = 0, qdx = 0, acf = 0, an = 0;
   st->pre_post.resize((size_t)nseg * PRE_NV);
   for (int i = 0; i < nseg; ++i) {
-    const double *r = st->h_red + i * POST_NV;
+    const double *r = st->red.data() + i * POST_NV;
     sn[i] = r[0];
     sdn[i] = r[1];
     sdx[i] = r[2];
@@ -1327,11 +1316,8 @@ static int n_latents(const wdc_ctx *ctx) {
 
 size_t wdc_state_bytes(const wdc_ctx *ctx) {
   if (!ctx) return 0;
-  SegPlan pl = make_seg_plan(ctx->d.lat_c, ctx->T, G8);
   size_t lat = (((size_t)ctx->E * 4 + 255) / 256) * 256;
-  size_t part = (((size_t)pl.nblocks() * POST_NV * 4 + 255) / 256) * 256;
-  size_t red = (((size_t)pl.nseg() * POST_NV * 8 + 255) / 256) * 256;
-  return lat * (n_latents(ctx) + 3) + part + red;
+  return lat * (n_latents(ctx) + 3);
 }
 
 wdc_status wdc_state_create(wdc_ctx *ctx, void *d_mem, size_t bytes, wdc_state **out) {
@@ -1356,13 +1342,12 @@ wdc_status wdc_state_create(wdc_ctx *ctx, void *d_mem, size_t bytes, wdc_state *
     for (int i = 0; i < ctx->p.bank_capacity; ++i)
       st->bank_in[i] = (float *)(b + lat * (2 + ctx->p.bank_capacity + i));
   for (int i = 0; i < 3; ++i) st->rz[i] = (float *)(b + lat * (n_latents(ctx) + i));
-  size_t o = lat * (n_latents(ctx) + 3);
-  st->partials = (float *)(b + o);
-  o += (((size_t)st->plan.nblocks() * POST_NV * 4 + 255) / 256) * 256;
-  st->d_red = (double *)(b + o);
-  if (hipHostMalloc((void **)&st->h_red, sizeof(double) * st->plan.nseg() * POST_NV, hipHostMallocDefault) !=
-      hipSuccess) {
-    set_err(ctx, "hipHostMalloc failed");
+  st->red.resize((size_t)st->plan.nseg() * POST_NV);
+  hipError_t e = hipHostMalloc((void **)&st->h_part, sizeof(float) * st->plan.nblocks() * POST_NV, hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&st->partials, st->h_part, 0);
+  if (e != hipSuccess) {
+    set_err(ctx, "pinned host memory for the statistics: %s", hipGetErrorString(e));
+    if (st->h_part) (void)hipHostFree(st->h_part);
     delete st;
     return WDC_E_HIP;
   }
@@ -1385,7 +1370,7 @@ wdc_status wdc_state_reset(wdc_state *st, const float *h_cam) {
 
 wdc_status wdc_state_destroy(wdc_state *st) {
   if (!st) return WDC_E_ARG;
-  if (st->h_red) (void)hipHostFree(st->h_red);
+  if (st->h_part) (void)hipHostFree(st->h_part);
   delete st;
   return WDC_OK;
 }
@@ -1443,27 +1428,16 @@ wdc_status wdc_scheduler_step(wdc_ctx *ctx, const float *d_z, const float *d_v, 
 wdc_status wdc_surrogate_step(wdc_ctx *ctx, wdc_state *st, const float *d_z, int32_t k, int32_t S, float *d_zhat,
                               wdc_step_log *h_log) {
   if (!ctx || !st || st->ctx != ctx || !d_z || !d_zhat || !h_log || S < 1 || k < 0 || k >= S) return WDC_E_ARG;
-  return surrogate_step(st, d_z, k, S, d_zhat, h_log, nullptr, own_scratch(st));
+  return surrogate_step(st, d_z, k, S, d_zhat, h_log, nullptr);
 }
 
 wdc_status wdc_surrogate_step_noalloc(wdc_ctx *ctx, wdc_state *st, const float *d_z, int32_t k, int32_t S,
                                       float *d_zhat, wdc_step_log *h_log) {
   if (!ctx || !st || st->ctx != ctx || !d_z || !d_zhat || !h_log || S < 1 || k < 0 || k >= S) return WDC_E_ARG;
-  // the statistics kernels write OBS_NV values per block at most (pass 1: PRE_NV)
-  const size_t part = (size_t)st->plan.nblocks() * OBS_NV * sizeof(float);
-  const size_t red = (size_t)st->plan.nseg() * OBS_NV * sizeof(double);
-  if (part > kScratchRedOffset || red > kScratchBytes - kScratchRedOffset) {
-    set_err(ctx, "latent needs %zu + %zu bytes of statistics scratch, more than the fixed %zu + %zu", part, red,
-            kScratchRedOffset, kScratchBytes - kScratchRedOffset);
-    return WDC_E_WORKSPACE;
-  }
-  void *p = nullptr;
-  HIPCHK(ctx, scratch_address(&p));
-  const Scratch sc{(float *)p, (double *)((char *)p + kScratchRedOffset)};
   // kernel timing records HIP events, which this entry point does not create
   const bool timing = ctx->timing;
   ctx->timing = false;
-  const wdc_status s = surrogate_step(st, d_z, k, S, d_zhat, h_log, nullptr, sc);
+  const wdc_status s = surrogate_step(st, d_z, k, S, d_zhat, h_log, nullptr);
   ctx->timing = timing;
   return s;
 }
@@ -1523,6 +1497,7 @@ wdc_status wdc_rollout_batch(wdc_ctx *ctx, wdc_state *const *states, int32_t B, 
     wdc_state *st;
     float *zc, *zh, *zn;
     std::vector<double> pre;  // pass-1 statistics of zc, emitted by the kernel that wrote it
+    bool own;                 // no other sample of the call has the same latent
   };
   std::vector<Sample> sm(B);
   for (int b = 0; b < B; ++b) {
@@ -1536,8 +1511,9 @@ wdc_status wdc_rollout_batch(wdc_ctx *ctx, wdc_state *const *states, int32_t B, 
       HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     }
     state_reset(st, cam.empty() ? nullptr : cam.data());
-    sm[b] = Sample{st, st->rz[0], st->rz[1], st->rz[2], {}};
-    HIPCHK(ctx, hipMemcpyAsync(sm[b].zc, d_z[b], bytes, hipMemcpyDeviceToDevice, ctx->stream));
+    // The first step reads the caller's latent where it is; it is written by the
+    // last step only (as the candidate's buffer, or by a copy at the end).
+    sm[b] = Sample{st, d_z[b], st->rz[1], st->rz[2], {}, std::count(d_z, d_z + B, d_z[b]) == 1};
   }
   wdc_step_log tmp;
   std::vector<int> ex;
@@ -1549,11 +1525,13 @@ wdc_status wdc_rollout_batch(wdc_ctx *ctx, wdc_state *const *states, int32_t B, 
     for (int b = 0; b < B; ++b) {
       Sample &q = sm[b];
       wdc_step_log *lg = h_log ? &h_log[(size_t)b * S + k] : &tmp;
-      CHK(surrogate_step(q.st, q.zc, k, S, q.zh, lg, k > 0 ? q.pre.data() : nullptr, own_scratch(q.st)));
+      if (k == S - 1 && q.zc != d_z[b] && q.own) q.zh = d_z[b];
+      CHK(surrogate_step(q.st, q.zc, k, S, q.zh, lg, k > 0 ? q.pre.data() : nullptr));
       pre_decision(q.st, k, S, mode, h_forced ? h_forced[(size_t)b * S + k] : 0, lg);
       if (q.st->pend_surrogate) {
         post_surrogate(q.st, lg);
         std::swap(q.zc, q.zh);
+        if (q.zh == d_z[b]) q.zh = q.st->rz[0];
         q.pre.swap(q.st->pre_obs);
         h_schedule[(size_t)b * S + k] = 1;
       } else {
@@ -1586,10 +1564,13 @@ wdc_status wdc_rollout_batch(wdc_ctx *ctx, wdc_state *const *states, int32_t B, 
       const float *v = d_replay_v ? d_replay_v[b] + (size_t)k * ctx->E : ctx->r_v + j * ctx->E;
       CHK(post_exact(q.st, q.zc, v, q.zn, k, S, lg));
       std::swap(q.zc, q.zn);
+      if (q.zn == d_z[b]) q.zn = q.st->rz[0];
       q.pre.swap(q.st->pre_post);
     }
   }
-  for (int b = 0; b < B; ++b) HIPCHK(ctx, hipMemcpyAsync(d_z[b], sm[b].zc, bytes, hipMemcpyDeviceToDevice, ctx->stream));
+  for (int b = 0; b < B; ++b)
+    if (sm[b].zc != d_z[b])
+      HIPCHK(ctx, hipMemcpyAsync(d_z[b], sm[b].zc, bytes, hipMemcpyDeviceToDevice, ctx->stream));
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   return WDC_OK;
 }

@@ -1,0 +1,50 @@
+"""Statistics kernels of the surrogate at the edges of their slice plan, and
+the rollout's use of the caller's latent, against the oracle (GPU)."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import params as P
+from oracle import rollout as ro
+from tests.gpu_util import context, rel_l2, torch_cuda, wdc_params
+from tests.test_gpu_variants import compare, run_variant
+
+pytestmark = pytest.mark.gpu
+
+
+def _cfg(t):
+    """A latent of 16 channels x t positions (no blocks: surrogate-only use)."""
+    return synth.ModelConfig(name=f"t{t}", dtype="f32", hidden=256, heads=4, head_dim=64, latent=(16, 1, 1, t),
+                             patch=(1, 1, t), rope=(0, 0, 0), steps=10, seed=17)
+
+
+# segments (t / 8 positions) of one element and remainders, one slice, the last
+# length of four 256-thread slices and the first of 1,024-thread ones, several of those
+@pytest.mark.parametrize("t,overrides", [
+    (9, {}), (8 * 61 + 3, {"bank_capacity": 8}), (8 * 4096 + 1, {"bank_capacity": 1}),
+    (8 * 16384, {"observation": "linear", "bank_capacity": 3}), (8 * 16384 + 5, {"bank_capacity": 5}),
+    (8 * 40000 + 7, {"surrogate": "secant"})])
+def test_replay_rollout_at_slice_edges(t, overrides):
+    run_variant(_cfg(t), 10, {"period": 3, **overrides}, "periodic")
+
+
+@pytest.mark.parametrize("steps,forced", [
+    (1, [0]), (2, [0, 0]), (2, [0, 1]), (3, [0, 1, 1]), (5, [0, 0, 1, 1, 0]), (6, [0, 1, 0, 1, 0, 1])])
+def test_rollout_writes_the_callers_latent_only_at_the_end(steps, forced):
+    """Every way the last step can end (exact or surrogate, from the caller's
+    latent or the library's), twice on one state: the second rollout starts
+    from the first one's result."""
+    torch = torch_cuda()
+    cfg = _cfg(8 * 50 + 2)
+    p = P.with_(P.DEFAULTS, theta_q=1.0, theta_sim=-1.0)
+    vel = synth.gen_replay_velocities(cfg, steps)
+    ctx = context(cfg, weights=False, params=wdc_params(p))
+    st, z, ref_z = ctx.new_state(), None, synth.gen_inputs(cfg)["z_T"]
+    z = torch.from_numpy(ref_z).cuda()
+    for _ in range(2):
+        ref = ro.rollout(ro.replay_denoiser(vel), ref_z, steps, p, mode="forced", forced=forced)
+        sched, logs = ctx.rollout(st, z, steps, mode=1, forced=forced, replay_v=torch.from_numpy(vel).cuda())
+        assert sched == ref.schedule == forced
+        compare(logs, ref.log)
+        assert rel_l2(z.cpu().numpy(), ref.z) <= 1e-5
+        ref_z = z.cpu().numpy()
