@@ -11,13 +11,16 @@
 // one read at a time between its MFMAs, and the stage barrier sits before a
 // stage's last k-step so the matrix cores never drain at it. Large single
 // products take an XCD-aware block order, and long-K ones whose last dispatch
-// round would be thin run their last rows as a second launch of 128 x 128 tiles;
+// round would be thin run their last rows as a second launch of smaller tiles;
 // products too small to fill one dispatch round of 256 x 256 tiles run on
-// 128 x 128 tiles throughout (128 x 64 when even those would not fill it).
+// smaller ones throughout, with three or four LDS buffers where one block per
+// compute unit has to hide its own loads (launch_small).
 // float32 products run on the matrix cores too (gemm_f32.hip). Shapes that
 // neither covers (K not a multiple of 32 or 64, unaligned operands): a plain
 // LDS-tiled FMA kernel.
 #include "common.h"
+
+#include <algorithm>
 
 namespace wdc {
 
@@ -121,7 +124,7 @@ __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, char *lds, 
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)lds, 16, voff, soff, 0, 0);
 }
 
-template <int BM, int BN, int WM, int WN>
+template <int BM, int BN, int WM, int WN, int NB = 2>
 struct Cfg {
   static constexpr int NT = 64 * WM * WN;       // threads
   static constexpr int TM = BM / WM / 32;       // 32x32 tiles per wave along M
@@ -131,7 +134,7 @@ struct Cfg {
   static constexpr int LW = NT / 64 >= 4 ? 4 : NT / 64;
   static constexpr int A_CHUNKS = BM * 8 / (64 * LW);  // 1 KB stripes per loading wave per stage
   static constexpr int B_CHUNKS = BN * 8 / (64 * LW);
-  static constexpr int LDS_BYTES = 2 * (BM + BN) * BK * 2;
+  static constexpr int LDS_BYTES = NB * (BM + BN) * BK * 2;
 };
 
 // Each tile row is 8 chunks of 16 bytes (128 B, two rows per 256-byte span of
@@ -342,9 +345,9 @@ __device__ __forceinline__ void v_scatter(const GemmArgs &g, const char *smem, i
   }
 }
 
-template <int BM, int BN, int WM, int WN, int EPI>
+template <int BM, int BN, int WM, int WN, int EPI, int NB = 2>
 __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
-  using C = Cfg<BM, BN, WM, WN>;
+  using C = Cfg<BM, BN, WM, WN, NB>;
   // bf16 outputs: compute C^T tiles (weight fragment as the MFMA A operand) so a
   // lane holds 4 consecutive columns of one row (8-byte stores); float32 outputs
   // keep C tiles, whose lanes cover 32 consecutive columns of two rows (a full
@@ -355,8 +358,8 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
   constexpr bool STAGE_OUT = BM == 256;   // bf16 output through LDS, whole-line non-temporal stores
   const GemmArgs g = batch_entry<bf16_t>(g0);
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  char *sA = smem;                      // [2][BM][128 B]
-  char *sB = smem + 2 * BM * BK * 2;    // [2][BN][128 B]
+  char *sA = smem;                      // [NB][BM][128 B]
+  char *sB = smem + NB * BM * BK * 2;   // [NB][BN][128 B]
 
   // Tile order: a group of 8 consecutive M tiles walks all N tiles, so blocks
   // running at once share A rows and the weight panel in L2.
@@ -470,10 +473,11 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
   // Stages 0 and 1 fill both buffers; stage 0 is complete once no more than
   // stage 1's loads are pending (a wave's memory operations complete in issue
   // order).
-  WDC_GEMM_LOAD(0, 0);
-  if (nk > 1) WDC_GEMM_LOAD(1, 1);
+#pragma unroll
+  for (int st = 0; st < NB; ++st)
+    if (st < nk) WDC_GEMM_LOAD(st, st);
   if (wu < NW) {
-    if (nk > 1) __builtin_amdgcn_s_waitcnt(vm_wait(SL));
+    if (nk >= NB) __builtin_amdgcn_s_waitcnt(vm_wait((NB - 1) * SL));
     else __builtin_amdgcn_s_waitcnt(WAIT_VM0);
   }
   WDC_GEMM_BARRIER();
@@ -558,20 +562,84 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
     }                                                                                              \
     (void)v_;                                                                                      \
   }
+  if constexpr (NQ <= 4) {
+    // Wave tiles of up to 64 x 64: a k-step is only 64 to 128 cycles of MFMAs,
+    // less than an LDS read takes, so the fragments are read two k-steps ahead
+    // (four sets, one per k-step) and early in a step. The stage barrier then
+    // sits before the third k-step, whose fragments and the fourth's are in
+    // registers by then.
+    bf16x8 fa[S][C::TM], fb[S][C::TN];
+    WDC_GEMM_READ(fa[0], fb[0], 0, 0);
+    WDC_GEMM_READ(fa[1], fb[1], 0, 1);
+    int buf = 0, prv = NB - 1, v2_ = va0;
+    for (int kt = 0; kt < nk; ++kt) {
+      const int nxt = NB == 2 ? buf ^ 1 : buf + 1 == NB ? 0 : buf + 1;
+#pragma unroll
+      for (int st = 0; st < S; ++st) {
+        if (st == 2) {
+          if (wu < NW) {
+            if (NB > 2 && kt + NB <= nk) __builtin_amdgcn_s_waitcnt(vm_wait((NB - 2) * SL));
+            else __builtin_amdgcn_s_waitcnt(WAIT_VM0);
+          }
+          WDC_GEMM_BARRIER();
+        }
+        // the stage NB ahead goes into the buffer that the barrier freed: with
+        // 64 x 64 wave tiles its loads are spread over the four k-steps from one
+        // barrier to the next (a burst stalls the wave that issues it: 2,688 x
+        // 4,096, K = 1,024 on 256 x 128 tiles 30.8 us against 32.2), with smaller
+        // ones, bound by the loads' latency, over the first two (226 x 3,072,
+        // K = 4,096 on 64 x 64 tiles 19.4 against 21.4)
+        constexpr int LSTEPS = NQ == 4 ? S : 2;
+        const int lkt = st >= 2 ? kt + NB : kt + NB - 1, lbuf = st >= 2 ? buf : prv, lst = (st + 2) % S;
+        const bool ld = lst < LSTEPS && lkt < nk && lkt >= NB && wu < NW;
+        const int rs = (st + 2) % S, rbuf = st < 2 ? buf : nxt;
+        if (st == 2) v2_ = va0;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          WDC_GEMM_MFMA1(fa[st], fb[st], q);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int r = 0; r < NR; ++r)
+            if (r * NQ / (2 * NR) == q) {
+              WDC_GEMM_READ1(fa[rs], fb[rs], rbuf, rs, r);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          if (ld) {
+#pragma unroll
+            for (int l = 0; l < SL; ++l)
+              if (l * LSTEPS * NQ / SL == lst * NQ + q) {
+                int v_ = v2_;
+                WDC_GEMM_LOAD1(lbuf, lkt, l);
+                v2_ = v_;
+              }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      prv = buf;
+      buf = nxt;
+    }
+  } else {
   bf16x8 xa[C::TM], xb[C::TN], ya[C::TM], yb[C::TN];
-  WDC_GEMM_READ(xa, xb, 0, 0);
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    WDC_GEMM_STEP(xa, xb, ya, yb, buf, 1, true, 0, 0, false);
-    WDC_GEMM_STEP(ya, yb, xa, xb, buf, 2, true, 0, 0, false);
-    WDC_GEMM_STEP(xa, xb, ya, yb, buf, 3, true, 0, 0, false);
-    // stage kt+1 was requested a stage ago; after the barrier every wave's
-    // reads of buffer buf are complete. The last stage's step also reads the
-    // other buffer's first fragments: stale data, never used.
-    if (wu < NW) __builtin_amdgcn_s_waitcnt(WAIT_VM0);
-    WDC_GEMM_BARRIER();
-    const bool ld = kt + 2 < nk && wu < NW;
-    WDC_GEMM_STEP(ya, yb, xa, xb, buf ^ 1, 0, true, buf, kt + 2, ld);
+    WDC_GEMM_READ(xa, xb, 0, 0);
+    int buf = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+      const int nxt = NB == 2 ? buf ^ 1 : buf + 1 == NB ? 0 : buf + 1;
+      WDC_GEMM_STEP(xa, xb, ya, yb, buf, 1, true, 0, 0, false);
+      WDC_GEMM_STEP(ya, yb, xa, xb, buf, 2, true, 0, 0, false);
+      WDC_GEMM_STEP(xa, xb, ya, yb, buf, 3, true, 0, 0, false);
+      // stage kt+1 was requested a stage ago; after the barrier every wave's
+      // reads of buffer buf are complete. The last stage's step also reads the
+      // other buffer's first fragments: stale data, never used.
+      if (wu < NW) {
+        if (NB > 2 && kt + NB <= nk) __builtin_amdgcn_s_waitcnt(vm_wait((NB - 2) * SL));
+        else __builtin_amdgcn_s_waitcnt(WAIT_VM0);
+      }
+      WDC_GEMM_BARRIER();
+      const bool ld = kt + NB < nk && wu < NW;
+      WDC_GEMM_STEP(ya, yb, xa, xb, nxt, 0, true, buf, kt + NB, ld);
+      buf = nxt;
+    }
   }
 #undef WDC_GEMM_STEP
 #undef WDC_GEMM_LOAD1
@@ -735,9 +803,9 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
 #undef WDC_GEMM_LOAD
 }
 
-template <int BM, int BN, int WM, int WN>
+template <int BM, int BN, int WM, int WN, int NB = 2>
 hipError_t launch_mfma(const GemmArgs &g0, hipStream_t s) {
-  using C = Cfg<BM, BN, WM, WN>;
+  using C = Cfg<BM, BN, WM, WN, NB>;
   GemmArgs g = g0;
   const int m_tiles = (int)((g.m + BM - 1) / BM), n_tiles = (int)(g.n / BN);
   // The rectangle order pays on large single products; a z-batch would put every
@@ -757,36 +825,36 @@ hipError_t launch_mfma(const GemmArgs &g0, hipStream_t s) {
   if (g.order == 1) blocks = (chunks + 7) / 8 * 256;
   dim3 grid(blocks, 1, g.batch > 1 ? g.batch : 1), block(C::NT);
   switch (g.epi) {
-    case EPI_STORE: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_STORE>), grid, block, C::LDS_BYTES, s, g); break;
-    case EPI_GELU: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GELU>), grid, block, C::LDS_BYTES, s, g); break;
-    case EPI_GATE_RES: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES>), grid, block, C::LDS_BYTES, s, g); break;
-    case EPI_GATE_RES_NT: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES_NT>), grid, block, C::LDS_BYTES, s, g); break;
+    case EPI_STORE: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_STORE, NB>), grid, block, C::LDS_BYTES, s, g); break;
+    case EPI_GELU: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GELU, NB>), grid, block, C::LDS_BYTES, s, g); break;
+    case EPI_GATE_RES: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES, NB>), grid, block, C::LDS_BYTES, s, g); break;
+    case EPI_GATE_RES_NT: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES_NT, NB>), grid, block, C::LDS_BYTES, s, g); break;
     case EPI_QKV:
       if constexpr (BM == 256 && BN == 256 && WM == 2 && WN == 4) {
-        hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_QKV>), grid, block, C::LDS_BYTES, s, g);
+        hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_QKV, NB>), grid, block, C::LDS_BYTES, s, g);
         break;
       } else {
         return hipErrorInvalidValue;
       }
-    default: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_STORE_F32>), grid, block, C::LDS_BYTES, s, g); break;
+    default: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_STORE_F32, NB>), grid, block, C::LDS_BYTES, s, g); break;
   }
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN>
+template <int BM, int BN, int WM, int WN, int NB = 2>
 hipError_t set_lds_limit() {
-  using C = Cfg<BM, BN, WM, WN>;
-  const void *k[5] = {(const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_STORE>,
-                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GELU>,
-                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES>,
-                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES_NT>,
-                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_STORE_F32>};
+  using C = Cfg<BM, BN, WM, WN, NB>;
+  const void *k[5] = {(const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_STORE, NB>,
+                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GELU, NB>,
+                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES, NB>,
+                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES_NT, NB>,
+                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_STORE_F32, NB>};
   for (const void *f : k) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
     if (e != hipSuccess) return e;
   }
   if constexpr (BM == 256 && BN == 256 && WM == 2 && WN == 4)
-    return hipFuncSetAttribute((const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_QKV>,
+    return hipFuncSetAttribute((const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_QKV, NB>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
   return hipSuccess;
 }
@@ -797,8 +865,47 @@ bool operands_aligned(const GemmArgs &g) {
          (g.batch <= 1 || (g.a_bs % 8 == 0 && g.c_bs % 4 == 0 && g.gate_bs % 4 == 0));
 }
 
+int64_t tile_count(const GemmArgs &g, int bm, int bn) {
+  return (g.m + bm - 1) / bm * (g.n / bn) * (g.batch > 1 ? g.batch : 1);
+}
+
+// Tile shape of a product too small for the 256 x 256 tiles (n % 64 == 0).
+// Measured per 64-deep K stage (microseconds a compute unit takes for the
+// blocks it holds) and per round, the products alone on the device:
+//   64 x 64, 3 buffers: 0.30 for one block, 0.45 for two, 0.64 for three
+//   128 x 128, 4 buffers, one block: 0.43 on 48 CUs, 0.53 on 168
+//   128 x 128, 2 buffers, two blocks: 0.95
+//   256 x 128, 3 buffers, 8 waves of 64 x 64, one block: 0.78
+// so: 64 x 64 while they do not fill the device (226 x 3,072, K = 4,096: 19.4 us
+// against 36.7 on 128 x 64; 256 x 3,072, K = 12,288: 55 against 104), then 128 x
+// 128 one per CU (256 x 9,216, K = 3,072: 26.3 against 34.6 with two buffers;
+// 2,688 x 1,024, K = 4,096: 37.7 against 41.3 on 128 x 64), then the cheaper of
+// two 128 x 128 blocks per CU (2,688 x 3,072, K = 1,024: 24.6 us) and 256 x 128
+// (2,688 x 4,096, K = 1,024: 30.8 against 34.9; 5,000 x 1,536, K = 1,536: 24.4
+// against 29.7). 256 x 128 needs 16-byte output rows.
+hipError_t launch_small(const GemmArgs &g, bool out16, hipStream_t s) {
+  const int64_t cus = device_cus() > 0 ? device_cus() : 256;
+  const int64_t t64 = tile_count(g, 64, 64);
+  if (t64 <= cus) return launch_mfma<64, 64, 2, 2, 3>(g, s);
+  if (g.n % 128 != 0) {   // narrow outputs (the output head: n = 64 latent values per token)
+    if (t64 <= 3 * cus) return launch_mfma<64, 64, 2, 2, 3>(g, s);
+    return launch_mfma<128, 64, 2, 2>(g, s);
+  }
+  const int64_t t128 = tile_count(g, 128, 128), t256 = tile_count(g, 256, 128);
+  if (t128 <= cus) return launch_mfma<128, 128, 2, 2, 4>(g, s);
+  // rounds of two 128 x 128 blocks per CU (and a last one of single blocks)
+  // against rounds of 256 x 128 blocks: stage time x stages + the prologue and
+  // epilogue of a round, which nothing overlaps
+  const int64_t rest = t128 % (2 * cus);
+  const double st = (double)(g.k / BK), pair = 0.95 * st + 9.4, single = 0.55 * st + 4.0;
+  const double c128 = pair * (double)(t128 / (2 * cus)) + (rest == 0 ? 0.0 : rest <= cus ? single : pair);
+  const double c256 = (0.78 * st + 3.0) * (double)((t256 + cus - 1) / cus);
+  if (out16 && c256 <= c128) return launch_mfma<256, 128, 4, 2, 3>(g, s);
+  return launch_mfma<128, 128, 2, 2>(g, s);
+}
+
 // products on fewer 256 x 256 tiles than the device has compute units take
-// 128 x 128 tiles when the caller allows it (GemmArgs::fill_tiles)
+// smaller tiles when the caller allows it (GemmArgs::fill_tiles)
 bool small_product(const GemmArgs &g) {
   const int64_t tiles = (g.m + 255) / 256 * (g.n / 256) * (g.batch > 1 ? g.batch : 1);
   return g.fill_tiles && g.n % 128 == 0 && tiles < device_cus();
@@ -824,8 +931,11 @@ hipError_t launch_gemm(int dtype, const GemmArgs &g_in, hipStream_t s) {
     static bool seen[64] = {};
     if (first_on_device(seen)) {
       hipError_t e = set_lds_limit<256, 256, 2, 4>();
+      if (e == hipSuccess) e = set_lds_limit<256, 128, 4, 2, 3>();
       if (e == hipSuccess) e = set_lds_limit<128, 128, 2, 2>();
+      if (e == hipSuccess) e = set_lds_limit<128, 128, 2, 2, 4>();
       if (e == hipSuccess) e = set_lds_limit<128, 64, 2, 2>();
+      if (e == hipSuccess) e = set_lds_limit<64, 64, 2, 2, 3>();
       if (e != hipSuccess) return e;
     }
     // 256 x 256 block tiles: 8 waves of 128 x 64 (two per SIMD). With the reads
@@ -844,27 +954,20 @@ hipError_t launch_gemm(int dtype, const GemmArgs &g_in, hipStream_t s) {
     const bool c16 = g.epi == EPI_STORE || g.epi == EPI_GELU;
     const bool out16 = !c16 || ((uintptr_t)g.c % 16 == 0 && g.ldc % 8 == 0 && (g.batch <= 1 || g.c_bs % 8 == 0));
     if (g.epi == EPI_QKV) return launch_mfma<256, 256, 2, 4>(g, s);
-    // A product that would leave compute units idle in its only dispatch round
-    // (the mid-size model's products: 44 to 176 tiles of 256 x 256) runs four
-    // times the blocks on 128 x 128 tiles: 17% off the mid-size forward, whose
-    // q/k/v projection then takes the separate preparation kernels. One that
-    // would still leave CUs idle on 128 x 128 tiles (its N = 1,024 products:
-    // 168 tiles) runs on 128 x 64 tiles, up to two blocks per CU: 5.7% off the
-    // mid-size forward's products. Every output is summed over K in the same
-    // order on any tile shape, so the results are the same bits.
-    if (small_product(g)) {
-      const int64_t t128 = (g.m + 127) / 128 * (g.n / 128) * (g.batch > 1 ? g.batch : 1);
-      if (t128 < device_cus()) return launch_mfma<128, 64, 2, 2>(g, s);
-      return launch_mfma<128, 128, 2, 2>(g, s);
-    }
+    // A product that would leave compute units idle in its only dispatch round of
+    // 256 x 256 tiles (the mid-size model's products: 44 to 176 of them) runs on
+    // smaller ones, and its q/k/v projection takes the separate preparation
+    // kernels. Every output is summed over K in the same order on any tile shape,
+    // so the results are the same bits.
+    if (small_product(g)) return launch_small(g, out16, s);
     if (g.n % 256 == 0 && g.m >= 512 && out16) {
       // Tail split for a single large long-K product on a 256-CU device: the
       // rows whose 256 x 256 tiles fill whole dispatch rounds (m1 tiles, a
       // multiple of 256 / gcd(n_tiles, 256)) run as above; the remaining rows,
       // which would leave most CUs idle in a last round at most half full, run
-      // as 128 x 128 tiles (two blocks per CU). At M = 67,576 and N = 3,072 that
+      // on smaller tiles. At M = 67,576 and N = 3,072 that
       // turns 12.375 rounds into 12 plus 2,040 rows: +1.5% at K = 12,288, +2% at
-      // K = 15,360; at K = 3,072 the small tiles' lower efficiency costs more
+      // K = 15,360 (with 128 x 128 tiles); at K = 3,072 the small tiles' lower efficiency costs more
       // than the idle CUs (-1.3%), so short products keep one launch.
       const int64_t m_tiles = (g.m + 255) / 256, n_tiles = g.n / 256;
       int64_t gcd = n_tiles, r = 256;
@@ -879,13 +982,11 @@ hipError_t launch_gemm(int dtype, const GemmArgs &g_in, hipStream_t s) {
         g2.c = c16 ? (void *)((bf16_t *)g.c + m1 * g.ldc) : (void *)((float *)g.c + m1 * g.ldc);
         hipError_t e = big(g1);
         if (e != hipSuccess) return e;
-        return launch_mfma<128, 128, 2, 2>(g2, s);
+        return launch_small(g2, out16, s);
       }
       return big(g);
     }
-    if (g.n % 128 == 0) return launch_mfma<128, 128, 2, 2>(g, s);
-    // narrow outputs (the output head: n = 64 latent values per token)
-    if (g.n % 64 == 0) return launch_mfma<128, 64, 2, 2>(g, s);
+    if (g.n % 64 == 0) return launch_small(g, out16, s);
   }
   if (dtype == 0 && gemm_f32_mfma(g)) return launch_gemm_f32(g, s);
   dim3 grid((unsigned)((g.n + 63) / 64), (unsigned)((g.m + 63) / 64), g.batch > 1 ? g.batch : 1), block(256);

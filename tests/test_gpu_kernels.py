@@ -313,3 +313,29 @@ def test_forward_batch_several_blocks_of_each_kind_match_oracle():
         err = rel_l2(outs[b].cpu().numpy(), ref)
         print("sample", b, err)
         assert err <= TOL_F32
+
+
+# (m, n, k, ldc padding): 64 x 64 tiles with 1, 2, 3 and 4 K stages in three
+# buffers; 128 x 128 with 1 to 5 stages in four; 256 x 128 with partial last rows;
+# two 128 x 128 blocks per compute unit; narrow outputs on 64 x 64 and 128 x 64;
+# 128 x 128 in place of 256 x 128 where output rows are not 16-byte aligned
+@pytest.mark.parametrize("m,n,k,pad", [
+    (1, 64, 64, 0), (65, 192, 128, 0), (63, 128, 192, 8), (130, 320, 256, 0), (1500, 1024, 64, 0), (1409, 1152, 192, 0),
+    (1500, 1024, 256, 8), (1300, 896, 320, 0), (4900, 1536, 64, 0), (4993, 1536, 256, 8), (4993, 1536, 192, 4),
+    (2600, 3072, 448, 0), (5001, 64, 128, 0), (49500, 64, 64, 0)])
+def test_linear_bf16_small_tiles_match_oracle(m, n, k, pad):
+    torch = torch_cuda()
+    cfg = synth.get_config("mid")
+    ctx = context(cfg, weights=False)
+    rng = _rng(m + 3 * n + k)
+    a, w, b = (synth.stored(rng.standard_normal(s, dtype=np.float32) * f, "bf16")
+               for s, f in (((m, k), 1.0), ((n, k), 0.05), ((n,), 0.1)))
+    out = torch.full((m, n + pad), 7.0, dtype=torch.bfloat16, device="cuda")
+    ctx.linear(ctx.to_device(a), ctx.to_device(w), ctx.to_device(b), out, m, n, k, ldc=n + pad)
+    got = out.float().cpu().numpy()
+    ref = dit.linear({"l.w": w, "l.b": b}, "l", a.astype(np.float64))
+    err, rerr = rel_l2(got[:, :n], ref), row_rel_l2(got[:, :n], ref)
+    print(f"{m}x{n}x{k}: rel_l2 {err:.2e}, worst row {rerr:.2e}")
+    # bf16 output rounding: at most 2^-9 of each element
+    assert err <= 4e-3 and rerr <= ROW_TOL_LINEAR_BF16
+    assert (got[:, n:] == 7.0).all()
