@@ -217,6 +217,8 @@ struct QKVPrepArgs {
   int heads, hd, d;       // d = heads*hd; q at columns [0,d), k [d,2d), v [2d,3d)
   int qk_norm;
   const float2 *rope;     // [n_video, hd/2] (cos, sin) or null
+  int nb;                 // samples; source and destination strides in elements
+  int64_t src_bs, dst_bs;
 };
 hipError_t launch_qkv_prep(int dtype, const QKVPrepArgs &a, hipStream_t s);
 // zero rows [n, n_pad) of q, k and the matching columns of v

@@ -55,10 +55,22 @@ __global__ __launch_bounds__(256) void k_ln_mod(const float *__restrict__ x, int
 }
 
 // ---------------------------------------------------------------- q/k preparation
+// Sample blockIdx.z of a batched preparation: shifted source and destinations
+template <typename T>
+__device__ __forceinline__ void prep_sample(QKVPrepArgs &a) {
+  const int64_t z = blockIdx.z;
+  a.src = (const T *)a.src + z * a.src_bs;
+  a.q = (T *)a.q + z * a.dst_bs;
+  a.k = (T *)a.k + z * a.dst_bs;
+  a.v = (T *)a.v + z * a.dst_bs;
+}
+
 // One thread per rotary pair (2p, 2p+1) of one head of one row. The hd/2
 // threads of a head sit in one wavefront, so the RMS reduction is a shuffle.
+// float32: v, whose layout is the same, goes along.
 template <typename T, int HALF>
 __global__ __launch_bounds__(256) void k_qk_prep(QKVPrepArgs a) {
+  prep_sample<T>(a);
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int p = (int)(gid % HALF);
   const int64_t rh = gid / HALF;
@@ -99,18 +111,10 @@ __global__ __launch_bounds__(256) void k_qk_prep(QKVPrepArgs a) {
   st<T>((T *)a.q + o + 1, q1);
   st<T>((T *)a.k + o, k0);
   st<T>((T *)a.k + o + 1, k1);
-}
-
-// v rows -> [H, n_pad, hd] (float32 attention path)
-template <typename T>
-__global__ __launch_bounds__(256) void k_v_copy(QKVPrepArgs a) {
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int c = (int)(gid % a.d);
-  const int64_t r = gid / a.d;
-  if (r >= a.rows) return;
-  const int h = c / a.hd, e = c % a.hd;
-  const T *src = (const T *)a.src + r * a.ld + 2 * a.d + c;
-  ((T *)a.v)[((int64_t)h * a.n_pad + a.row0 + r) * a.hd + e] = *src;
+  if constexpr (sizeof(T) == 4) {
+    ((T *)a.v)[o] = src[2 * a.d];
+    ((T *)a.v)[o + 1] = src[2 * a.d + 1];
+  }
 }
 
 // Position of key j in a V^T row: inside each aligned group of 16 keys the
@@ -122,6 +126,7 @@ __device__ __forceinline__ int64_t vt_pos(int64_t j) { return (j & ~(int64_t)12)
 // the reads (rows of the projection output) and the writes (runs of 64 tokens)
 // are coalesced.
 __global__ __launch_bounds__(256) void k_v_transpose(QKVPrepArgs a) {
+  prep_sample<bf16_t>(a);
   __shared__ bf16_t tile[64][128 + 2];
   const int h = blockIdx.y;
   const int64_t r0 = (int64_t)blockIdx.x * 64;
@@ -170,10 +175,10 @@ __device__ __forceinline__ uint4 pack8(const float (&x)[8]) {
 // (No fused multiply-adds in the norm and rotation arithmetic, here and in the
 // GEMM's fused q/k epilogue, so both give the same bits.)
 template <int HD>
-__global__ __launch_bounds__(256) void k_qk_prep8(QKVPrepArgs a) {
+__device__ __forceinline__ void qk_prep8(const QKVPrepArgs &a, int64_t block) {
 #pragma clang fp contract(off)
   constexpr int TPH = HD / 8;              // threads per head row
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t gid = block * 256 + threadIdx.x;
   const int c = (int)(gid % TPH);
   const int64_t rh = gid / TPH;
   const int h = (int)(rh % a.heads);
@@ -230,10 +235,8 @@ __global__ __launch_bounds__(256) void k_qk_prep8(QKVPrepArgs a) {
 // inverse). Groups of 16 with rows missing are written element by element,
 // valid tokens only (their other positions are padding, zeroed separately).
 template <int HD>
-__global__ __launch_bounds__(256) void k_v_transpose8(QKVPrepArgs a) {
+__device__ __forceinline__ void v_transpose8(const QKVPrepArgs &a, int64_t r0, int h) {
   __shared__ __attribute__((aligned(16))) bf16_t tile[64][HD + 8];
-  const int h = blockIdx.y;
-  const int64_t r0 = (int64_t)blockIdx.x * 64;
   for (int idx = threadIdx.x; idx < 64 * (HD / 8); idx += 256) {
     const int rr = idx / (HD / 8), c = idx % (HD / 8);
     const int64_t r = r0 + rr;
@@ -263,22 +266,39 @@ __global__ __launch_bounds__(256) void k_v_transpose8(QKVPrepArgs a) {
   }
 }
 
-template <typename T>
-__global__ void k_qkv_pad(T *q, T *k, T *v, int heads, int hd, int64_t n, int64_t n_pad, int v_transposed) {
-  const int64_t tail = n_pad - n;
-  const int64_t total = (int64_t)heads * tail * hd;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    int e = (int)(i % hd);
-    int64_t rt = (i / hd) % tail;
-    int h = (int)(i / ((int64_t)hd * tail));
-    int64_t row = n + rt;
-    int64_t o = ((int64_t)h * n_pad + row) * hd + e;
-    q[o] = 0;
-    k[o] = 0;
-    if (v_transposed)
-      v[((int64_t)h * hd + e) * n_pad + vt_pos(row)] = 0;
-    else
-      v[o] = 0;
+// q, k and v of all samples in one launch: the first qk_blocks blocks of a
+// sample take q and k, the others one 64-row tile of one head of v each.
+template <int HD>
+__global__ __launch_bounds__(256) void k_qkv_prep8(QKVPrepArgs a, int qk_blocks) {
+  prep_sample<bf16_t>(a);
+  if ((int)blockIdx.x < qk_blocks) {
+    qk_prep8<HD>(a, blockIdx.x);
+  } else {
+    const int b = (int)blockIdx.x - qk_blocks;
+    v_transpose8<HD>(a, (int64_t)(b / a.heads) * 64, b % a.heads);
+  }
+}
+
+// Zero rows (keys) [n, n_pad) of head blockIdx.x of q (blockIdx.y 0), k (1) or v
+// (2). Rows of q, k and a row-major v are one contiguous run per head; of V^T
+// each feature row has the keys of the group of 16 that n falls in, at their
+// permuted positions, then a contiguous run.
+template <typename T, bool VT>
+__global__ __launch_bounds__(256) void k_qkv_pad(T *q, T *k, T *v, int hd, int64_t n, int64_t n_pad) {
+  T *p = (blockIdx.y == 0 ? q : blockIdx.y == 1 ? k : v) + (int64_t)blockIdx.x * n_pad * hd;
+  constexpr int V = 16 / sizeof(T);
+  const uint4 zero = make_uint4(0, 0, 0, 0);
+  if (!VT || blockIdx.y < 2) {
+    uint4 *p4 = (uint4 *)(p + n * hd);     // hd is a multiple of V
+    for (int64_t i = threadIdx.x; i < (n_pad - n) * hd / V; i += 256) p4[i] = zero;
+    return;
+  }
+  const int64_t g = min((n + 15) / 16 * 16, n_pad);
+  for (int e = threadIdx.x >> 4; e < hd; e += 16) {
+    T *row = p + e * n_pad;
+    const int64_t j = g - 16 + (threadIdx.x & 15);
+    if (j >= n) row[vt_pos(j)] = 0;
+    for (int64_t i = g + V * (threadIdx.x & 15); i < n_pad; i += 16 * V) *(uint4 *)(row + i) = zero;
   }
 }
 
@@ -615,57 +635,52 @@ hipError_t launch_ln_mod(int dtype, const float *x, int64_t ldx, void *h, int64_
 }
 
 hipError_t launch_qkv_prep(int dtype, const QKVPrepArgs &a, hipStream_t s) {
-  if (a.rows <= 0) return hipSuccess;
+  if (a.rows <= 0 || a.nb <= 0) return hipSuccess;
   if (a.hd != 64 && a.hd != 128) return hipErrorInvalidValue;
-  const int64_t threads = a.rows * a.heads * (a.hd / 2);
-  dim3 g(nblk(threads, 256)), b(256);
+  const dim3 g(nblk(a.rows * a.heads * (a.hd / 2), 256), 1, a.nb), b(256);
   if (dtype == 1) {
     // 16-byte forms when every row and head start is 16-byte aligned
     const bool vec = (uintptr_t)a.src % 16 == 0 && a.ld % 8 == 0 && a.d % 8 == 0 && (uintptr_t)a.q % 16 == 0 &&
                      (uintptr_t)a.k % 16 == 0 && (uintptr_t)a.v % 16 == 0 && a.n_pad % 8 == 0 &&
-                     (a.rope == nullptr || (uintptr_t)a.rope % 16 == 0);
-    if (vec) {
-      const dim3 g8(nblk(a.rows * a.heads * (a.hd / 8), 256));
+                     a.src_bs % 8 == 0 && a.dst_bs % 8 == 0 && (a.rope == nullptr || (uintptr_t)a.rope % 16 == 0);
+    if (vec && a.row0 % 16 == 0) {
+      const unsigned nq = nblk(a.rows * a.heads * (a.hd / 8), 256);
+      const dim3 g8(nq + nblk(a.rows, 64) * a.heads, 1, a.nb);
       if (a.hd == 64)
-        hipLaunchKernelGGL(k_qk_prep8<64>, g8, b, 0, s, a);
+        hipLaunchKernelGGL(k_qkv_prep8<64>, g8, b, 0, s, a, (int)nq);
       else
-        hipLaunchKernelGGL(k_qk_prep8<128>, g8, b, 0, s, a);
+        hipLaunchKernelGGL(k_qkv_prep8<128>, g8, b, 0, s, a, (int)nq);
+      return hipGetLastError();
+    }
+    if (vec) {
+      const unsigned nq = nblk(a.rows * a.heads * (a.hd / 8), 256);
+      if (a.hd == 64)
+        hipLaunchKernelGGL(k_qkv_prep8<64>, dim3(nq, 1, a.nb), b, 0, s, a, (int)nq);
+      else
+        hipLaunchKernelGGL(k_qkv_prep8<128>, dim3(nq, 1, a.nb), b, 0, s, a, (int)nq);
     } else if (a.hd == 64) {
       hipLaunchKernelGGL((k_qk_prep<bf16_t, 32>), g, b, 0, s, a);
     } else {
       hipLaunchKernelGGL((k_qk_prep<bf16_t, 64>), g, b, 0, s, a);
     }
-    const dim3 gv(nblk(a.rows, 64), a.heads);
-    if (vec && a.row0 % 16 == 0) {
-      if (a.hd == 64)
-        hipLaunchKernelGGL(k_v_transpose8<64>, gv, dim3(256), 0, s, a);
-      else
-        hipLaunchKernelGGL(k_v_transpose8<128>, gv, dim3(256), 0, s, a);
-    } else {
-      hipLaunchKernelGGL(k_v_transpose, gv, dim3(256), 0, s, a);
-    }
+    hipLaunchKernelGGL(k_v_transpose, dim3(nblk(a.rows, 64), a.heads, a.nb), b, 0, s, a);
   } else {
     if (a.hd == 64)
       hipLaunchKernelGGL((k_qk_prep<float, 32>), g, b, 0, s, a);
     else
       hipLaunchKernelGGL((k_qk_prep<float, 64>), g, b, 0, s, a);
-    hipLaunchKernelGGL((k_v_copy<float>), dim3(nblk(a.rows * a.d, 256)), dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_qkv_pad(int dtype, void *q, void *k, void *v, int heads, int hd, int64_t n, int64_t n_pad,
                           hipStream_t s) {
-  if (n_pad <= n) return hipSuccess;
-  int64_t total = (int64_t)heads * (n_pad - n) * hd;
-  unsigned g = nblk(total, 256);
-  if (g > 4096) g = 4096;
+  if (n_pad <= n || heads <= 0) return hipSuccess;
+  const dim3 g((unsigned)heads, 3), b(256);
   if (dtype == 1)
-    hipLaunchKernelGGL((k_qkv_pad<bf16_t>), dim3(g), dim3(256), 0, s, (bf16_t *)q, (bf16_t *)k, (bf16_t *)v, heads,
-                       hd, n, n_pad, 1);
+    hipLaunchKernelGGL((k_qkv_pad<bf16_t, true>), g, b, 0, s, (bf16_t *)q, (bf16_t *)k, (bf16_t *)v, hd, n, n_pad);
   else
-    hipLaunchKernelGGL((k_qkv_pad<float>), dim3(g), dim3(256), 0, s, (float *)q, (float *)k, (float *)v, heads, hd,
-                       n, n_pad, 0);
+    hipLaunchKernelGGL((k_qkv_pad<float, false>), g, b, 0, s, (float *)q, (float *)k, (float *)v, hd, n, n_pad);
   return hipGetLastError();
 }
 

@@ -135,6 +135,7 @@ struct Cfg {
   static constexpr int A_CHUNKS = BM * 8 / (64 * LW);  // 1 KB stripes per loading wave per stage
   static constexpr int B_CHUNKS = BN * 8 / (64 * LW);
   static constexpr int LDS_BYTES = NB * (BM + BN) * BK * 2;
+  static constexpr bool QKV = BN % 128 == 0 && BN / WN == 64;   // tiles that take EPI_QKV
 };
 
 // Each tile row is 8 chunks of 16 bytes (128 B, two rows per 256-byte span of
@@ -190,44 +191,52 @@ __device__ __forceinline__ uint4 pack8(const float (&x)[8]) {
 // V^T position of token j (and token of position j): bits 2 and 3 swapped
 __device__ __forceinline__ int64_t vt_swap(int64_t j) { return (j & ~(int64_t)12) | ((j & 4) << 1) | ((j & 8) >> 1); }
 
-// The block's 256 x 256 bf16 tile (bias added, rounded once) sits in LDS as the
-// staged epilogue leaves it: wave (wm, wn) of 2 x 4 holds rows 128 wm.., columns
+// The block's bf16 tile (bias added, rounded once) sits in LDS as the staged
+// epilogue leaves it: wave (wm, wn) of WM x WN holds rows WR wm.., columns
 // 64 wn.. as 128-byte rows, 16-byte chunk c of row r at c ^ (r & 7). The tile
-// lies inside the q, k or v columns (d is a multiple of 256).
-__device__ __forceinline__ const char *qkv_chunk(const char *smem, int row, int cc) {
-  const int slice = (row >> 7) * 4 + (cc >> 3), r = row & 127;
-  return smem + slice * (128 * 128) + r * 128 + (((cc & 7) ^ (r & 7)) * 16);
-}
+// lies inside the q, k or v columns and holds whole heads (d is a multiple of
+// 256, BN of 128).
+template <int BM_, int BN_, int WM_, int WN_>
+struct QkvTile {
+  static constexpr int BM = BM_, BN = BN_, NT = 64 * WM_ * WN_, WR = BM_ / WM_;
+  static_assert(BN_ / WN_ == 64, "128-byte slice rows");
+  __device__ static __forceinline__ const char *chunk(const char *smem, int row, int cc) {
+    const int slice = row / WR * WN_ + (cc >> 3), r = row % WR;
+    return smem + slice * (WR * 128) + r * 128 + (((cc & 7) ^ (r & 7)) * 16);
+  }
+};
 
 // q or k: per head row the RMSNorm (float32, eps 1e-6) and the rotation of the
 // video tokens' pairs (2p, 2p + 1), one more bf16 rounding, 16-byte stores of
 // whole head rows. HD / 8 consecutive lanes hold one head row. The arithmetic
 // is that of the separate preparation kernel (k_qk_prep8), without fused
 // multiply-adds in either, so both give the same bits.
-template <int HD, bool ROPE>
+template <class QT, int HD, bool ROPE>
 __device__ __forceinline__ void qk_scatter(const GemmArgs &g, const char *smem, int64_t m0, int h0, bf16_t *dst) {
 #pragma clang fp contract(off)
   const QkvOut &o = g.qkv;
   constexpr int TPH = HD / 8;
-  // Iteration it handles tile row 16 it + threadIdx.x / 32; the thread's chunk
-  // of the row (threadIdx.x % 32: head hh, eight columns from 8 c) is the same
+  // Iteration it handles tile row RPI it + threadIdx.x / CPR; the thread's chunk
+  // of the row (threadIdx.x % CPR: head hh, eight columns from 8 c) is the same
   // in every iteration. The sample and token advance incrementally (no
   // division per row). With a rotation table (ROPE: a table and video rows)
   // its entries go out four rows at a time, one group of four ahead, and
   // unconditionally (rows that take no rotation read table row 0), so the
   // stores of a group never stand between a table read and its use.
-  const int cc = threadIdx.x & 31, hh = cc / TPH, c = cc % TPH;
-  const int64_t r_first = m0 + (threadIdx.x >> 5);
+  constexpr int CPR = QT::BN / 8, RPI = QT::NT / CPR, NG = QT::BM / RPI / 4;
+  static_assert(NG * RPI * 4 == QT::BM, "whole groups of four rows");
+  const int cc = threadIdx.x % CPR, hh = cc / TPH, c = cc % TPH, rt = threadIdx.x / CPR;
+  const int64_t r_first = m0 + rt;
   int64_t b = (int64_t)blockIdx.z + r_first / o.rps, jr = r_first % o.rps;
   int64_t bsv[2][4], jv[2][4];   // group g4 in slot g4 & 1
   float4 cs4v[2][4][2];
-  auto rotates = [&](int it, int64_t jt) { return ROPE && jt < o.n_video && m0 + 16 * it + (threadIdx.x >> 5) < g.m; };
+  auto rotates = [&](int it, int64_t jt) { return ROPE && jt < o.n_video && m0 + RPI * it + rt < g.m; };
   auto coords = [&](int64_t (&bs4)[4], int64_t (&j4)[4]) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       bs4[u] = b;
       j4[u] = o.row0 + jr;
-      jr += 16;
+      jr += RPI;
       while (jr >= o.rps) {
         jr -= o.rps;
         ++b;
@@ -247,17 +256,17 @@ __device__ __forceinline__ void qk_scatter(const GemmArgs &g, const char *smem, 
   coords(bsv[0], jv[0]);
   fetch(0, jv[0], cs4v[0]);
 #pragma unroll
-  for (int g4 = 0; g4 < 4; ++g4) {
+  for (int g4 = 0; g4 < NG; ++g4) {
     const int sl = g4 & 1;
-    if (g4 + 1 < 4) {
+    if (g4 + 1 < NG) {
       coords(bsv[sl ^ 1], jv[sl ^ 1]);
       fetch(g4 + 1, jv[sl ^ 1], cs4v[sl ^ 1]);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int it = 4 * g4 + u, row = 16 * it + (threadIdx.x >> 5);
+      const int it = 4 * g4 + u, row = RPI * it + rt;
       float x[8];
-      unpack8(*(const uint4 *)qkv_chunk(smem, row, cc), x);
+      unpack8(*(const uint4 *)QT::chunk(smem, row, cc), x);
       if (o.qk_norm) {
         float sq = 0.f;
 #pragma unroll
@@ -289,16 +298,17 @@ __device__ __forceinline__ void qk_scatter(const GemmArgs &g, const char *smem, 
 // consecutive positions (one 16-byte store) per lane for every group of 16
 // tokens it holds whole; partial groups and other tiles go element by element
 // (positions of missing tokens are padding, zeroed separately).
-template <int HD>
+template <class QT, int HD>
 __device__ __forceinline__ void v_scatter(const GemmArgs &g, const char *smem, int64_t m0, int h0) {
   const QkvOut &o = g.qkv;
   bf16_t *v = (bf16_t *)o.v;
   auto at = [&](int row, int col) -> uint32_t {
-    return *(const bf16_t *)(qkv_chunk(smem, row, col >> 3) + 2 * (col & 7));
+    return *(const bf16_t *)(QT::chunk(smem, row, col >> 3) + 2 * (col & 7));
   };
   const int64_t mr = m0 % o.rps;
-  const bool clean = (o.row0 + mr) % 16 == 0 && mr + 256 <= o.rps;
+  const bool clean = (o.row0 + mr) % 16 == 0 && mr + QT::BM <= o.rps;
   static_assert(HD == 64 || HD == 128, "head size");
+  constexpr int PPI = QT::NT / QT::BN;   // columns' threads: positions (or rows) per iteration
   if (clean) {
     // a wavefront's lanes take 64 consecutive columns at one chunk of 8
     // positions: every LDS read of the wave hits one 128-byte tile row segment
@@ -306,8 +316,8 @@ __device__ __forceinline__ void v_scatter(const GemmArgs &g, const char *smem, i
     // apart would all fall on one bank)
     const int64_t b = (int64_t)blockIdx.z + m0 / o.rps, j0 = o.row0 + mr;
 #pragma unroll 2
-    for (int it = 0; it < 16; ++it) {
-      const int col = threadIdx.x & 255, p8 = 2 * it + (threadIdx.x >> 8);
+    for (int it = 0; it < QT::BM / 8 / PPI; ++it) {
+      const int col = threadIdx.x % QT::BN, p8 = PPI * it + threadIdx.x / QT::BN;
       const int hh = col / HD, e = col % HD, grp = 16 * (p8 >> 1), half = p8 & 1;
       bf16_t *dst = v + ((b * o.heads + h0 + hh) * HD + e) * o.n_pad + j0;
       if (m0 + grp + 16 <= g.m) {
@@ -327,14 +337,14 @@ __device__ __forceinline__ void v_scatter(const GemmArgs &g, const char *smem, i
       }
     }
   } else {
-    // element by element: the thread's column is fixed, its row steps by 2
-    const int col = threadIdx.x & 255, hh = col / HD, e = col % HD;
-    const int64_t r_first = m0 + (threadIdx.x >> 8);
+    // element by element: the thread's column is fixed, its row steps by PPI
+    const int col = threadIdx.x % QT::BN, hh = col / HD, e = col % HD;
+    const int64_t r_first = m0 + threadIdx.x / QT::BN;
     int64_t b = (int64_t)blockIdx.z + r_first / o.rps, jr = r_first % o.rps;
-    for (int it = 0; it < 128; ++it) {
-      const int row = 2 * it + (threadIdx.x >> 8);
+    for (int it = 0; it < QT::BM / PPI; ++it) {
+      const int row = PPI * it + threadIdx.x / QT::BN;
       const int64_t bs = b, j = o.row0 + jr;
-      jr += 2;
+      jr += PPI;
       while (jr >= o.rps) {
         jr -= o.rps;
         ++b;
@@ -353,9 +363,9 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
   // keep C tiles, whose lanes cover 32 consecutive columns of two rows (a full
   // 128-byte line per read-modify-write instruction)
   constexpr bool TR = EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_QKV;
-  static_assert(EPI != EPI_QKV || (BM == 256 && BN == 256 && WM == 2 && WN == 4), "EPI_QKV: 256 x 256, 8 waves");
   constexpr bool RES = EPI == EPI_GATE_RES || EPI == EPI_GATE_RES_NT;   // gated residual into the float32 stream
-  constexpr bool STAGE_OUT = BM == 256;   // bf16 output through LDS, whole-line non-temporal stores
+  // bf16 output through LDS: whole-line non-temporal stores, or the q/k/v layouts
+  constexpr bool STAGE_OUT = BM == 256 || EPI == EPI_QKV;
   const GemmArgs g = batch_entry<bf16_t>(g0);
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char *sA = smem;                      // [NB][BM][128 B]
@@ -678,22 +688,23 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
       }
     }
     if constexpr (EPI == EPI_QKV) {
+      using QT = QkvTile<BM, BN, WM, WN>;
       __syncthreads();                      // every wave's slice is written
       const int region = (int)(n0 / g.qkv.d), h0 = (int)((n0 % g.qkv.d) / g.qkv.hd);
       if (region < 2) {
         bf16_t *dst = (bf16_t *)(region == 0 ? g.qkv.q : g.qkv.k);
         const bool rope = g.qkv.rope && g.qkv.n_video > 0;
         if (g.qkv.hd == 128) {
-          if (rope) qk_scatter<128, true>(g, smem, m0, h0, dst);
-          else qk_scatter<128, false>(g, smem, m0, h0, dst);
+          if (rope) qk_scatter<QT, 128, true>(g, smem, m0, h0, dst);
+          else qk_scatter<QT, 128, false>(g, smem, m0, h0, dst);
         } else {
-          if (rope) qk_scatter<64, true>(g, smem, m0, h0, dst);
-          else qk_scatter<64, false>(g, smem, m0, h0, dst);
+          if (rope) qk_scatter<QT, 64, true>(g, smem, m0, h0, dst);
+          else qk_scatter<QT, 64, false>(g, smem, m0, h0, dst);
         }
       } else if (g.qkv.hd == 128) {
-        v_scatter<128>(g, smem, m0, h0);
+        v_scatter<QT, 128>(g, smem, m0, h0);
       } else {
-        v_scatter<64>(g, smem, m0, h0);
+        v_scatter<QT, 64>(g, smem, m0, h0);
       }
       return;
     }
@@ -830,7 +841,7 @@ hipError_t launch_mfma(const GemmArgs &g0, hipStream_t s) {
     case EPI_GATE_RES: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES, NB>), grid, block, C::LDS_BYTES, s, g); break;
     case EPI_GATE_RES_NT: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES_NT, NB>), grid, block, C::LDS_BYTES, s, g); break;
     case EPI_QKV:
-      if constexpr (BM == 256 && BN == 256 && WM == 2 && WN == 4) {
+      if constexpr (C::QKV) {
         hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_QKV, NB>), grid, block, C::LDS_BYTES, s, g);
         break;
       } else {
@@ -853,7 +864,7 @@ hipError_t set_lds_limit() {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
     if (e != hipSuccess) return e;
   }
-  if constexpr (BM == 256 && BN == 256 && WM == 2 && WN == 4)
+  if constexpr (C::QKV)
     return hipFuncSetAttribute((const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_QKV, NB>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
   return hipSuccess;
@@ -914,7 +925,7 @@ bool small_product(const GemmArgs &g) {
 
 bool gemm_qkv_fusable(int dtype, const GemmArgs &g) {
   const QkvOut &o = g.qkv;
-  return dtype == 1 && operands_aligned(g) && g.n % 256 == 0 && g.m >= 512 && g.k < 8192 && !small_product(g) &&
+  return dtype == 1 && operands_aligned(g) && g.n % 256 == 0 && g.m >= 512 && g.k < 8192 && (!small_product(g) || tile_count(g, 64, 64) > device_cus()) &&
          (o.hd == 64 || o.hd == 128) && o.d % 256 == 0 && g.n == 3 * (int64_t)o.d && o.rps > 0 &&
          o.n_pad % 8 == 0 && (uintptr_t)o.q % 16 == 0 && (uintptr_t)o.k % 16 == 0 && (uintptr_t)o.v % 16 == 0 &&
          (uintptr_t)o.rope % 16 == 0;
@@ -953,11 +964,10 @@ hipError_t launch_gemm(int dtype, const GemmArgs &g_in, hipStream_t s) {
     // outputs take the 128 x 128 kernels, which store 8-byte groups)
     const bool c16 = g.epi == EPI_STORE || g.epi == EPI_GELU;
     const bool out16 = !c16 || ((uintptr_t)g.c % 16 == 0 && g.ldc % 8 == 0 && (g.batch <= 1 || g.c_bs % 8 == 0));
-    if (g.epi == EPI_QKV) return launch_mfma<256, 256, 2, 4>(g, s);
+    if (g.epi == EPI_QKV && !small_product(g)) return launch_mfma<256, 256, 2, 4>(g, s);
     // A product that would leave compute units idle in its only dispatch round of
     // 256 x 256 tiles (the mid-size model's products: 44 to 176 of them) runs on
-    // smaller ones, and its q/k/v projection takes the separate preparation
-    // kernels. Every output is summed over K in the same order on any tile shape,
+    // smaller ones. Every output is summed over K in the same order on any tile shape,
     // so the results are the same bits.
     if (small_product(g)) return launch_small(g, out16, s);
     if (g.n % 256 == 0 && g.m >= 512 && out16) {

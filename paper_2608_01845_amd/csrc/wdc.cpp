@@ -400,10 +400,16 @@ void attn_scratch(const wdc_ctx *c, AttnArgs &a) {
   a.force_splits = c->attn_splits;
 }
 
+// Rows (keys) [n, n_pad) of every sample's q, k and v: zero for the whole call,
+// since the blocks write only the rows below n
+wdc_status pad_qkv(wdc_ctx *c) {
+  HIPCHK(c, launch_qkv_pad(c->d.dtype, c->q, c->k, c->v, c->H * c->nb, c->hd, c->n, c->n_pad, c->stream));
+  return WDC_OK;
+}
+
 // joint attention of every sample: q/k/v hold nb x H heads, O rows follow the samples
 wdc_status attention(wdc_ctx *c, void *o, int64_t ldo) {
   const int hb = c->H * c->nb;
-  HIPCHK(c, launch_qkv_pad(c->d.dtype, c->q, c->k, c->v, hb, c->hd, c->n, c->n_pad, c->stream));
   AttnArgs a{};
   a.q = c->q;
   a.k = c->k;
@@ -424,34 +430,34 @@ wdc_status attention(wdc_ctx *c, void *o, int64_t ldo) {
 // q/k/v of every sample from the fused projection rows [row0, row0 + rows) of
 // each sample (row stride ld) into the attention layouts of its heads
 wdc_status qkv_prep(wdc_ctx *c, const void *src, int64_t ld, int64_t row0, int64_t rows) {
-  const int64_t hs = (int64_t)c->H * c->n_pad * c->hd;  // elements per sample of q/k/v
-  for (int b = 0; b < c->nb; ++b) {
-    QKVPrepArgs a;
-    a.src = elem(c, src, (int64_t)b * c->n * ld);
-    a.ld = ld;
-    a.row0 = row0;
-    a.rows = rows;
-    a.n_video = c->nv;
-    a.n_pad = c->n_pad;
-    a.q = elem(c, c->q, b * hs);
-    a.k = elem(c, c->k, b * hs);
-    a.v = elem(c, c->v, b * hs);
-    a.heads = c->H;
-    a.hd = c->hd;
-    a.d = c->D;
-    a.qk_norm = c->d.qk_norm;
-    a.rope = (c->d.rope_t + c->d.rope_h + c->d.rope_w) ? c->rope : nullptr;
-    HIPCHK(c, launch_qkv_prep(c->d.dtype, a, c->stream));
-  }
+  QKVPrepArgs a{};
+  a.src = src;
+  a.ld = ld;
+  a.row0 = row0;
+  a.rows = rows;
+  a.n_video = c->nv;
+  a.n_pad = c->n_pad;
+  a.q = c->q;
+  a.k = c->k;
+  a.v = c->v;
+  a.heads = c->H;
+  a.hd = c->hd;
+  a.d = c->D;
+  a.qk_norm = c->d.qk_norm;
+  a.rope = (c->d.rope_t + c->d.rope_h + c->d.rope_w) ? c->rope : nullptr;
+  a.nb = c->nb;
+  a.src_bs = c->n * ld;
+  a.dst_bs = (int64_t)c->H * c->n_pad * c->hd;  // elements per sample of q/k/v
+  HIPCHK(c, launch_qkv_prep(c->d.dtype, a, c->stream));
   return WDC_OK;
 }
 
 // q/k/v projection of the modulated rows [row0, row0 + rows) of every sample
 // (a: the first of them, row stride D). batched: one batch entry per sample
 // (sample stride N rows); else one product over all samples' rows (row0 = 0,
-// rows = N). The 256 x 256 GEMM writes q, k and v^T straight into the
-// attention layouts (per-head RMSNorm and RoPE in its epilogue); products it
-// does not run (few rows) take the plain GEMM into the qkv buffer and the
+// rows = N). The GEMM writes q, k and v^T straight into the
+// attention layouts (per-head RMSNorm and RoPE in its epilogue); products too
+// small for tiles of whole heads (few rows) take the plain GEMM into the qkv buffer and the
 // separate preparation kernels, with the same arithmetic.
 wdc_status qkv_project(wdc_ctx *c, const void *a, const void *w, const void *bias, int64_t row0, int64_t rows,
                        bool batched) {
@@ -639,6 +645,7 @@ wdc_status dit_forward_batch(wdc_ctx *c, int nb, const float *const *z, double t
   const auto &d = c->d;
   CHK(cond_embed(c, nb, t, cond, cam, c->cemb));
   CHK(modulation(c, -1));
+  CHK(pad_qkv(c));
   SamplePtrs zp{}, vp{};
   for (int b = 0; b < nb; ++b) {
     zp.p[b] = z[b];
@@ -1402,6 +1409,7 @@ wdc_status wdc_dit_block_forward(wdc_ctx *ctx, int32_t block, float *d_x, const 
   ctx->x = d_x;
   ctx->cemb = const_cast<float *>(d_cemb);
   wdc_status s = modulation(ctx, block);
+  if (s == WDC_OK) s = pad_qkv(ctx);
   if (s == WDC_OK) s = block_forward(ctx, block);
   ctx->x = x_saved;
   ctx->cemb = c_saved;

@@ -106,3 +106,31 @@ def test_fill_tiles_mid_forward_bitwise_equal():
     b = shape.forward(z, 0.7, cond)
     print("mid forward: 128 x 128 + separate vs 256 x 256 + fused max |diff|", float((a - b).abs().max()))
     assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("hidden,head_dim,latent,batch", [
+    (256, 64, (16, 7, 28, 30), 1),      # 1,470 + 21 tokens: 128 x 128 tiles, one per compute unit
+    (256, 128, (16, 7, 28, 30), 1),
+    (256, 64, (16, 4, 20, 38), 2),      # two samples of 781 tokens share tiles: element-wise V^T
+    (512, 128, (16, 7, 38, 42), 1),     # 2,793 + 21 tokens: 256 x 128 tiles
+    (512, 64, (16, 4, 38, 38), 2)])
+def test_fused_qkv_on_small_tiles_equals_separate_preparation(hidden, head_dim, latent, batch):
+    """Projections that do not fill a dispatch round of 256 x 256 tiles, fused on
+    the tiles they take instead, against the separate kernels bit for bit."""
+    torch = torch_cuda()
+    import paper_2608_01845_amd as wdc
+    cfg = small_cfg("bf16", head_dim=head_dim, hidden=hidden, heads=hidden // head_dim, latent=latent)
+    fused = wdc.Context(cfg, max_batch=batch)
+    fused.load_weights(synth.gen_weights(cfg))
+    os.environ["WDC_FUSE_QKV"] = "0"
+    try:
+        sep = wdc.Context(cfg, max_batch=batch, allocate_weights=False)
+    finally:
+        del os.environ["WDC_FUSE_QKV"]
+    sep.bind_weights(fused.weights)
+    zs = [torch.from_numpy(synth.gen_tensor(s, "z", cfg.latent)).cuda() for s in range(batch)]
+    inp = {k: [fused.to_device(v)] * batch for k, v in synth.gen_inputs(cfg).items()}
+    vf = fused.forward_batch(zs, 0.4, inp["cond"], inp["text"], inp["cam"])
+    vs = sep.forward_batch(zs, 0.4, inp["cond"], inp["text"], inp["cam"])
+    for a, b in zip(vf, vs):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
