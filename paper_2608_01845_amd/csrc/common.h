@@ -103,7 +103,8 @@ enum Epi {
 };
 
 // Destination of EPI_QKV. Row r of batch entry z of the product is token
-// row0 + r % rps of sample z + r / rps; q and k of sample b, head h, token j at
+// row0 + (rbase + r) % rps of sample z + (rbase + r) / rps, column c of it
+// column cbase + c of the projection; q and k of sample b, head h, token j at
 // ((b * heads + h) * n_pad + j) * hd, v transposed at ((b * heads + h) * hd + e)
 // * n_pad + vt(j), vt swapping bits 2 and 3 of j (the key order of the
 // attention kernels' V^T operand).
@@ -112,6 +113,7 @@ struct QkvOut {
   const float2 *rope;     // [n_video, hd/2] (cos, sin) or null
   int64_t n_pad, n_video, rps, row0;
   int heads, hd, d, qk_norm;
+  int64_t rbase, cbase;   // of a part of a product (0 in the whole one)
 };
 
 struct GemmArgs {

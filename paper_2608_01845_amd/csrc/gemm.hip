@@ -226,7 +226,7 @@ __device__ __forceinline__ void qk_scatter(const GemmArgs &g, const char *smem, 
   constexpr int CPR = QT::BN / 8, RPI = QT::NT / CPR, NG = QT::BM / RPI / 4;
   static_assert(NG * RPI * 4 == QT::BM, "whole groups of four rows");
   const int cc = threadIdx.x % CPR, hh = cc / TPH, c = cc % TPH, rt = threadIdx.x / CPR;
-  const int64_t r_first = m0 + rt;
+  const int64_t r_first = o.rbase + m0 + rt;
   int64_t b = (int64_t)blockIdx.z + r_first / o.rps, jr = r_first % o.rps;
   int64_t bsv[2][4], jv[2][4];   // group g4 in slot g4 & 1
   float4 cs4v[2][4][2];
@@ -305,7 +305,7 @@ __device__ __forceinline__ void v_scatter(const GemmArgs &g, const char *smem, i
   auto at = [&](int row, int col) -> uint32_t {
     return *(const bf16_t *)(QT::chunk(smem, row, col >> 3) + 2 * (col & 7));
   };
-  const int64_t mr = m0 % o.rps;
+  const int64_t mr = (o.rbase + m0) % o.rps;
   const bool clean = (o.row0 + mr) % 16 == 0 && mr + QT::BM <= o.rps;
   static_assert(HD == 64 || HD == 128, "head size");
   constexpr int PPI = QT::NT / QT::BN;   // columns' threads: positions (or rows) per iteration
@@ -314,7 +314,7 @@ __device__ __forceinline__ void v_scatter(const GemmArgs &g, const char *smem, i
     // positions: every LDS read of the wave hits one 128-byte tile row segment
     // (columns of a fixed token are contiguous; tokens of a fixed column 16
     // apart would all fall on one bank)
-    const int64_t b = (int64_t)blockIdx.z + m0 / o.rps, j0 = o.row0 + mr;
+    const int64_t b = (int64_t)blockIdx.z + (o.rbase + m0) / o.rps, j0 = o.row0 + mr;
 #pragma unroll 2
     for (int it = 0; it < QT::BM / 8 / PPI; ++it) {
       const int col = threadIdx.x % QT::BN, p8 = PPI * it + threadIdx.x / QT::BN;
@@ -339,7 +339,7 @@ __device__ __forceinline__ void v_scatter(const GemmArgs &g, const char *smem, i
   } else {
     // element by element: the thread's column is fixed, its row steps by PPI
     const int col = threadIdx.x % QT::BN, hh = col / HD, e = col % HD;
-    const int64_t r_first = m0 + threadIdx.x / QT::BN;
+    const int64_t r_first = o.rbase + m0 + threadIdx.x / QT::BN;
     int64_t b = (int64_t)blockIdx.z + r_first / o.rps, jr = r_first % o.rps;
     for (int it = 0; it < QT::BM / PPI; ++it) {
       const int row = PPI * it + threadIdx.x / QT::BN;
@@ -690,7 +690,8 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
     if constexpr (EPI == EPI_QKV) {
       using QT = QkvTile<BM, BN, WM, WN>;
       __syncthreads();                      // every wave's slice is written
-      const int region = (int)(n0 / g.qkv.d), h0 = (int)((n0 % g.qkv.d) / g.qkv.hd);
+      const int64_t nq = g.qkv.cbase + n0;
+      const int region = (int)(nq / g.qkv.d), h0 = (int)((nq % g.qkv.d) / g.qkv.hd);
       if (region < 2) {
         bf16_t *dst = (bf16_t *)(region == 0 ? g.qkv.q : g.qkv.k);
         const bool rope = g.qkv.rope && g.qkv.n_video > 0;
@@ -814,26 +815,35 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
 #undef WDC_GEMM_LOAD
 }
 
+// 8 x 4 rectangles of 256 x 256 tiles ("chunks", one per XCD and dispatch round)
+// of a product that takes the rectangle order, 0 of one that does not. The order
+// pays on large single products; a z-batch would put every slice's rectangles
+// on the same XCDs, and with fewer than 8 dispatch rounds the partly filled last
+// round costs more than the L2 reuse gains (a batched rollout of 8 mid-size
+// samples ran 40% slower with it). 2 x 16 rectangles (A panels, larger than the
+// last-level cache, re-read once per rectangle column; weight panels, which fit
+// it, once per rectangle row) made the N = 12,288 product 2.5-3% faster alone
+// but the whole 13B forward's GEMMs 1% slower (same-box A/B), so they are not
+// used; nor 2 x 16 for that product alone (1.1% slower over the forward) or 16 x 2
+// for the N = 3,072 ones (1.8% slower).
+constexpr int RECT_M = 8, RECT_N = 4;
+int rect_chunks(const GemmArgs &g) {
+  const int m_tiles = (int)((g.m + 255) / 256), n_tiles = (int)(g.n / 256);
+  if (n_tiles % RECT_N != 0 || g.batch > 1 || device_cus() != 256) return 0;
+  const int chunks = (m_tiles + RECT_M - 1) / RECT_M * (n_tiles / RECT_N);
+  return chunks >= 64 ? chunks : 0;
+}
+
 template <int BM, int BN, int WM, int WN, int NB = 2>
-hipError_t launch_mfma(const GemmArgs &g0, hipStream_t s) {
+hipError_t launch_mfma(const GemmArgs &g0, hipStream_t s, int max_chunks = 0) {
   using C = Cfg<BM, BN, WM, WN, NB>;
   GemmArgs g = g0;
   const int m_tiles = (int)((g.m + BM - 1) / BM), n_tiles = (int)(g.n / BN);
-  // The rectangle order pays on large single products; a z-batch would put every
-  // slice's rectangles on the same XCDs, and with fewer than 8 dispatch rounds
-  // the partly filled last round costs more than the L2 reuse gains (a batched
-  // rollout of 8 mid-size samples ran 40% slower with it).
-  // 8 x 4 rectangles. 2 x 16 ones (A panels, larger than the last-level cache,
-  // re-read once per rectangle column; weight panels, which fit it, once per
-  // rectangle row) made the N = 12,288 product 2.5-3% faster alone but the
-  // whole 13B forward's GEMMs 1% slower (same-box A/B), so they are not used;
-  // nor 2 x 16 for that product alone (1.1% slower over the forward) or 16 x 2
-  // for the N = 3,072 ones (1.8% slower).
-  g.rect_n = 4;
-  const int chunks = n_tiles % g.rect_n == 0 ? (m_tiles + 32 / g.rect_n - 1) / (32 / g.rect_n) * (n_tiles / g.rect_n) : 0;
-  g.order = (BM == 256 && chunks >= 64 && g.batch <= 1 && device_cus() == 256) ? 1 : 0;
+  g.rect_n = RECT_N;
+  const int chunks = BM == 256 && BN == 256 ? rect_chunks(g) : 0;
+  g.order = chunks > 0;
   int blocks = m_tiles * n_tiles;
-  if (g.order == 1) blocks = (chunks + 7) / 8 * 256;
+  if (g.order == 1) blocks = ((max_chunks > 0 ? max_chunks : chunks) + 7) / 8 * 256;
   dim3 grid(blocks, 1, g.batch > 1 ? g.batch : 1), block(C::NT);
   switch (g.epi) {
     case EPI_STORE: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_STORE, NB>), grid, block, C::LDS_BYTES, s, g); break;
@@ -894,25 +904,107 @@ int64_t tile_count(const GemmArgs &g, int bm, int bn) {
 // two 128 x 128 blocks per CU (2,688 x 3,072, K = 1,024: 24.6 us) and 256 x 128
 // (2,688 x 4,096, K = 1,024: 30.8 against 34.9; 5,000 x 1,536, K = 1,536: 24.4
 // against 29.7). 256 x 128 needs 16-byte output rows.
-hipError_t launch_small(const GemmArgs &g, bool out16, hipStream_t s) {
+enum SmallTile { T64, T128_64, T128_ONE, T128_TWO, T256_128 };
+SmallTile pick_small(const GemmArgs &g, bool out16, double *us) {
   const int64_t cus = device_cus() > 0 ? device_cus() : 256;
+  const double st = (double)(g.k / BK);
+  auto rounds = [&](int64_t tiles) { return (double)((tiles + cus - 1) / cus); };
   const int64_t t64 = tile_count(g, 64, 64);
-  if (t64 <= cus) return launch_mfma<64, 64, 2, 2, 3>(g, s);
+  *us = 0.30 * st + 2.5;
+  if (t64 <= cus) return T64;
   if (g.n % 128 != 0) {   // narrow outputs (the output head: n = 64 latent values per token)
-    if (t64 <= 3 * cus) return launch_mfma<64, 64, 2, 2, 3>(g, s);
-    return launch_mfma<128, 64, 2, 2>(g, s);
+    *us = (0.30 * st + 2.5) * rounds(t64);
+    return t64 <= 3 * cus ? T64 : T128_64;
   }
   const int64_t t128 = tile_count(g, 128, 128), t256 = tile_count(g, 256, 128);
-  if (t128 <= cus) return launch_mfma<128, 128, 2, 2, 4>(g, s);
   // rounds of two 128 x 128 blocks per CU (and a last one of single blocks)
   // against rounds of 256 x 128 blocks: stage time x stages + the prologue and
   // epilogue of a round, which nothing overlaps
+  const double pair = 0.95 * st + 9.4, single = 0.53 * st + 4.0;
+  *us = single;
+  if (t128 <= cus) return T128_ONE;
   const int64_t rest = t128 % (2 * cus);
-  const double st = (double)(g.k / BK), pair = 0.95 * st + 9.4, single = 0.55 * st + 4.0;
   const double c128 = pair * (double)(t128 / (2 * cus)) + (rest == 0 ? 0.0 : rest <= cus ? single : pair);
-  const double c256 = (0.78 * st + 3.0) * (double)((t256 + cus - 1) / cus);
-  if (out16 && c256 <= c128) return launch_mfma<256, 128, 4, 2, 3>(g, s);
-  return launch_mfma<128, 128, 2, 2>(g, s);
+  const double c256 = (0.78 * st + 3.0) * rounds(t256);
+  *us = out16 && c256 <= c128 ? c256 : c128;
+  return out16 && c256 <= c128 ? T256_128 : T128_TWO;
+}
+
+hipError_t launch_small(const GemmArgs &g, bool out16, hipStream_t s) {
+  double us;
+  switch (pick_small(g, out16, &us)) {
+    case T64: return launch_mfma<64, 64, 2, 2, 3>(g, s);
+    case T128_64: return launch_mfma<128, 64, 2, 2>(g, s);
+    case T128_ONE: return launch_mfma<128, 128, 2, 2, 4>(g, s);
+    case T128_TWO: return launch_mfma<128, 128, 2, 2>(g, s);
+    default: return launch_mfma<256, 128, 4, 2, 3>(g, s);
+  }
+}
+
+// Rows [m0, m) and columns [n0, n) of a product, as a product of its own
+GemmArgs sub_product(const GemmArgs &g, int64_t m0, int64_t n0) {
+  GemmArgs t = g;
+  const int64_t o = m0 * g.ldc + n0;
+  t.m = g.m - m0;
+  t.n = g.n - n0;
+  t.a = (const bf16_t *)g.a + m0 * g.lda;
+  t.w = (const bf16_t *)g.w + n0 * g.k;
+  if (g.bias) t.bias = (const bf16_t *)g.bias + n0;
+  if (g.gate) t.gate = g.gate + n0;
+  if (g.epi == EPI_QKV) {
+    t.qkv.rbase += m0;
+    t.qkv.cbase += n0;
+  } else {
+    t.c = g.epi == EPI_STORE || g.epi == EPI_GELU ? (void *)((bf16_t *)g.c + o) : (void *)((float *)g.c + o);
+  }
+  return t;
+}
+
+// The leftover of a large product on smaller tiles. The fused q/k/v epilogue
+// needs tiles of whole heads: 128 x 128 ones where 64 x 64 would be picked.
+hipError_t launch_tail(const GemmArgs &g, bool out16, hipStream_t s) {
+  double us;
+  if (g.epi == EPI_QKV && pick_small(g, out16, &us) == T64) return launch_mfma<128, 128, 2, 2, 4>(g, s);
+  return launch_small(g, out16, s);
+}
+
+// A product on 256 x 256 tiles: the tiles that fill whole dispatch rounds, then
+// what is left of them on smaller tiles, when those take less than the thin last
+// round would (a round: 1.45 us a K stage and 8 us of prologue and epilogue).
+// In the rectangle order the last chunks of the last chunk row are left, else the
+// last rows. 17,776 x 3,072, K = 3,072 (3.28 rounds): 323 -> 314 us; 21,504 x
+// 4,096, K = 1,024 (5.25): 172 -> 168; 67,576 x 3,072, K = 3,072 (12.4): 1,026 ->
+// 997; 118,800 x 3,072, K = 15,360 (22 rounds and one chunk): 8.63 -> 8.41 ms; less
+// than the idle compute units suggest, since a thin round runs at a higher clock.
+// Every output is summed in the same order on all of them.
+hipError_t launch_big(const GemmArgs &g, bool out16, hipStream_t s) {
+  const int64_t cus = device_cus();
+  const double round = 1.45 * (double)(g.k / BK) + 8.0;
+  double us;
+  const int chunks = rect_chunks(g);
+  if (chunks > 0 && chunks % 8 != 0 && chunks % 8 <= g.n / (256 * RECT_N)) {
+    const int left = chunks % 8;
+    const GemmArgs t = sub_product(g, ((g.m + 255) / 256 - 1) / RECT_M * RECT_M * 256, g.n - left * RECT_N * 256);
+    (void)pick_small(t, out16, &us);
+    if (us < 0.85 * round) {
+      const hipError_t e = launch_mfma<256, 256, 2, 4>(g, s, chunks - left);
+      return e != hipSuccess ? e : launch_tail(t, out16, s);
+    }
+  } else if (chunks == 0 && cus > 0) {
+    const int64_t per_row = g.n / 256 * (g.batch > 1 ? g.batch : 1), full = tile_count(g, 256, 256) / cus * cus;
+    const int64_t m1 = full / per_row * 256;   // rows in whole rounds
+    if (m1 > 0 && m1 < g.m) {
+      const GemmArgs t = sub_product(g, m1, 0);
+      (void)pick_small(t, out16, &us);
+      if (us < 0.85 * round) {
+        GemmArgs g1 = g;
+        g1.m = m1;
+        const hipError_t e = launch_mfma<256, 256, 2, 4>(g1, s);
+        return e != hipSuccess ? e : launch_tail(t, out16, s);
+      }
+    }
+  }
+  return launch_mfma<256, 256, 2, 4>(g, s);
 }
 
 // products on fewer 256 x 256 tiles than the device has compute units take
@@ -958,44 +1050,18 @@ hipError_t launch_gemm(int dtype, const GemmArgs &g_in, hipStream_t s) {
     // tiles: +7.5% at K = 12,288, +2% at K = 15,360; at K = 3,072 it was 1.5%
     // slower, so shorter products keep cached accesses.
     if (g.epi == EPI_GATE_RES && g.k >= 8192) g.epi = EPI_GATE_RES_NT;
-    auto big = [&](const GemmArgs &gg) { return launch_mfma<256, 256, 2, 4>(gg, s); };
     // the 256 x 256 kernels stage bf16 outputs through LDS and store whole
     // 16-byte row chunks: they need 16-byte-aligned output rows (other bf16
     // outputs take the 128 x 128 kernels, which store 8-byte groups)
     const bool c16 = g.epi == EPI_STORE || g.epi == EPI_GELU;
     const bool out16 = !c16 || ((uintptr_t)g.c % 16 == 0 && g.ldc % 8 == 0 && (g.batch <= 1 || g.c_bs % 8 == 0));
-    if (g.epi == EPI_QKV && !small_product(g)) return launch_mfma<256, 256, 2, 4>(g, s);
+    if (g.epi == EPI_QKV && !small_product(g)) return launch_big(g, out16, s);
     // A product that would leave compute units idle in its only dispatch round of
     // 256 x 256 tiles (the mid-size model's products: 44 to 176 of them) runs on
     // smaller ones. Every output is summed over K in the same order on any tile shape,
     // so the results are the same bits.
     if (small_product(g)) return launch_small(g, out16, s);
-    if (g.n % 256 == 0 && g.m >= 512 && out16) {
-      // Tail split for a single large long-K product on a 256-CU device: the
-      // rows whose 256 x 256 tiles fill whole dispatch rounds (m1 tiles, a
-      // multiple of 256 / gcd(n_tiles, 256)) run as above; the remaining rows,
-      // which would leave most CUs idle in a last round at most half full, run
-      // on smaller tiles. At M = 67,576 and N = 3,072 that
-      // turns 12.375 rounds into 12 plus 2,040 rows: +1.5% at K = 12,288, +2% at
-      // K = 15,360 (with 128 x 128 tiles); at K = 3,072 the small tiles' lower efficiency costs more
-      // than the idle CUs (-1.3%), so short products keep one launch.
-      const int64_t m_tiles = (g.m + 255) / 256, n_tiles = g.n / 256;
-      int64_t gcd = n_tiles, r = 256;
-      while (r) { const int64_t t = gcd % r; gcd = r; r = t; }
-      const int64_t m1 = m_tiles / (256 / gcd) * (256 / gcd) * 256;   // rows in whole rounds
-      const bool thin_tail = (m_tiles * n_tiles) % 256 != 0 && (m_tiles * n_tiles) % 256 <= 128;
-      if (g.batch <= 1 && g.k >= 8192 && thin_tail && device_cus() == 256 && m1 > 0 && m1 < g.m) {
-        GemmArgs g1 = g, g2 = g;
-        g1.m = m1;
-        g2.m = g.m - m1;
-        g2.a = (const bf16_t *)g.a + m1 * g.lda;
-        g2.c = c16 ? (void *)((bf16_t *)g.c + m1 * g.ldc) : (void *)((float *)g.c + m1 * g.ldc);
-        hipError_t e = big(g1);
-        if (e != hipSuccess) return e;
-        return launch_small(g2, out16, s);
-      }
-      return big(g);
-    }
+    if (g.n % 256 == 0 && g.m >= 512 && out16) return launch_big(g, out16, s);
     if (g.n % 64 == 0) return launch_small(g, out16, s);
   }
   if (dtype == 0 && gemm_f32_mfma(g)) return launch_gemm_f32(g, s);
