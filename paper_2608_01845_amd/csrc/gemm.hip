@@ -127,8 +127,8 @@ __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, char *lds, 
 template <int BM, int BN, int WM, int WN, int NB = 2>
 struct Cfg {
   static constexpr int NT = 64 * WM * WN;       // threads
-  static constexpr int TM = BM / WM / 32;       // 32x32 tiles per wave along M
-  static constexpr int TN = BN / WN / 32;       // along N
+  static constexpr int TM = BM / WM / 16;       // 16x16 tiles per wave along M
+  static constexpr int TN = BN / WN / 16;       // along N
   // the first LW waves (one per SIMD) issue the tile loads: with all 16 waves
   // loading, the 16-wave kernel was 2-5% slower on the 13B products
   static constexpr int LW = NT / 64 >= 4 ? 4 : NT / 64;
@@ -358,11 +358,9 @@ __device__ __forceinline__ void v_scatter(const GemmArgs &g, const char *smem, i
 template <int BM, int BN, int WM, int WN, int EPI, int NB = 2>
 __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
   using C = Cfg<BM, BN, WM, WN, NB>;
-  // bf16 outputs: compute C^T tiles (weight fragment as the MFMA A operand) so a
-  // lane holds 4 consecutive columns of one row (8-byte stores); float32 outputs
-  // keep C tiles, whose lanes cover 32 consecutive columns of two rows (a full
-  // 128-byte line per read-modify-write instruction)
-  constexpr bool TR = EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_QKV;
+  // C^T tiles (weight fragment as the MFMA A operand): a lane holds 4 consecutive
+  // columns of one row, 8 bytes of a bf16 output, 16 of a float32 one
+  constexpr bool OUT16 = EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_QKV;
   constexpr bool RES = EPI == EPI_GATE_RES || EPI == EPI_GATE_RES_NT;   // gated residual into the float32 stream
   // bf16 output through LDS: whole-line non-temporal stores, or the q/k/v layouts
   constexpr bool STAGE_OUT = BM == 256 || EPI == EPI_QKV;
@@ -413,7 +411,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
 
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wm = wid / WN, wn = wid % WN;
-  const int lr = lane & 31, lg = lane >> 5;
+  const int lr = lane & 15, lg = lane >> 4;
 
   // Tiles go straight from HBM to LDS (buffer_load_dwordx4 ... lds: lane L of a
   // wavefront's load writes 16 bytes at LDS base + 16 L). Stripe s = 1 KB = 8
@@ -441,8 +439,8 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
   const int a_step = 8 * NW * (int)g.lda * 2;
   const int vb = row0 * (int)g.k * 2 + lch * 16;
 
-  // fragment read offsets: row wm*(BM/WM) + 32i + lr, chunk 2s + lg; the
-  // swizzle key depends on the row only, so k-step s reads at offset(0) ^ 32 s
+  // fragment read offsets: row wm*(BM/WM) + 16i + lr, chunk 4s + lg; the
+  // swizzle key depends on the row only, so k-step s reads at offset(0) ^ 64 s
   const int ra0 = swz(wm * (BM / WM) + lr, lg), rb0 = swz(wn * (BN / WN) + lr, lg);
 
 #define WDC_GEMM_LOAD(buf, kt)                                                                     \
@@ -459,14 +457,9 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
     }                                                                                              \
   }
 
-  // k-step s of the stage in buffer buf: the wave's TM A and TN B fragments
-#define WDC_GEMM_READ(fa, fb, buf, s)                                                               \
-  {                                                                                                \
-    const char *a_ = sA + (buf) * BM * 128, *b_ = sB + (buf) * BN * 128;                           \
-    const int oa_ = ra0 ^ (32 * (s)), ob_ = rb0 ^ (32 * (s));                                      \
-    _Pragma("unroll") for (int i = 0; i < C::TM; ++i) fa[i] = *(const bf16x8 *)(a_ + oa_ + i * 32 * 128); \
-    _Pragma("unroll") for (int j = 0; j < C::TN; ++j) fb[j] = *(const bf16x8 *)(b_ + ob_ + j * 32 * 128); \
-  }
+  // fragments of k-step s of the stage in buffer buf
+#define WDC_GEMM_READA(buf, s, i) fa[i] = *(const bf16x8 *)(sA + (buf) * BM * 128 + (ra0 ^ (64 * (s))) + (i) * 16 * 128)
+#define WDC_GEMM_READB(buf, s, j) fb[s][j] = *(const bf16x8 *)(sB + (buf) * BN * 128 + (rb0 ^ (64 * (s))) + (j) * 16 * 128)
   // Workgroup barrier after this wave's LDS reads complete, without the memory
   // fence of __syncthreads (whose vmcnt(0) would also wait for a stage still
   // in flight). The wait is the builtin rather than asm so that the compiler's
@@ -477,7 +470,6 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
     __builtin_amdgcn_s_barrier();                                                                  \
   }
 
-  constexpr int S = BK / 16;                              // k-steps per stage
   constexpr int SL = C::A_CHUNKS + C::B_CHUNKS;           // load instructions per loading wave per stage
   const int nk = (int)(g.k / BK);
   // Stages 0 and 1 fill both buffers; stage 0 is complete once no more than
@@ -492,172 +484,120 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
   }
   WDC_GEMM_BARRIER();
 
-  f32x16 acc[C::TM][C::TN];
+  constexpr int TM = C::TM, TN = C::TN;
+  f32x4 acc[TM][TN];
 #pragma unroll
-  for (int i = 0; i < C::TM; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j)
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
-  // Software pipeline over two fragment sets x and y: the fragments of k-step
-  // s+1 are read while the MFMAs of step s run. The stage barrier sits before
-  // the last k-step, whose fragments are already in registers: after it the
-  // stage two ahead goes into the buffer just consumed and the next stage's
-  // first fragments are read, both under the last step's MFMAs, so the matrix
-  // cores do not drain at the barrier. Within a step the reads and loads are
-  // interleaved one by one with the MFMAs in a fixed order (a scheduling
-  // barrier after each), so they issue while the wave's MFMAs execute; the
-  // reads go in the order the next step's MFMAs use them (A0, every B, then
-  // the other A fragments).
-  static_assert(S == 4, "the x/y alternation assumes four k-steps per stage");
-  constexpr int NQ = C::TM * C::TN, NR = C::TM + C::TN;
-#define WDC_GEMM_MFMA1(fa, fb, q)                                                                   \
-  {                                                                                                \
-    const int i_ = (q) / C::TN, j_ = (q) % C::TN;                                                  \
-    acc[i_][j_] = TR ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j_], fa[i_], acc[i_][j_], 0, 0, 0) \
-                     : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i_], fb[j_], acc[i_][j_], 0, 0, 0); \
-  }
-  // read number r of a step: 0 -> A0, 1..TN -> B0..B(TN-1), then A1..A(TM-1)
-#define WDC_GEMM_READ1(fa, fb, buf, s, r)                                                          \
-  {                                                                                                \
-    const bool isb_ = (r) >= 1 && (r) <= C::TN;                                                    \
-    const int ia_ = (r) == 0 ? 0 : (r) - C::TN, jb_ = (r) - 1;                                     \
-    if (isb_)                                                                                      \
-      fb[isb_ ? jb_ : 0] = *(const bf16x8 *)(sB + (buf) * BN * 128 + (rb0 ^ (32 * (s))) + (isb_ ? jb_ : 0) * 32 * 128); \
-    else                                                                                           \
-      fa[isb_ ? 0 : ia_] = *(const bf16x8 *)(sA + (buf) * BM * 128 + (ra0 ^ (32 * (s))) + (isb_ ? 0 : ia_) * 32 * 128); \
-  }
-  // load number l of a stage (A stripes first, then B); v_ steps through the A stripes
-#define WDC_GEMM_LOAD1(buf, kt, l)                                                                 \
+  // Two k-steps of 32 per stage, each TM rows of TN MFMAs (v_mfma_16x16x32: at
+  // the power limit a loop of them sustains 2,065 TFLOP/s on random operands
+  // with two waves per SIMD where 32x32x16 sustains 1,500, and at 64 x 64 to 128
+  // x 64 wave tiles both read the same fragments per FLOP). An A fragment is
+  // replaced by the next k-step's as soon as its row of MFMAs is issued, the B
+  // fragments are double-buffered: every read has about one k-step of MFMAs to
+  // arrive. The stage barrier sits D rows into the second k-step, whose
+  // fragments are in registers by then: after it the stage NB ahead goes into
+  // the buffer just consumed and the next stage's first fragments are read. A
+  // scheduling barrier after each MFMA, read and load keeps that order.
+  constexpr int D = TM == 8 ? 2 : 1;
+  static_assert(BK == 64 && D < TM && TN <= TM, "two k-steps per stage");
+  // Loads of a stage go one by one between MFMAs: within the rest of the second
+  // k-step with two buffers (they have the next stage to arrive in), spread on
+  // to the next barrier with more buffers and 64 x 64 wave tiles (a burst stalls
+  // the wave that issues it).
+  constexpr int LQ0 = (TM - D) * TN;                      // MFMAs from the barrier to the end of the stage
+  constexpr int LQ = NB > 2 && TM == 4 && TN == 4 ? LQ0 + TM * TN : LQ0;
+  bf16x8 fa[TM], fb[2][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) WDC_GEMM_READA(0, 0, i);
+#pragma unroll
+  for (int j = 0; j < TN; ++j) WDC_GEMM_READB(0, 0, j);
+  int va = va0;                                           // steps through the A stripes of the stage being loaded
+  // load number l of stage lkt (A stripes first, then B) into buffer lbuf
+#define WDC_GEMM_LOAD1(lbuf, lkt, l)                                                               \
   {                                                                                                \
     if ((l) < C::A_CHUNKS) {                                                                       \
-      lds_load16(a_desc, sA + (buf) * BM * 128 + ((l) * NW + wu) * 1024, v_, (kt) * BK * 2);       \
-      if ((l) + 1 < C::A_CHUNKS) asm volatile("v_add_u32 %0, %0, %1" : "+v"(v_) : "s"(a_step));     \
+      lds_load16(a_desc, sA + (lbuf) * BM * 128 + ((l) * NW + wu) * 1024, va, (lkt) * BK * 2);     \
+      if ((l) + 1 < C::A_CHUNKS) asm volatile("v_add_u32 %0, %0, %1" : "+v"(va) : "s"(a_step));     \
     } else {                                                                                       \
       const int lb_ = (l) - C::A_CHUNKS;                                                           \
-      lds_load16(b_desc, sB + (buf) * BN * 128 + (lb_ * NW + wu) * 1024, vb,                       \
-                 lb_ * 8 * NW * (int)g.k * 2 + (kt) * BK * 2);                                     \
+      lds_load16(b_desc, sB + (lbuf) * BN * 128 + (lb_ * NW + wu) * 1024, vb,                      \
+                 lb_ * 8 * NW * (int)g.k * 2 + (lkt) * BK * 2);                                    \
     }                                                                                              \
   }
-  // one k-step: the MFMAs on (ca, cb); if READS, the reads of step rs of buffer
-  // rbuf into (na, nb); if LOADS (a uniform condition), the loads of stage lkt
-  // into buffer lbuf
-#define WDC_GEMM_STEP(ca, cb, na, nb, rbuf, rs, READS, lbuf, lkt, LOADS)                           \
-  {                                                                                                \
-    int v_ = va0;                                                                                  \
-    _Pragma("unroll") for (int q = 0; q < NQ; ++q) {                                               \
-      WDC_GEMM_MFMA1(ca, cb, q);                                                                   \
-      __builtin_amdgcn_sched_barrier(0);                                                           \
-      /* load l goes after MFMA l NQ / SL, read r after MFMA r NQ / NR (constant bounds, */     \
-      /* so the loops unroll fully and every register index is a constant) */                      \
-      /* (LOADS is a run-time condition: the branch holds loads only, so the */                   \
-      /* accumulators never meet at a join) */                                                     \
-      if (LOADS) {                                                                                 \
-        _Pragma("unroll") for (int l = 0; l < SL; ++l) {                                           \
-          if (l * NQ / SL == q) {                                                                  \
-            WDC_GEMM_LOAD1(lbuf, lkt, l);                                                          \
-          }                                                                                        \
-        }                                                                                          \
-      }                                                                                            \
-      __builtin_amdgcn_sched_barrier(0);                                                           \
-      if (READS) {                                                                                 \
-        _Pragma("unroll") for (int r = 0; r < NR; ++r) {                                           \
-          if (r * NQ / NR == q) {                                                                  \
-            WDC_GEMM_READ1(na, nb, rbuf, rs, r);                                                   \
-            __builtin_amdgcn_sched_barrier(0);                                                     \
-          }                                                                                        \
-        }                                                                                          \
-      }                                                                                            \
-    }                                                                                              \
-    (void)v_;                                                                                      \
+  // the loads that belong after MFMA q of LQ since the barrier (the branch holds
+  // loads only, so the accumulators never meet at a join)
+#define WDC_GEMM_LOADS(cond, lbuf, lkt, q)                                                         \
+  if (cond) {                                                                                      \
+    _Pragma("unroll") for (int l = 0; l < SL; ++l)                                                 \
+      if (l * LQ / SL == (q)) WDC_GEMM_LOAD1(lbuf, lkt, l)                                         \
   }
-  if constexpr (NQ <= 4) {
-    // Wave tiles of up to 64 x 64: a k-step is only 64 to 128 cycles of MFMAs,
-    // less than an LDS read takes, so the fragments are read two k-steps ahead
-    // (four sets, one per k-step) and early in a step. The stage barrier then
-    // sits before the third k-step, whose fragments and the fourth's are in
-    // registers by then.
-    bf16x8 fa[S][C::TM], fb[S][C::TN];
-    WDC_GEMM_READ(fa[0], fb[0], 0, 0);
-    WDC_GEMM_READ(fa[1], fb[1], 0, 1);
-    int buf = 0, prv = NB - 1, v2_ = va0;
-    for (int kt = 0; kt < nk; ++kt) {
-      const int nxt = NB == 2 ? buf ^ 1 : buf + 1 == NB ? 0 : buf + 1;
+  int buf = 0, prv = NB - 1;
+  for (int kt = 0; kt < nk; ++kt) {
+    const int nxt = NB == 2 ? buf ^ 1 : buf + 1 == NB ? 0 : buf + 1;
+    const bool ld0 = LQ > LQ0 && kt > 0 && kt + NB - 1 < nk && wu < NW;   // rest of the previous barrier's loads
 #pragma unroll
-      for (int st = 0; st < S; ++st) {
-        if (st == 2) {
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[0][j], fa[i], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (j == 0 && i < TN) WDC_GEMM_READB(buf, 1, i);
+        if (j == TN - 1) WDC_GEMM_READA(buf, 1, i);
+        __builtin_amdgcn_sched_barrier(0);
+        WDC_GEMM_LOADS(ld0, prv, kt + NB - 1, LQ0 + i * TN + j)
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    const bool ld1 = kt + NB < nk && wu < NW;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        if (i == D && j == 0) {
+          // stage kt + 1 has landed once only the loads of later stages are
+          // pending; after the barrier every wave is done with buffer buf. Past
+          // the last stage the reads fetch stale data, never used.
           if (wu < NW) {
             if (NB > 2 && kt + NB <= nk) __builtin_amdgcn_s_waitcnt(vm_wait((NB - 2) * SL));
             else __builtin_amdgcn_s_waitcnt(WAIT_VM0);
           }
           WDC_GEMM_BARRIER();
+          va = va0;
         }
-        // the stage NB ahead goes into the buffer that the barrier freed: with
-        // 64 x 64 wave tiles its loads are spread over the four k-steps from one
-        // barrier to the next (a burst stalls the wave that issues it: 2,688 x
-        // 4,096, K = 1,024 on 256 x 128 tiles 30.8 us against 32.2), with smaller
-        // ones, bound by the loads' latency, over the first two (226 x 3,072,
-        // K = 4,096 on 64 x 64 tiles 19.4 against 21.4)
-        constexpr int LSTEPS = NQ == 4 ? S : 2;
-        const int lkt = st >= 2 ? kt + NB : kt + NB - 1, lbuf = st >= 2 ? buf : prv, lst = (st + 2) % S;
-        const bool ld = lst < LSTEPS && lkt < nk && lkt >= NB && wu < NW;
-        const int rs = (st + 2) % S, rbuf = st < 2 ? buf : nxt;
-        if (st == 2) v2_ = va0;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[1][j], fa[i], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (i >= D) {
+          // the next stage's A0 and B0.. first, spread over the rows that are left
+          constexpr int BPR = (TN + TM - D - 1) / (TM - D);
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          WDC_GEMM_MFMA1(fa[st], fb[st], q);
-          __builtin_amdgcn_sched_barrier(0);
+          for (int b = 0; b < BPR; ++b)
+            if (j == b * TN / BPR && (i - D) * BPR + b < TN) WDC_GEMM_READB(nxt, 0, (i - D) * BPR + b);
+          if (j == TN - 1) {
+            WDC_GEMM_READA(nxt, 0, i - D);
+            if (i == TM - 1)
 #pragma unroll
-          for (int r = 0; r < NR; ++r)
-            if (r * NQ / (2 * NR) == q) {
-              WDC_GEMM_READ1(fa[rs], fb[rs], rbuf, rs, r);
-              __builtin_amdgcn_sched_barrier(0);
-            }
-          if (ld) {
-#pragma unroll
-            for (int l = 0; l < SL; ++l)
-              if (l * LSTEPS * NQ / SL == lst * NQ + q) {
-                int v_ = v2_;
-                WDC_GEMM_LOAD1(lbuf, lkt, l);
-                v2_ = v_;
-              }
+              for (int x = TM - D; x < TM; ++x) WDC_GEMM_READA(nxt, 0, x);
           }
           __builtin_amdgcn_sched_barrier(0);
+          WDC_GEMM_LOADS(ld1, buf, kt + NB, (i - D) * TN + j)
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
-      prv = buf;
-      buf = nxt;
-    }
-  } else {
-  bf16x8 xa[C::TM], xb[C::TN], ya[C::TM], yb[C::TN];
-    WDC_GEMM_READ(xa, xb, 0, 0);
-    int buf = 0;
-    for (int kt = 0; kt < nk; ++kt) {
-      const int nxt = NB == 2 ? buf ^ 1 : buf + 1 == NB ? 0 : buf + 1;
-      WDC_GEMM_STEP(xa, xb, ya, yb, buf, 1, true, 0, 0, false);
-      WDC_GEMM_STEP(ya, yb, xa, xb, buf, 2, true, 0, 0, false);
-      WDC_GEMM_STEP(xa, xb, ya, yb, buf, 3, true, 0, 0, false);
-      // stage kt+1 was requested a stage ago; after the barrier every wave's
-      // reads of buffer buf are complete. The last stage's step also reads the
-      // other buffer's first fragments: stale data, never used.
-      if (wu < NW) {
-        if (NB > 2 && kt + NB <= nk) __builtin_amdgcn_s_waitcnt(vm_wait((NB - 2) * SL));
-        else __builtin_amdgcn_s_waitcnt(WAIT_VM0);
-      }
-      WDC_GEMM_BARRIER();
-      const bool ld = kt + NB < nk && wu < NW;
-      WDC_GEMM_STEP(ya, yb, xa, xb, nxt, 0, true, buf, kt + NB, ld);
-      buf = nxt;
-    }
+    prv = buf;
+    buf = nxt;
   }
-#undef WDC_GEMM_STEP
+#undef WDC_GEMM_LOADS
 #undef WDC_GEMM_LOAD1
-#undef WDC_GEMM_READ1
-#undef WDC_GEMM_MFMA1
+#undef WDC_GEMM_READA
+#undef WDC_GEMM_READB
 
   const bf16_t *bias = (const bf16_t *)g.bias;
-  if (TR && STAGE_OUT) {
+  const int cb = wn * (BN / WN) + 4 * lg;                 // the lane's columns in the block: cb + 16 j + 0..3
+  if constexpr (OUT16 && STAGE_OUT) {
     // bf16 output staged through LDS (free once the last K stage is consumed:
     // every read that matters completed before the last stage barrier): each
     // wave writes its BM/WM x BN/WN tile into its own slice, row-major with the
@@ -666,25 +606,21 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
     constexpr int RB = BN / WN * 2, CPR = RB / 16, RPI = 1024 / RB, WR = BM / WM;
     static_assert(WR * RB * C::NT / 64 <= C::LDS_BYTES, "staging slices exceed LDS");
     char *wl = smem + wid * (WR * RB);
-    uint2 bw[C::TN][4];
+    uint2 bw[TN];
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j)
+    for (int j = 0; j < TN; ++j) bw[j] = bias ? *(const uint2 *)(bias + n0 + cb + 16 * j) : make_uint2(0, 0);
+    // the last stage's stale fragment reads may still be in flight; nothing
+    // else touches LDS
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        bw[j][q] = bias ? *(const uint2 *)(bias + n0 + wn * (BN / WN) + j * 32 + 4 * lg + 8 * q) : make_uint2(0, 0);
+    for (int j = 0; j < TN; ++j) {
+      const float b0 = bf2f((bf16_t)(bw[j].x & 0xffff)), b1 = bf2f((bf16_t)(bw[j].x >> 16));
+      const float b2 = bf2f((bf16_t)(bw[j].y & 0xffff)), b3 = bf2f((bf16_t)(bw[j].y >> 16));
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j) {
-#pragma unroll
-      for (int i = 0; i < C::TM; ++i) {
-        const int r = i * 32 + lr;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float b0 = bf2f((bf16_t)(bw[j][q].x & 0xffff)), b1 = bf2f((bf16_t)(bw[j][q].x >> 16));
-          const float b2 = bf2f((bf16_t)(bw[j][q].y & 0xffff)), b3 = bf2f((bf16_t)(bw[j][q].y >> 16));
-          const uint32_t w0 = pack_bf16(epi_act<EPI>(acc[i][j][4 * q + 0] + b0), epi_act<EPI>(acc[i][j][4 * q + 1] + b1));
-          const uint32_t w1 = pack_bf16(epi_act<EPI>(acc[i][j][4 * q + 2] + b2), epi_act<EPI>(acc[i][j][4 * q + 3] + b3));
-          *(uint2 *)(wl + r * RB + (((4 * j + q) ^ (r & 7)) * 16) + 8 * lg) = make_uint2(w0, w1);
-        }
+      for (int i = 0; i < TM; ++i) {
+        const int r = i * 16 + lr;
+        const uint32_t w0 = pack_bf16(epi_act<EPI>(acc[i][j][0] + b0), epi_act<EPI>(acc[i][j][1] + b1));
+        const uint32_t w1 = pack_bf16(epi_act<EPI>(acc[i][j][2] + b2), epi_act<EPI>(acc[i][j][3] + b3));
+        *(uint2 *)(wl + r * RB + (((2 * j + (lg >> 1)) ^ (r & 7)) * 16) + 8 * (lg & 1)) = make_uint2(w0, w1);
       }
     }
     if constexpr (EPI == EPI_QKV) {
@@ -718,99 +654,68 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
       if (row < g.m)
         __builtin_nontemporal_store(v, (u32x4_t *)((bf16_t *)g.c + row * g.ldc + n0 + wn * (BN / WN) + ch * 8));
     }
-  } else if constexpr (TR) {
-    // bf16 output: lane (lr, lg) of tile (i, j) holds row lr of the 32x32 output
-    // tile and, in accumulator entries 4q..4q+3, the four consecutive columns
-    // 8q + 4lg + 0..3, stored as one 8-byte group. The bias of all the lane's
+  } else if constexpr (OUT16) {
+    // bf16 output in 8-byte groups of 4 columns. The bias of all the lane's
     // columns is read before the first store, so one wait covers every read.
-    uint2 bw[C::TN][4];
+    uint2 bw[TN];
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j)
+    for (int j = 0; j < TN; ++j) bw[j] = bias ? *(const uint2 *)(bias + n0 + cb + 16 * j) : make_uint2(0, 0);
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        bw[j][q] = bias ? *(const uint2 *)(bias + n0 + wn * (BN / WN) + j * 32 + 4 * lg + 8 * q) : make_uint2(0, 0);
+    for (int i = 0; i < TM; ++i) {
+      const int64_t row = m0 + wm * (BM / WM) + i * 16 + lr;
+      if (row >= g.m) continue;
+      bf16_t *out = (bf16_t *)g.c + row * g.ldc + n0 + cb;
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j) {
-      const int64_t cb = n0 + wn * (BN / WN) + j * 32 + 4 * lg;   // column of group q: cb + 8 q
-      float bq[4][4];                                               // bias of the lane's 16 columns
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        bq[q][0] = bf2f((bf16_t)(bw[j][q].x & 0xffff));
-        bq[q][1] = bf2f((bf16_t)(bw[j][q].x >> 16));
-        bq[q][2] = bf2f((bf16_t)(bw[j][q].y & 0xffff));
-        bq[q][3] = bf2f((bf16_t)(bw[j][q].y >> 16));
-      }
-#pragma unroll
-      for (int i = 0; i < C::TM; ++i) {
-        const int64_t row = m0 + wm * (BM / WM) + i * 32 + lr;
-        if (row >= g.m) continue;
-        bf16_t *out = (bf16_t *)g.c + row * g.ldc + cb;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const uint32_t w0 = pack_bf16(epi_act<EPI>(acc[i][j][4 * q + 0] + bq[q][0]),
-                                        epi_act<EPI>(acc[i][j][4 * q + 1] + bq[q][1]));
-          const uint32_t w1 = pack_bf16(epi_act<EPI>(acc[i][j][4 * q + 2] + bq[q][2]),
-                                        epi_act<EPI>(acc[i][j][4 * q + 3] + bq[q][3]));
-          *(uint2 *)(out + 8 * q) = make_uint2(w0, w1);
-        }
+      for (int j = 0; j < TN; ++j) {
+        const float b0 = bf2f((bf16_t)(bw[j].x & 0xffff)), b1 = bf2f((bf16_t)(bw[j].x >> 16));
+        const float b2 = bf2f((bf16_t)(bw[j].y & 0xffff)), b3 = bf2f((bf16_t)(bw[j].y >> 16));
+        const uint32_t w0 = pack_bf16(epi_act<EPI>(acc[i][j][0] + b0), epi_act<EPI>(acc[i][j][1] + b1));
+        const uint32_t w1 = pack_bf16(epi_act<EPI>(acc[i][j][2] + b2), epi_act<EPI>(acc[i][j][3] + b3));
+        *(uint2 *)(out + 16 * j) = make_uint2(w0, w1);
       }
     }
   } else {
-    // float32 output: lane holds column lr of each 32x32 tile, rows
-    // 8 (e / 4) + 4 lg + e % 4; 32 lanes cover one 128-byte line per row
-    float bvs[C::TN], gvs[C::TN];
+    // float32 output, 16 bytes of a row per lane (64 of it per quad of lanes).
+    // The residual reads of two tile rows go out together, before their stores:
+    // vmcnt also counts stores, and a read behind each store would serialise
+    // every read-modify-write.
+    constexpr int RI = TM >= 2 ? 2 : 1;
+    f32x4 bv[TN], gv[TN];
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j) {
-      const int64_t col = n0 + wn * (BN / WN) + j * 32 + lr;
-      bvs[j] = bias ? bf2f(bias[col]) : 0.f;
-      gvs[j] = RES ? g.gate[col] : 0.f;
+    for (int j = 0; j < TN; ++j) {
+      const uint2 bw = bias ? *(const uint2 *)(bias + n0 + cb + 16 * j) : make_uint2(0, 0);
+      bv[j] = f32x4{bf2f((bf16_t)(bw.x & 0xffff)), bf2f((bf16_t)(bw.x >> 16)), bf2f((bf16_t)(bw.y & 0xffff)),
+                    bf2f((bf16_t)(bw.y >> 16))};
+      if (RES) gv[j] = *(const f32x4 *)(g.gate + n0 + cb + 16 * j);
     }
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j) {
-      const int64_t col = n0 + wn * (BN / WN) + j * 32 + lr;
-      const float bv = bvs[j], gv = gvs[j];
+    for (int i0 = 0; i0 < TM; i0 += RI) {
+      f32x4 xr[RI][TN];
+      f32x4 *xp[RI];
+      bool in[RI];
 #pragma unroll
-      for (int i = 0; i < C::TM; ++i) {
-        const int64_t rb = m0 + wm * (BM / WM) + i * 32 + 4 * lg;   // row of element e: rb + 8 (e / 4) + e % 4
-        float *xc = (float *)g.c + rb * g.ldc + col;
-        if (m0 + wm * (BM / WM) + i * 32 + 32 <= g.m) {
-          // whole 32-row tile inside m (uniform per wave): no per-element guard, so
-          // the residual reads go out together (vmcnt also counts stores, and a
-          // guarded store per element would serialise every read-modify-write)
-          if constexpr (RES) {
-            float xr[16];
-            if constexpr (EPI == EPI_GATE_RES_NT) {
+      for (int u = 0; u < RI; ++u) {
+        const int64_t row = m0 + wm * (BM / WM) + (i0 + u) * 16 + lr;
+        in[u] = row < g.m;
+        xp[u] = (f32x4 *)((float *)g.c + row * g.ldc + n0 + cb);
+        if (RES && in[u])
 #pragma unroll
-              for (int e = 0; e < 16; ++e) xr[e] = __builtin_nontemporal_load(&xc[(8 * (e / 4) + (e % 4)) * g.ldc]);
+          for (int j = 0; j < TN; ++j)
+            xr[u][j] = EPI == EPI_GATE_RES_NT ? __builtin_nontemporal_load(xp[u] + 4 * j) : xp[u][4 * j];
+      }
 #pragma unroll
-              for (int e = 0; e < 16; ++e)
-                __builtin_nontemporal_store(xr[e] + gv * (acc[i][j][e] + bv), &xc[(8 * (e / 4) + (e % 4)) * g.ldc]);
-            } else {
+      for (int u = 0; u < RI; ++u) {
+        if (!in[u]) continue;
 #pragma unroll
-              for (int e = 0; e < 16; ++e) xr[e] = xc[(8 * (e / 4) + (e % 4)) * g.ldc];
-#pragma unroll
-              for (int e = 0; e < 16; ++e) xc[(8 * (e / 4) + (e % 4)) * g.ldc] = xr[e] + gv * (acc[i][j][e] + bv);
-            }
-          } else {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) xc[(8 * (e / 4) + (e % 4)) * g.ldc] = acc[i][j][e] + bv;
-          }
-          continue;
-        }
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int64_t row = rb + 8 * (e / 4) + (e % 4);
-          if (row >= g.m) continue;
-          float *x = (float *)g.c + row * g.ldc + col;
-          if (RES)
-            *x += gv * (acc[i][j][e] + bv);
-          else
-            *x = acc[i][j][e] + bv;
+        for (int j = 0; j < TN; ++j) {
+          f32x4 v = acc[i0 + u][j] + bv[j];
+          if (RES) v = xr[u][j] + gv[j] * v;
+          if (EPI == EPI_GATE_RES_NT) __builtin_nontemporal_store(v, xp[u] + 4 * j);
+          else xp[u][4 * j] = v;
         }
       }
     }
   }
-#undef WDC_GEMM_READ
 #undef WDC_GEMM_BARRIER
 #undef WDC_GEMM_LOAD
 }
