@@ -503,7 +503,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
   // fragments are in registers by then: after it the stage NB ahead goes into
   // the buffer just consumed and the next stage's first fragments are read. A
   // scheduling barrier after each MFMA, read and load keeps that order.
-  constexpr int D = TM == 8 ? 2 : 1;
+  constexpr int D = 1;   // 2, 3 and 4 were 0.5 to 2% slower on the large products
   static_assert(BK == 64 && D < TM && TN <= TM, "two k-steps per stage");
   // Loads of a stage go one by one between MFMAs: within the rest of the second
   // k-step with two buffers (they have the next stage to arrive in), spread on
