@@ -6,13 +6,13 @@
 //    SIMD; K tiles [64 keys][hd] and V^T tiles [hd][64 keys] reach LDS by
 //    direct buffer loads, issued three or four tile steps ahead by four of the
 //    waves;
-//  * S^T = K Q^T with v_mfma_f32_32x32x16_bf16: the accumulator of a 32x32
-//    tile gives lane l one query (l % 32) and 16 keys, so a query's row
-//    statistics live in one lane and its partner l ^ 32 (one exchange);
+//  * S^T = K Q^T with v_mfma_f32_16x16x32_bf16: the accumulator of a 16x16
+//    tile gives lane l one query (l % 16) and 4 keys, so a query's row
+//    statistics live in four lanes (two exchanges);
 //  * O^T = V^T P^T reuses the S^T accumulators directly as the B operand: the
-//    8 accumulator values a lane holds for 16 consecutive keys become its 8
-//    bf16 k-values, and the V^T operand is read with the same key order, so P
-//    never goes through LDS;
+//    4 + 4 accumulator values a lane holds of two key tiles become its 8 bf16
+//    k-values, and the K rows of those tiles are chosen so that these are the 8
+//    keys of one 16-byte chunk of the V^T layout (krow); P never goes through LDS;
 //  * softmax in base 2 against a per-row reference max, each step running the
 //    vector work of tile t + 1 inside the MFMA stream of tiles t and t + 2
 //    (k_attn_bf16_ppr3);
@@ -180,20 +180,30 @@ constexpr int KV = 64;                   // keys per LDS tile
 constexpr int RSRC_WORD3 = 0x00020000;   // raw buffer descriptor word 3
 constexpr int WAIT_VM0 = 0x0F70;         // s_waitcnt vmcnt(0), other counters untouched
 
+// Key of row r of a 16-row K fragment (h8 = 0 or 1: the two fragments of a group
+// of 32 keys): r bits 0-2, 8 h8, 16 x r bit 3. Lane group lg then holds, in the
+// accumulators of the two fragments, the keys of V^T slot lg of that group.
+__device__ __forceinline__ int krow(int r, int h8) { return (r & 7) | ((r & 8) << 1) | (h8 << 3); }
+
 // LDS swizzles: 16 consecutive lanes read 16 different rows at one logical
 // chunk; the XOR spreads them over distinct bank groups of the 64 x 4-byte banks.
-// K tile: rows of HD bf16 = HD/8 16-byte chunks. hd = 128 (256-byte rows):
-// chunk c of row r at c ^ (r & 15); hd = 64 (128-byte rows, two per bank span):
-// c ^ ((r >> 1) & 7).
+// K tile: rows of HD bf16 = HD/8 16-byte chunks, rows krow(0..15) of a group read
+// together. hd = 128 (256-byte rows): chunk c of row r at c ^ (r bits 0-2, bit 4);
+// hd = 64 (128-byte rows, two per bank span): c ^ (r bits 1-2, bit 4).
+template <int HD>
+__device__ __forceinline__ int kkey(int r) {
+  return HD == 128 ? (r & 7) | ((r & 16) >> 1) : ((r >> 1) & 3) | ((r & 16) >> 2);
+}
 template <int HD>
 __device__ __forceinline__ int kswz(int r, int c) {
-  return HD == 128 ? (r * 16 + (c ^ (r & 15))) * 16 : (r * 8 + (c ^ ((r >> 1) & 7))) * 16;
+  return (r * (HD / 8) + (c ^ kkey<HD>(r))) * 16;
 }
 // V^T tile: rows of 64 keys (128 B) = 8 16-byte slots. Within 16-key group j,
 // slot 2j holds keys 16j+[0,4) and 16j+8+[0,4), slot 2j+1 keys 16j+4+[0,4) and
-// 16j+12+[0,4): exactly the 8 keys lane group 0 / 1 feeds to one 32x32x16 step
-// of O^T = V^T P^T (the key order of the S^T accumulator), so each A operand is
-// one 16-byte read. Slot p of row r lives at p ^ ((r >> 1) & 7).
+// 16j+12+[0,4): the four slots of 32 keys are the 8 keys that lane groups 0 to 3
+// feed to one 16x16x32 step of O^T = V^T P^T (the key order of the S^T
+// accumulators, see krow), so each A operand is one 16-byte read. Slot p of row r
+// lives at p ^ ((r >> 1) & 7).
 __device__ __forceinline__ int vslot(int r, int p) { return (r * 8 + (p ^ ((r >> 1) & 7))) * 16; }
 
 // Direct global -> LDS tile loads (buffer_load_dwordx4 ... lds): lane L of a
@@ -204,8 +214,9 @@ __device__ __forceinline__ int vslot(int r, int p) { return (r * 8 + (p ^ ((r >>
 //   V^T tile: stripe holds 8 rows of 128 bytes (the global V^T rows are stored
 //             with the slot key order already applied, see k_v_transpose).
 // Stripe i of wave w starts at LDS byte w*1024 + i*4096 in both tiles; the row
-// swizzle keys are the same for every stripe of a wave, so one VGPR offset per
-// tile kind plus a uniform SGPR offset per stripe addresses the global side.
+// swizzle keys are the same for every stripe of a wave (at hd 128 those of K for
+// every second one), so one or two VGPR offsets per tile kind plus a uniform
+// SGPR offset per stripe address the global side.
 typedef __attribute__((address_space(3))) void lds_void;
 // (kept out of line of the kernel templates: called directly from a template
 // kernel body the builtin makes the host pass drop the kernel's launch stub)
@@ -217,11 +228,11 @@ struct TileLoad {
   static constexpr int K_ROWS = 1024 / (2 * HD);   // K rows per 1 KB stripe (4 or 8)
   static constexpr int K_STRIPES = 16 / K_ROWS;    // stripes per wave per K tile (4 or 2)
   static constexpr int V_STRIPES = HD / 32;        // stripes per wave per V^T tile (4 or 2)
-  int kvo, vvo;                                    // per-lane global byte offsets (stripe 0, tile 0)
+  int kvo[2], vvo;                                 // per-lane global byte offsets (tile 0; K: even, odd stripes)
   __device__ __forceinline__ TileLoad(int w, int lane, int64_t n_pad) {
     const int kr0 = w * K_ROWS + lane / (HD / 8), kps = lane % (HD / 8);
-    const int kc = HD == 128 ? (kps ^ (kr0 & 15)) : (kps ^ ((kr0 >> 1) & 7));
-    kvo = kr0 * HD * 2 + kc * 16;
+    kvo[0] = kr0 * HD * 2 + (kps ^ kkey<HD>(kr0)) * 16;
+    kvo[1] = kr0 * HD * 2 + (kps ^ kkey<HD>(kr0 + 4 * K_ROWS)) * 16;   // stripe i: rows kr0 + 4 K_ROWS i
     const int vr0 = 8 * w + lane / 8, vps = lane % 8;
     vvo = vr0 * (int)n_pad * 2 + (vps ^ ((vr0 >> 1) & 7)) * 16;
   }
@@ -239,9 +250,12 @@ __device__ __forceinline__ void pp_wait4(int n_outstanding) {
     __builtin_amdgcn_s_waitcnt(WAIT_VM0);
 }
 
+// A wave's 32 queries are two tiles t of 16: lane (lr, lg) holds query lr of
+// both. S' of a 64-key tile is S[kt][t]: key tiles kt = 2 p + h8 of 16 keys, four
+// of them per lane.
 // Vector phase: Q is scaled by sc = log2(e)/sqrt(HD) once, and -m is the
-// accumulator input of the first Q K MFMA of each 32-key half (a lane holds one
-// query, so the tile is -m in all 16 values), so the matrix phase hands over
+// accumulator input of the first Q K MFMA of each key tile (a lane holds one
+// query per tile, so all four values are -m), so the matrix phase hands over
 // S' = sc Q K^T - m and the vector phase is P = exp2(S'), its bf16 conversion
 // and the row sum of those bf16 values (the weights the PV product uses). m is
 // a reference, not a running max: the first tile's row max, moved to a row's
@@ -253,43 +267,53 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 constexpr float PPR_LIMIT = 0x1p64f;
 
 // accumulator tile that starts a row's Q K contraction at -m
-__device__ __forceinline__ f32x16 ppr_mtile(float m) {
-  f32x16 t;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) t[e] = -m;
-  return t;
-}
+__device__ __forceinline__ f32x4 ppr_mtile(float m) { return f32x4{-m, -m, -m, -m}; }
 
 template <int HD>
-__device__ __forceinline__ void ppr_qk(f32x16 (&S)[2], const char *k, const bf16x8 (&qf)[HD / 16],
-                                       const int (&kro)[HD / 16], const f32x16 &mi) {
+__device__ __forceinline__ void ppr_qk(f32x4 (&S)[4][2], const char *k, const bf16x8 (&qf)[2][HD / 32],
+                                       const int (&kro)[HD / 32][2], const f32x4 (&mi)[2]) {
 #pragma unroll
-  for (int st_ = 0; st_ < HD / 16; ++st_)
+  for (int c = 0; c < HD / 32; ++c)
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      const bf16x8 kf = *(const bf16x8 *)(k + kro[st_] + kt * 32 * HD * 2);
-      S[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[st_], st_ == 0 ? mi : S[kt], 0, 0, 0);
+    for (int kt = 0; kt < 4; ++kt) {
+      const bf16x8 kf = *(const bf16x8 *)(k + kro[c][kt & 1] + (kt >> 1) * 32 * HD * 2);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        S[kt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[t][c], c == 0 ? mi[t] : S[kt][t], 0, 0, 0);
     }
 }
 
-// row max over the tile's 64 keys (32 per lane, the rest in lane l ^ 32)
-__device__ __forceinline__ float ppr_rowmax(const f32x16 (&S)[2]) {
-  float mx = fmaxf(S[0][0], S[1][0]);
-#pragma unroll
-  for (int e = 1; e < 16; ++e) mx = fmaxf(mx, fmaxf(S[0][e], S[1][e]));
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+// key of the lane's entry e of key tile kt within the 64-key tile
+__device__ __forceinline__ int ppr_key(int kt, int lg, int e) { return 32 * (kt >> 1) + krow(4 * lg, kt & 1) + e; }
+
+// max and sum over the four lanes of a query
+__device__ __forceinline__ float quad_max(float v) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-__device__ __forceinline__ float ppr_exp(const f32x16 (&S)[2], bf16x8 (&pf)[4]) {
+// row max over the tile's 64 keys (16 per lane, the rest in the query's other lanes)
+__device__ __forceinline__ float ppr_rowmax(const f32x4 (&S)[4][2], int t) {
+  float mx = S[0][t][0];
+#pragma unroll
+  for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) mx = fmaxf(mx, S[kt][t][e]);
+  return quad_max(mx);
+}
+
+// P of one query tile: pf[p] holds the lane's 8 keys of the 32-key group p
+__device__ __forceinline__ float ppr_exp(const f32x4 (&S)[4][2], bf16x8 (&pf)[2], int t) {
   const bf16x2_t one2 = {(__bf16)1.f, (__bf16)1.f};
   float ls = 0.f;
 #pragma unroll
-  for (int kt = 0; kt < 2; ++kt)
+  for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) pf[2 * kt + e / 8][e % 8] = (__bf16)__builtin_amdgcn_exp2f(S[kt][e]);
+    for (int e = 0; e < 4; ++e) pf[kt >> 1][4 * (kt & 1) + e] = (__bf16)__builtin_amdgcn_exp2f(S[kt][t][e]);
 #pragma unroll
-  for (int q = 0; q < 16; ++q)
+  for (int q = 0; q < 8; ++q)
     ls = __builtin_amdgcn_fdot2_f32_bf16(bf16x2_t{pf[q / 4][2 * (q % 4)], pf[q / 4][2 * (q % 4) + 1]}, one2, ls,
                                          false);
   return ls;
@@ -300,20 +324,19 @@ __device__ __forceinline__ float ppr_exp(const f32x16 (&S)[2], bf16x8 (&pf)[4]) 
 // reference maxima m and row sums l go to slot (j * 256 + query) of the
 // scratch: O at part + slot * HD, (m, l) at part + slots * HD + 2 slot.
 template <int HD>
-__device__ __forceinline__ void attn_split_store(const AttnArgs &a, const f32x16 (&o)[HD / 32], float m, float lt,
-                                                 int j) {
-  const int lane = threadIdx.x & 63, lr = lane & 31, lg = lane >> 5, wid = threadIdx.x >> 6;
+__device__ __forceinline__ void attn_split_store(const AttnArgs &a, const f32x4 (&o)[HD / 16][2], const float (&m)[2],
+                                                 const float (&lt)[2], int j) {
+  const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4, wid = threadIdx.x >> 6;
   const int tail = (int)(a.n_pad / 256) - a.qb_main;
   const int64_t slots = (int64_t)a.heads * tail * a.kv_splits * 256;
-  const int64_t slot = (int64_t)j * 256 + wid * 32 + lr;
-  float *po = a.part + slot * HD;
 #pragma unroll
-  for (int i = 0; i < HD / 32; ++i)
+  for (int t = 0; t < 2; ++t) {
+    const int64_t slot = (int64_t)j * 256 + wid * 32 + 16 * t + lr;
+    float *po = a.part + slot * HD;
 #pragma unroll
-    for (int g4 = 0; g4 < 4; ++g4)
-      *(float4 *)(po + 32 * i + 8 * g4 + 4 * lg) =
-          make_float4(o[i][4 * g4], o[i][4 * g4 + 1], o[i][4 * g4 + 2], o[i][4 * g4 + 3]);
-  if (lg == 0) *(float2 *)(a.part + slots * HD + 2 * slot) = make_float2(m, lt);
+    for (int i = 0; i < HD / 16; ++i) *(f32x4 *)(po + 16 * i + 4 * lg) = o[i][t];
+    if (lg == 0) *(float2 *)(a.part + slots * HD + 2 * slot) = make_float2(m[t], lt[t]);
+  }
 }
 
 // Combine of the split round, after the attention launch: for each of its
@@ -362,7 +385,15 @@ __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
                                  (uint32_t)f2bf(acc[6] * inv) | ((uint32_t)f2bf(acc[7] * inv) << 16));
 }
 
-// bf16 flash attention. 8 wavefronts per block (two per SIMD), 32 queries each
+// bf16 flash attention, bound by the matrix cores at the power limit, where the
+// instruction shape sets the rate: a loop of 16x16x32 MFMAs on random operands
+// sustains 2,065 TFLOP/s with two waves per SIMD, one of 32x32x16 1,500. Same-box
+// against the 32x32x16 form with the same tiles, reads and schedule: hd 128, 24
+// heads, 33,000 tokens 9.93 -> 9.04 ms (1,479 TFLOP/s), 9,001 tokens 824 -> 761
+// us; hd 64, 48 heads, 17,776 tokens 3.36 -> 3.27 ms (1,185). Between a pair's two
+// MFMAs one exponential fits (hd 128: 9.45 ms with it after both; hd 64, two per
+// pair: 3.27 ms after both, 3.33 between them).
+// 8 wavefronts per block (two per SIMD), 32 queries each
 // (256 per block); K tiles of 64 keys and V^T tiles reach four K and four V^T
 // LDS slots by direct buffer loads issued by waves 0-3; one block barrier per
 // tile step. Step t runs the P V MFMAs of
@@ -413,18 +444,20 @@ __global__ __launch_bounds__(512, 1) void k_attn_bf16_ppr3(AttnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool grp_a = wid < 4;
-  const int lr = lane & 31, lg = lane >> 5;
+  const int lr = lane & 15, lg = lane >> 4;
   const int64_t qbase = (int64_t)qb * QB + wid * 32;
   const bf16_t *Q = (const bf16_t *)a.q + (int64_t)h * a.n_pad * HD;
 
   const float sc = 1.4426950408889634f * rsqrtf((float)HD);
-  bf16x8 qf[HD / 16];                      // Q^T scaled by sc: scores in log2 units
+  bf16x8 qf[2][HD / 32];                   // Q^T scaled by sc: scores in log2 units
 #pragma unroll
-  for (int s = 0; s < HD / 16; ++s) {
-    const bf16x8 raw = *(const bf16x8 *)(Q + (qbase + lr) * HD + 16 * s + 8 * lg);
+  for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) qf[s][j] = (__bf16)((float)raw[j] * sc);
-  }
+    for (int c = 0; c < HD / 32; ++c) {
+      const bf16x8 raw = *(const bf16x8 *)(Q + (qbase + 16 * t + lr) * HD + 32 * c + 8 * lg);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) qf[t][c][j] = (__bf16)((float)raw[j] * sc);
+    }
 
   // key tiles [t_first, t_first + ntiles) of tiles_all (all of them outside
   // the split round); only the range that ends the sequence holds the partial
@@ -444,17 +477,19 @@ __global__ __launch_bounds__(512, 1) void k_attn_bf16_ppr3(AttnArgs a) {
       (int)((a.n_pad * HD - key0) * 2), RSRC_WORD3);
   const int lw = wid & 3;
   const TileLoad<HD> tl(lw, lane, a.n_pad);
-  int kro[HD / 16];
+  int kro[HD / 32][2];                     // K fragment offsets: dims 32 c.., fragment h8 of a 32-key group
 #pragma unroll
-  for (int s = 0; s < HD / 16; ++s) kro[s] = kswz<HD>(lr, 2 * s + lg);
-  int vro[4];                              // V^T fragment offsets, V region base folded in
+  for (int c = 0; c < HD / 32; ++c)
 #pragma unroll
-  for (int j = 0; j < 4; ++j) vro[j] = V_BASE + vslot(lr, 2 * j + lg);
+    for (int h8 = 0; h8 < 2; ++h8) kro[c][h8] = kswz<HD>(krow(lr, h8), 4 * c + lg);
+  int vro[2];                              // V^T fragment offsets of 32-key group p, V region base folded in
+#pragma unroll
+  for (int p = 0; p < 2; ++p) vro[p] = V_BASE + vslot(lr, 4 * p + lg);
 
   auto load_k = [&](int b, int tile) {
 #pragma unroll
     for (int i = 0; i < TL::K_STRIPES; ++i)
-      lds_load16(kdesc, smem + b * K_BYTES + lw * 1024 + i * 4096, tl.kvo, tile * KV * HD * 2 + i * 4096);
+      lds_load16(kdesc, smem + b * K_BYTES + lw * 1024 + i * 4096, tl.kvo[i & 1], tile * KV * HD * 2 + i * 4096);
   };
   auto load_v = [&](int b, int tile) {
 #pragma unroll
@@ -474,55 +509,72 @@ __global__ __launch_bounds__(512, 1) void k_attn_bf16_ppr3(AttnArgs a) {
   }
   __syncthreads();
 
-  f32x16 o[HD / 32];
+  f32x4 o[HD / 16][2];
 #pragma unroll
-  for (int i = 0; i < HD / 32; ++i)
+  for (int i = 0; i < HD / 16; ++i)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) o[i][e] = 0.f;
-  float m = 0.f, l = 0.f;
-  f32x16 mi = ppr_mtile(m);
-  f32x16 S[2][2];                          // S' of tiles t + 1 and t + 2 (index tile & 1)
-  bf16x8 pf[2][4];                         // P of tiles t and t + 1 (index tile & 1)
+    for (int t = 0; t < 2; ++t) o[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m[2] = {0.f, 0.f}, l[2];
+  f32x4 mi[2] = {ppr_mtile(0.f), ppr_mtile(0.f)};
+  f32x4 S[2][4][2];                        // S' of tiles t + 1 and t + 2 (index tile & 1)
+  bf16x8 pf[2][2][2];                      // P of tiles t and t + 1 (index tile & 1), [query tile][32-key group]
   ppr_qk<HD>(S[0], smem, qf, kro, mi);
   {                                        // m = the first tile's row max
     const int v0 = ntiles == 1 ? last_valid : KV;
     if (v0 < KV) {
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+      for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
-          if (32 * kt + 8 * (e / 4) + 4 * lg + (e % 4) >= v0) S[0][kt][e] = -1e30f;
+        for (int e = 0; e < 4; ++e)
+          if (ppr_key(kt, lg, e) >= v0) S[0][kt][0][e] = S[0][kt][1][e] = -1e30f;
     }
-    m = ppr_rowmax(S[0]);
-    mi = ppr_mtile(m);
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
+    for (int t = 0; t < 2; ++t) {
+      m[t] = ppr_rowmax(S[0], t);
+      mi[t] = ppr_mtile(m[t]);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) S[0][kt][e] -= m;
-    l = ppr_exp(S[0], pf[0]);
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) S[0][kt][t][e] -= m[t];
+      l[t] = ppr_exp(S[0], pf[0][t], t);
+    }
   }
   if (ntiles > 1) ppr_qk<HD>(S[1], smem + K_BYTES, qf, kro, mi);
   // step 0 refills the slot of K_0, which every wave has just read
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
-  constexpr int NMF = 4 * (HD / 32) + 2 * (HD / 16);   // fragment reads per step
+  constexpr int NMF = 2 * (HD / 16) + 4 * (HD / 32);   // fragment reads per step, two MFMAs each
   static_assert(NMF == 16 || NMF == 32, "hd 64 or 128");
-  constexpr int NPV = NMF / 2;             // P V reads (and MFMAs) per step; as many Q K
-  constexpr int EPM = 32 / NMF;            // exponentials after each MFMA (32 per step)
+  constexpr int NPV = NMF / 2;             // P V reads per step; as many Q K
+  constexpr int EPM = 32 / NMF;            // exponentials after each pair of MFMAs (32 per step)
   // V^T tiles are loaded three steps ahead, so the tile of step t + 1 is
   // published by the barrier that ends step t - 1 and step t issues its first
   // four fragment reads after its own MFMA stream: the next step's first MFMA
   // finds its operand in registers instead of waiting on LDS after the barrier.
   const bf16x2_t one2_ = {(__bf16)1.f, (__bf16)1.f};
-  // fragment read r of a step from V^T slot vb and K slot kb: r < NPV V^T (k-step
-  // r / (HD/32), O tile r % (HD/32)), then K (hd step (r-NPV) / 2, key half (r-NPV) % 2)
+  // fragment read r of a step from V^T slot vb and K slot kb: r < NPV V^T (32-key
+  // group r / (HD/16), O tile r % (HD/16)), then K (dims 32 (g / 4).., key tile g % 4, g = r - NPV)
 #define WDC_PPR3_READ(r, vb, kb)                                                                 \
   {                                                                                              \
+    const int g__ = (r) >= NPV ? (r) - NPV : 0;                                                  \
     if ((r) < NPV)                                                                               \
-      fr_[(r)] = *(const bf16x8 *)((vb) + ((r) % (HD / 32)) * 32 * KV * 2 + vro[(r) / (HD / 32)]);\
+      fr_[(r)] = *(const bf16x8 *)((vb) + ((r) % (HD / 16)) * 16 * KV * 2 + vro[((r) < NPV ? (r) : 0) / (HD / 16)]);\
     else                                                                                         \
-      fr_[(r)] = *(const bf16x8 *)((kb) + kro[((r) >= NPV ? (r) - NPV : 0) / 2] +                \
-                                   (((r) >= NPV ? (r) - NPV : 0) % 2) * 32 * HD * 2);            \
+      fr_[(r)] = *(const bf16x8 *)((kb) + kro[g__ / 4][g__ & 1] + ((g__ % 4) >> 1) * 32 * HD * 2); \
+  }
+  // MFMA of pair q_ for query tile T
+#define WDC_PPR3_MFMA(T)                                                                         \
+  {                                                                                              \
+    if (q_ < NPV) {                                                                              \
+      constexpr int NI = HD / 16;                                                                \
+      o[q_ % NI][T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr_[q_], pf[n][T][(q_ < NPV ? q_ : 0) / NI],\
+                                                              o[q_ % NI][T], 0, 0, 0);           \
+    } else {                                                                                     \
+      const int g_ = q_ >= NPV ? q_ - NPV : 0;                                                   \
+      S[n][g_ % 4][T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr_[q_], qf[T][g_ / 4],          \
+                                                                g_ < 4 ? mi[T] : S[n][g_ % 4][T], 0, 0, 0);\
+    }                                                                                            \
+    __builtin_amdgcn_sched_barrier(0);                                                           \
   }
   bf16x8 fr_[NMF];
 #pragma unroll
@@ -548,80 +600,78 @@ __global__ __launch_bounds__(512, 1) void k_attn_bf16_ppr3(AttnArgs a) {
     const bool soft = t + 1 < ntiles;                                                            \
     if (t + 2 == ntiles && last_valid < KV) {  /* tile t + 1 is the partial last one */          \
       asm volatile("" ::: "memory");                                                             \
-      _Pragma("unroll") for (int kt = 0; kt < 2; ++kt)                                           \
-      _Pragma("unroll") for (int e = 0; e < 16; ++e)                                             \
-        if (32 * kt + 8 * (e / 4) + 4 * lg + (e % 4) >= last_valid) S[c][kt][e] = -1e30f;        \
+      _Pragma("unroll") for (int kt = 0; kt < 4; ++kt)                                           \
+      _Pragma("unroll") for (int e = 0; e < 4; ++e)                                              \
+        if (ppr_key(kt, lg, e) >= last_valid) S[c][kt][0][e] = S[c][kt][1][e] = -1e30f;          \
     }                                                                                            \
     __builtin_amdgcn_sched_barrier(0);                                                           \
     /* One fixed-order stream (unconditional: past the end the Q K reads a stale */              \
-    /* K slot and the exponentials a stale S', and neither result is used). MFMA */              \
-    /* q: 0-15 P V (k-step j = q / (HD/32), O tile i = q % (HD/32)), 16-31 Q K (hd */            \
-    /* step (q-16) / 2, key half q % 2; hd step 0 starts from the -m tile); */                   \
-    /* fragment read q goes out four reads ahead of its MFMA (reads 0-3 in the */                \
-    /* previous step); after MFMA q comes exponential q of S'_{t+1}, after every */              \
-    /* second one the bf16 pair and its row-sum dot product. */                                  \
+    /* K slot and the exponentials a stale S', and neither result is used). Pair of */           \
+    /* MFMAs q (one per query tile): first P V (32-key group q / (HD/16), O tile q % */          \
+    /* (HD/16)), then Q K (dims 32 (g / 4).., key tile g % 4, g = q - NPV; the first */          \
+    /* dims start from the -m tile); fragment read q goes out four reads ahead of its */         \
+    /* MFMAs (reads 0-3 in the previous step). Exponential x of S'_{t+1} is key tile */          \
+    /* x / 8, query tile (x / 4) % 2, entry x % 4: one per pair at hd 128, two at hd 64; */      \
+    /* both of a bf16 pair are converted together, then its row-sum dot product. The */          \
+    /* empty asm pins them under these MFMAs (left free, the compiler sinks them past */         \
+    /* the stream, where they no longer overlap the matrix cores). */                            \
     const char *vb_ = smem + (P) * K_BYTES, *kb_ = smem + (((P) + 2) % NB) * K_BYTES;            \
     const char *vn_ = smem + (((P) + 1) % NB) * K_BYTES;   /* V^T slot of tile t + 1 */          \
-    float ls = 0.f;                                                                              \
+    float ls[2] = {0.f, 0.f}, ex_[2];                                                           \
     _Pragma("unroll") for (int q_ = 0; q_ < NMF; ++q_) {                                         \
-      if (q_ < NPV) {                                                                            \
-        constexpr int NI = HD / 32;                                                              \
-        o[q_ % NI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr_[q_], pf[n][q_ / NI], o[q_ % NI], 0, 0, 0);\
-      } else {                                                                                   \
-        const int g_ = q_ >= NPV ? q_ - NPV : 0;                                                 \
-        S[n][g_ % 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr_[q_], qf[g_ / 2],              \
-                                                               g_ < 2 ? mi : S[n][g_ % 2], 0, 0, 0);\
+      /* hd 128: MFMA, exponential, MFMA, read, every second time the pair; hd 64: MFMAs, */      \
+      /* read, both exponentials and the pair */                                                 \
+      WDC_PPR3_MFMA(0)                                                                           \
+      if constexpr (EPM == 1) {                                                                  \
+        const int kt_ = q_ / 8, t_ = (q_ / 4) % 2, e_ = q_ % 4;                                  \
+        ex_[q_ & 1] = __builtin_amdgcn_exp2f(S[c][kt_][t_][e_]);                                 \
+        asm volatile("" : "+v"(ex_[q_ & 1]));                                                    \
+        __builtin_amdgcn_sched_barrier(0);                                                       \
       }                                                                                          \
-      __builtin_amdgcn_sched_barrier(0);                                                         \
+      WDC_PPR3_MFMA(1)                                                                           \
       if (q_ + 4 < NMF)                                                                          \
         WDC_PPR3_READ(q_ + 4, vb_, kb_)                                                          \
       else  /* the next step's first reads: V^T of tile t + 1, published by the last barrier */  \
         WDC_PPR3_READ(q_ + 4 - NMF, vn_, kb_)                                                    \
-      /* hd 64: the read goes out before the pair (0.8% faster than after it) */                 \
-      if constexpr (EPM == 2) __builtin_amdgcn_sched_barrier(0);                                  \
-      if constexpr (EPM == 2) {                                                                  \
-        /* both exponentials of a pair, converted together; the empty asm pins */                \
-        /* the pair under this MFMA (left free, the compiler sinks all of them */                \
-        /* past the stream, where they no longer overlap the matrix cores) */                    \
-        const int ei_ = 2 * q_, kt_ = ei_ / 16, e_ = ei_ % 16;                                   \
-        const bf16x2_t pr_ = {(__bf16)__builtin_amdgcn_exp2f(S[c][kt_][e_]),                     \
-                              (__bf16)__builtin_amdgcn_exp2f(S[c][kt_][e_ + 1])};                \
+      __builtin_amdgcn_sched_barrier(0);                                                         \
+      if (EPM == 2 || (q_ & 1)) {                                                                \
+        const int ei_ = EPM == 2 ? 2 * q_ : q_ - 1, kt_ = ei_ / 8, t_ = (ei_ / 4) % 2, e_ = ei_ % 4;\
+        if constexpr (EPM == 2) {                                                                \
+          ex_[0] = __builtin_amdgcn_exp2f(S[c][kt_][t_][e_]);                                    \
+          ex_[1] = __builtin_amdgcn_exp2f(S[c][kt_][t_][e_ + 1]);                                \
+        }                                                                                        \
+        const bf16x2_t pr_ = {(__bf16)ex_[0], (__bf16)ex_[1]};                                   \
         uint32_t u_ = __builtin_bit_cast(uint32_t, pr_);                                         \
         asm volatile("" : "+v"(u_));                                                             \
-        u32x4_t w_ = __builtin_bit_cast(u32x4_t, pf[c][2 * kt_ + e_ / 8]);                        \
-        w_[(e_ % 8) / 2] = u_;                                                                   \
-        pf[c][2 * kt_ + e_ / 8] = __builtin_bit_cast(bf16x8, w_);                                \
-        ls = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, u_), one2_, ls, false); \
-      } else {                                                                                   \
-        _Pragma("unroll") for (int x_ = 0; x_ < EPM; ++x_) {                                     \
-          const int ei_ = q_ * EPM + x_, kt_ = ei_ / 16, e_ = ei_ % 16;                          \
-          pf[c][2 * kt_ + e_ / 8][e_ % 8] = (__bf16)__builtin_amdgcn_exp2f(S[c][kt_][e_]);       \
-          if (ei_ & 1)                                                                           \
-            ls = __builtin_amdgcn_fdot2_f32_bf16(                                                \
-                bf16x2_t{pf[c][2 * kt_ + e_ / 8][(e_ - 1) % 8], pf[c][2 * kt_ + e_ / 8][e_ % 8]}, one2_, ls, false);\
-        }                                                                                        \
+        u32x4_t w_ = __builtin_bit_cast(u32x4_t, pf[c][t_][kt_ / 2]);                             \
+        w_[2 * (kt_ & 1) + e_ / 2] = u_;                                                         \
+        pf[c][t_][kt_ / 2] = __builtin_bit_cast(bf16x8, w_);                                     \
+        ls[t_] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, u_), one2_, ls[t_], false); \
+        __builtin_amdgcn_sched_barrier(0);                                                       \
       }                                                                                          \
-      __builtin_amdgcn_sched_barrier(0);                                                         \
     }                                                                                            \
     __builtin_amdgcn_sched_barrier(0);                                                           \
     if (soft) {                                                                                  \
-      if (__any(ls > PPR_LIMIT)) {                                                               \
-        const float mx = ppr_rowmax(S[c]);                                                       \
-        const float mn = m + (mx > 8.f ? mx : 0.f);                                              \
-        mi = ppr_mtile(mn);                                                                      \
-        const float d = mn - m, alpha = __builtin_amdgcn_exp2f(-d);                              \
-        m = mn;                                                                                  \
-        l *= alpha;                                                                              \
-        _Pragma("unroll") for (int i = 0; i < HD / 32; ++i)                                      \
-        _Pragma("unroll") for (int e = 0; e < 16; ++e) o[i][e] *= alpha;                         \
-        _Pragma("unroll") for (int kt = 0; kt < 2; ++kt)                                         \
-        _Pragma("unroll") for (int e = 0; e < 16; ++e) {                                         \
-          S[c][kt][e] -= d;                                                                      \
-          S[n][kt][e] -= d;                                                                      \
+      if (__any(fmaxf(ls[0], ls[1]) > PPR_LIMIT)) {                                              \
+        _Pragma("unroll") for (int t_ = 0; t_ < 2; ++t_) {                                       \
+          const float mx = ppr_rowmax(S[c], t_);                                                 \
+          const float mn = m[t_] + (mx > 8.f ? mx : 0.f);                                        \
+          mi[t_] = ppr_mtile(mn);                                                                \
+          const float d = mn - m[t_], alpha = __builtin_amdgcn_exp2f(-d);                        \
+          m[t_] = mn;                                                                            \
+          l[t_] *= alpha;                                                                        \
+          _Pragma("unroll") for (int i = 0; i < HD / 16; ++i)                                    \
+          _Pragma("unroll") for (int e = 0; e < 4; ++e) o[i][t_][e] *= alpha;                    \
+          _Pragma("unroll") for (int kt = 0; kt < 4; ++kt)                                       \
+          _Pragma("unroll") for (int e = 0; e < 4; ++e) {                                        \
+            S[c][kt][t_][e] -= d;                                                                \
+            S[n][kt][t_][e] -= d;                                                                \
+          }                                                                                      \
+          ls[t_] = ppr_exp(S[c], pf[c][t_], t_);                                                 \
         }                                                                                        \
-        ls = ppr_exp(S[c], pf[c]);                                                               \
       }                                                                                          \
-      l += ls;                                                                                   \
+      l[0] += ls[0];                                                                             \
+      l[1] += ls[1];                                                                             \
     }                                                                                            \
     if (grp_a) pp_wait4<HD>(issued);                                                             \
     /* every older read is done; the four just issued read a slot no load of */                  \
@@ -638,26 +688,30 @@ __global__ __launch_bounds__(512, 1) void k_attn_bf16_ppr3(AttnArgs a) {
     WDC_PPR3_STEP(3)
   }
 #undef WDC_PPR3_STEP
+#undef WDC_PPR3_MFMA
 #undef WDC_PPR3_READ
 
-  const float lt = l + __shfl_xor(l, 32, 64);
+  float lt[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    lt[t] = l[t] + __shfl_xor(l[t], 16, 64);
+    lt[t] += __shfl_xor(lt[t], 32, 64);
+  }
   if (bid >= main_blocks && ns > 1) {
     attn_split_store<HD>(a, o, m, lt, bid - main_blocks);
     return;
   }
-  const float inv = 1.f / lt;
-  const int64_t q = qbase + lr;
-  if (q < a.n) {
-    bf16_t *O = (bf16_t *)a.o + out_off(a, h, q, HD);
 #pragma unroll
-    for (int i = 0; i < HD / 32; ++i)
+  for (int t = 0; t < 2; ++t) {
+    const float inv = 1.f / lt[t];
+    const int64_t q = qbase + 16 * t + lr;
+    if (q >= a.n) continue;
+    bf16_t *O = (bf16_t *)a.o + out_off(a, h, q, HD) + 4 * lg;
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int d0 = 32 * i + 8 * g4 + 4 * lg;
-        uint32_t w0 = (uint32_t)f2bf(o[i][4 * g4 + 0] * inv) | ((uint32_t)f2bf(o[i][4 * g4 + 1] * inv) << 16);
-        uint32_t w1 = (uint32_t)f2bf(o[i][4 * g4 + 2] * inv) | ((uint32_t)f2bf(o[i][4 * g4 + 3] * inv) << 16);
-        *(uint2 *)(O + d0) = make_uint2(w0, w1);
-      }
+    for (int i = 0; i < HD / 16; ++i)
+      *(uint2 *)(O + 16 * i) = make_uint2(
+          (uint32_t)f2bf(o[i][t][0] * inv) | ((uint32_t)f2bf(o[i][t][1] * inv) << 16),
+          (uint32_t)f2bf(o[i][t][2] * inv) | ((uint32_t)f2bf(o[i][t][3] * inv) << 16));
   }
 }
 
