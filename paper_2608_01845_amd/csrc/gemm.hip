@@ -220,20 +220,20 @@ __device__ __forceinline__ void qk_scatter(const GemmArgs &g, const char *smem, 
   // of the row (threadIdx.x % CPR: head hh, eight columns from 8 c) is the same
   // in every iteration. The sample and token advance incrementally (no
   // division per row). With a rotation table (ROPE: a table and video rows)
-  // its entries go out four rows at a time, one group of four ahead, and
+  // its entries go out GS rows at a time, one group ahead, and
   // unconditionally (rows that take no rotation read table row 0), so the
   // stores of a group never stand between a table read and its use.
-  constexpr int CPR = QT::BN / 8, RPI = QT::NT / CPR, NG = QT::BM / RPI / 4;
-  static_assert(NG * RPI * 4 == QT::BM, "whole groups of four rows");
+  constexpr int CPR = QT::BN / 8, RPI = QT::NT / CPR, GS = QT::BM / RPI % 4 == 0 ? 4 : 2, NG = QT::BM / RPI / GS;
+  static_assert(NG * RPI * GS == QT::BM, "whole groups of rows");
   const int cc = threadIdx.x % CPR, hh = cc / TPH, c = cc % TPH, rt = threadIdx.x / CPR;
   const int64_t r_first = o.rbase + m0 + rt;
   int64_t b = (int64_t)blockIdx.z + r_first / o.rps, jr = r_first % o.rps;
-  int64_t bsv[2][4], jv[2][4];   // group g4 in slot g4 & 1
-  float4 cs4v[2][4][2];
+  int64_t bsv[2][GS], jv[2][GS];   // group g4 in slot g4 & 1
+  float4 cs4v[2][GS][2];
   auto rotates = [&](int it, int64_t jt) { return ROPE && jt < o.n_video && m0 + RPI * it + rt < g.m; };
-  auto coords = [&](int64_t (&bs4)[4], int64_t (&j4)[4]) {
+  auto coords = [&](int64_t (&bs4)[GS], int64_t (&j4)[GS]) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < GS; ++u) {
       bs4[u] = b;
       j4[u] = o.row0 + jr;
       jr += RPI;
@@ -243,11 +243,11 @@ __device__ __forceinline__ void qk_scatter(const GemmArgs &g, const char *smem, 
       }
     }
   };
-  auto fetch = [&](int g4, const int64_t (&js)[4], float4 (&dst4)[4][2]) {
+  auto fetch = [&](int g4, const int64_t (&js)[GS], float4 (&dst4)[GS][2]) {
     if (!ROPE) return;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t jt = rotates(4 * g4 + u, js[u]) ? js[u] : 0;
+    for (int u = 0; u < GS; ++u) {
+      const int64_t jt = rotates(GS * g4 + u, js[u]) ? js[u] : 0;
       const float4 *cs4 = (const float4 *)(o.rope + jt * (HD / 2) + 4 * c);
       dst4[u][0] = cs4[0];
       dst4[u][1] = cs4[1];
@@ -263,8 +263,8 @@ __device__ __forceinline__ void qk_scatter(const GemmArgs &g, const char *smem, 
       fetch(g4 + 1, jv[sl ^ 1], cs4v[sl ^ 1]);
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int it = 4 * g4 + u, row = RPI * it + rt;
+    for (int u = 0; u < GS; ++u) {
+      const int it = GS * g4 + u, row = RPI * it + rt;
       float x[8];
       unpack8(*(const uint4 *)QT::chunk(smem, row, cc), x);
       if (o.qk_norm) {
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
   constexpr bool OUT16 = EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_QKV;
   constexpr bool RES = EPI == EPI_GATE_RES || EPI == EPI_GATE_RES_NT;   // gated residual into the float32 stream
   // bf16 output through LDS: whole-line non-temporal stores, or the q/k/v layouts
-  constexpr bool STAGE_OUT = BM == 256 || EPI == EPI_QKV;
+  constexpr bool STAGE_OUT = BM >= 192 || EPI == EPI_QKV;
   const GemmArgs g = batch_entry<bf16_t>(g0);
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char *sA = smem;                      // [NB][BM][128 B]
@@ -504,13 +504,13 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
   // the buffer just consumed and the next stage's first fragments are read. A
   // scheduling barrier after each MFMA, read and load keeps that order.
   constexpr int D = 1;   // 2, 3 and 4 were 0.5 to 2% slower on the large products
-  static_assert(BK == 64 && D < TM && TN <= TM, "two k-steps per stage");
+  static_assert(BK == 64 && D < TM, "two k-steps per stage");
   // Loads of a stage go one by one between MFMAs: within the rest of the second
   // k-step with two buffers (they have the next stage to arrive in), spread on
   // to the next barrier with more buffers and 64 x 64 wave tiles (a burst stalls
   // the wave that issues it).
   constexpr int LQ0 = (TM - D) * TN;                      // MFMAs from the barrier to the end of the stage
-  constexpr int LQ = NB > 2 && TM == 4 && TN == 4 ? LQ0 + TM * TN : LQ0;
+  constexpr int LQ = NB > 2 && TM >= 3 && TN == 4 ? LQ0 + TM * TN : LQ0;
   bf16x8 fa[TM], fb[2][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i) WDC_GEMM_READA(0, 0, i);
@@ -539,6 +539,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
   int buf = 0, prv = NB - 1;
   for (int kt = 0; kt < nk; ++kt) {
     const int nxt = NB == 2 ? buf ^ 1 : buf + 1 == NB ? 0 : buf + 1;
+    constexpr int BPR0 = (TN + TM - 1) / TM;              // B fragments read per row of MFMAs
     const bool ld0 = LQ > LQ0 && kt > 0 && kt + NB - 1 < nk && wu < NW;   // rest of the previous barrier's loads
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -546,7 +547,9 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
       for (int j = 0; j < TN; ++j) {
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[0][j], fa[i], acc[i][j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        if (j == 0 && i < TN) WDC_GEMM_READB(buf, 1, i);
+#pragma unroll
+        for (int b = 0; b < BPR0; ++b)
+          if (j == b * TN / BPR0 && i * BPR0 + b < TN) WDC_GEMM_READB(buf, 1, i * BPR0 + b);
         if (j == TN - 1) WDC_GEMM_READA(buf, 1, i);
         __builtin_amdgcn_sched_barrier(0);
         WDC_GEMM_LOADS(ld0, prv, kt + NB - 1, LQ0 + i * TN + j)
@@ -797,19 +800,22 @@ int64_t tile_count(const GemmArgs &g, int bm, int bn) {
 
 // Tile shape of a product too small for the 256 x 256 tiles (n % 64 == 0).
 // Measured per 64-deep K stage (microseconds a compute unit takes for the
-// blocks it holds) and per round, the products alone on the device:
-//   64 x 64, 3 buffers: 0.30 for one block, 0.45 for two, 0.64 for three
-//   128 x 128, 4 buffers, one block: 0.43 on 48 CUs, 0.53 on 168
+// blocks it holds), the products alone on the device:
+//   64 x 64, 3 buffers: 0.30 for one block, 0.64 for three
+//   96 x 128, 4 buffers, one block: 0.43; 128 x 128, one block: 0.53
 //   128 x 128, 2 buffers, two blocks: 0.95
-//   256 x 128, 3 buffers, 8 waves of 64 x 64, one block: 0.78
-// so: 64 x 64 while they do not fill the device (226 x 3,072, K = 4,096: 19.4 us
-// against 36.7 on 128 x 64; 256 x 3,072, K = 12,288: 55 against 104), then 128 x
-// 128 one per CU (256 x 9,216, K = 3,072: 26.3 against 34.6 with two buffers;
-// 2,688 x 1,024, K = 4,096: 37.7 against 41.3 on 128 x 64), then the cheaper of
-// two 128 x 128 blocks per CU (2,688 x 3,072, K = 1,024: 24.6 us) and 256 x 128
-// (2,688 x 4,096, K = 1,024: 30.8 against 34.9; 5,000 x 1,536, K = 1,536: 24.4
-// against 29.7). 256 x 128 needs 16-byte output rows.
-enum SmallTile { T64, T128_64, T128_ONE, T128_TWO, T256_128 };
+//   192 x 128 and 256 x 128, 3 buffers, 8 waves, one block: 0.60 and 0.78
+// and a few microseconds of prologue and epilogue per round, which nothing
+// overlaps. So: 64 x 64 while they do not fill the device (226 x 3,072, K = 4,096:
+// 19.5 us against 36.7 on 128 x 64; 256 x 3,072, K = 12,288: 53 against 104), then
+// the smallest of 96 and 128 x 128 that fits it once (2,688 x 1,024, K = 4,096: 37.5
+// us against 41.6 on 128 x 128 and 45.1 on 128 x 64 with two buffers; 3,000 x
+// 1,536, K = 1,536: 18.8, 21.6 and 24.9), then the cheapest of two 128 x 128 blocks
+// per CU (2,688 x 3,072, K = 1,024: 24.2 us against 27.4 on 192 x 128) and rounds of
+// 192 x 128 (2,688 x 4,096, K = 1,024: 30.4 us against 33.9 on 256 x 128) or 256 x
+// 128 (5,000 x 1,536, K = 1,536: 24.3 against 29.8 on 128 x 128), which need
+// 16-byte output rows.
+enum SmallTile { T64, T128_64, T96_128, T128_ONE, T128_TWO, T192_128, T256_128 };
 SmallTile pick_small(const GemmArgs &g, bool out16, double *us) {
   const int64_t cus = device_cus() > 0 ? device_cus() : 256;
   const double st = (double)(g.k / BK);
@@ -826,13 +832,16 @@ SmallTile pick_small(const GemmArgs &g, bool out16, double *us) {
   // against rounds of 256 x 128 blocks: stage time x stages + the prologue and
   // epilogue of a round, which nothing overlaps
   const double pair = 0.95 * st + 9.4, single = 0.53 * st + 4.0;
+  *us = 0.43 * st + 4.0;
+  if (tile_count(g, 96, 128) <= cus) return T96_128;
   *us = single;
   if (t128 <= cus) return T128_ONE;
   const int64_t rest = t128 % (2 * cus);
   const double c128 = pair * (double)(t128 / (2 * cus)) + (rest == 0 ? 0.0 : rest <= cus ? single : pair);
-  const double c256 = (0.78 * st + 3.0) * rounds(t256);
-  *us = out16 && c256 <= c128 ? c256 : c128;
-  return out16 && c256 <= c128 ? T256_128 : T128_TWO;
+  const double c256 = (0.78 * st + 4.0) * rounds(t256);
+  const double c192 = (0.60 * st + 4.5) * rounds(tile_count(g, 192, 128));
+  *us = out16 ? std::min({c128, c192, c256}) : c128;
+  return *us == c128 ? T128_TWO : *us == c256 ? T256_128 : T192_128;
 }
 
 hipError_t launch_small(const GemmArgs &g, bool out16, hipStream_t s) {
@@ -840,7 +849,9 @@ hipError_t launch_small(const GemmArgs &g, bool out16, hipStream_t s) {
   switch (pick_small(g, out16, &us)) {
     case T64: return launch_mfma<64, 64, 2, 2, 3>(g, s);
     case T128_64: return launch_mfma<128, 64, 2, 2>(g, s);
+    case T96_128: return launch_mfma<96, 128, 2, 2, 4>(g, s);
     case T128_ONE: return launch_mfma<128, 128, 2, 2, 4>(g, s);
+    case T192_128: return launch_mfma<192, 128, 4, 2, 3>(g, s);
     case T128_TWO: return launch_mfma<128, 128, 2, 2>(g, s);
     default: return launch_mfma<256, 128, 4, 2, 3>(g, s);
   }
@@ -940,7 +951,9 @@ hipError_t launch_gemm(int dtype, const GemmArgs &g_in, hipStream_t s) {
     if (first_on_device(seen)) {
       hipError_t e = set_lds_limit<256, 256, 2, 4>();
       if (e == hipSuccess) e = set_lds_limit<256, 128, 4, 2, 3>();
+      if (e == hipSuccess) e = set_lds_limit<192, 128, 4, 2, 3>();
       if (e == hipSuccess) e = set_lds_limit<128, 128, 2, 2>();
+      if (e == hipSuccess) e = set_lds_limit<96, 128, 2, 2, 4>();
       if (e == hipSuccess) e = set_lds_limit<128, 128, 2, 2, 4>();
       if (e == hipSuccess) e = set_lds_limit<128, 64, 2, 2>();
       if (e == hipSuccess) e = set_lds_limit<64, 64, 2, 2, 3>();

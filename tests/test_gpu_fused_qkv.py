@@ -109,10 +109,12 @@ def test_fill_tiles_mid_forward_bitwise_equal():
 
 
 @pytest.mark.parametrize("hidden,head_dim,latent,batch", [
-    (256, 64, (16, 7, 28, 30), 1),      # 1,470 + 21 tokens: 128 x 128 tiles, one per compute unit
+    (256, 64, (16, 7, 28, 30), 1),      # 1,470 + 21 tokens: 96 x 128 tiles
     (256, 128, (16, 7, 28, 30), 1),
+    (256, 128, (16, 12, 38, 40), 1),    # 4,560 + 21 tokens: 128 x 128 tiles, one per compute unit
+    (768, 64, (16, 7, 38, 42), 1),      # 2,793 + 21 tokens: 256 x 128 tiles
     (256, 64, (16, 4, 20, 38), 2),      # two samples of 781 tokens share tiles: element-wise V^T
-    (512, 128, (16, 7, 38, 42), 1),     # 2,793 + 21 tokens: 256 x 128 tiles
+    (512, 128, (16, 7, 38, 42), 1),     # 192 x 128 tiles
     (512, 64, (16, 4, 38, 38), 2)])
 def test_fused_qkv_on_small_tiles_equals_separate_preparation(hidden, head_dim, latent, batch):
     """Projections that do not fill a dispatch round of 256 x 256 tiles, fused on
