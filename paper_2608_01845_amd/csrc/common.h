@@ -134,9 +134,13 @@ struct GemmArgs {
   int order;
   int rect_n;        // order 1: N tiles of the rectangle (32 / rect_n M tiles)
   // 1: a product whose 256 x 256 tiles would fill less than one dispatch round
-  // (fewer tiles than compute units) runs on 128 x 128 tiles, four times the
-  // blocks; 0: the tile size follows the shape alone
+  // (fewer tiles than compute units) runs on smaller tiles; 0: the tile size
+  // follows the shape alone
   int fill_tiles;
+  // 1: K may be summed in two interleaved groups where that is faster. Not for
+  // products whose rows are one sample's in some calls and several samples' in
+  // others: the sample's result would depend on its company.
+  int k_groups;
   QkvOut qkv;        // EPI_QKV only
 };
 

@@ -3,7 +3,7 @@
 // float32 store). Both operands are K-contiguous ("NT"), which is the layout
 // the MFMA operand registers want: every lane loads 8 consecutive bf16.
 //
-// bf16 path: v_mfma_f32_32x32x16_bf16 tiles, BMxBN block tile (256 x 256 in 8
+// bf16 path: v_mfma_f32_16x16x32_bf16 tiles, BMxBN block tile (256 x 256 in 8
 // waves of 128 x 64 for the large products), BK = 64, double-buffered LDS with
 // an XOR swizzle of the 16-byte chunks of each 128-byte row (conflict-free
 // fragment reads). K stages go straight from HBM into LDS (buffer loads with the
@@ -124,9 +124,9 @@ __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, char *lds, 
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)lds, 16, voff, soff, 0, 0);
 }
 
-template <int BM, int BN, int WM, int WN, int NB = 2>
+template <int BM, int BN, int WM, int WN, int NB = 2, int KG = 1>
 struct Cfg {
-  static constexpr int NT = 64 * WM * WN;       // threads
+  static constexpr int NT = 64 * WM * WN;       // threads of one K group
   static constexpr int TM = BM / WM / 16;       // 16x16 tiles per wave along M
   static constexpr int TN = BN / WN / 16;       // along N
   // the first LW waves (one per SIMD) issue the tile loads: with all 16 waves
@@ -134,7 +134,7 @@ struct Cfg {
   static constexpr int LW = NT / 64 >= 4 ? 4 : NT / 64;
   static constexpr int A_CHUNKS = BM * 8 / (64 * LW);  // 1 KB stripes per loading wave per stage
   static constexpr int B_CHUNKS = BN * 8 / (64 * LW);
-  static constexpr int LDS_BYTES = NB * (BM + BN) * BK * 2;
+  static constexpr int LDS_BYTES = KG * NB * (BM + BN) * BK * 2;
   static constexpr bool QKV = BN % 128 == 0 && BN / WN == 64;   // tiles that take EPI_QKV
 };
 
@@ -355,9 +355,12 @@ __device__ __forceinline__ void v_scatter(const GemmArgs &g, const char *smem, i
   }
 }
 
-template <int BM, int BN, int WM, int WN, int EPI, int NB = 2>
-__global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
-  using C = Cfg<BM, BN, WM, WN, NB>;
+// KG > 1: the block holds KG groups of WM x WN waves, group kg taking the K
+// stages kg, kg + KG, ... in LDS buffers of its own; the groups' sums are added
+// in group order before the epilogue.
+template <int BM, int BN, int WM, int WN, int EPI, int NB = 2, int KG = 1>
+__global__ __launch_bounds__(64 * WM * WN * KG) void k_gemm_mfma(GemmArgs g0) {
+  using C = Cfg<BM, BN, WM, WN, NB, KG>;
   // C^T tiles (weight fragment as the MFMA A operand): a lane holds 4 consecutive
   // columns of one row, 8 bytes of a bf16 output, 16 of a float32 one
   constexpr bool OUT16 = EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_QKV;
@@ -366,8 +369,9 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
   constexpr bool STAGE_OUT = BM >= 192 || EPI == EPI_QKV;
   const GemmArgs g = batch_entry<bf16_t>(g0);
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  char *sA = smem;                      // [NB][BM][128 B]
-  char *sB = smem + NB * BM * BK * 2;   // [NB][BN][128 B]
+  const int kg = KG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / C::NT) : 0;
+  char *sA = smem + kg * (C::LDS_BYTES / KG);   // [NB][BM][128 B]
+  char *sB = sA + NB * BM * BK * 2;             // [NB][BN][128 B]
 
   // Tile order: a group of 8 consecutive M tiles walks all N tiles, so blocks
   // running at once share A rows and the weight panel in L2.
@@ -409,7 +413,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
   }
   const int64_t m0 = (int64_t)mt * BM, n0 = (int64_t)nt * BN;
 
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int tid = threadIdx.x - kg * C::NT, lane = tid & 63, wid = tid >> 6;
   const int wm = wid / WN, wn = wid % WN;
   const int lr = lane & 15, lg = lane >> 4;
 
@@ -445,7 +449,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
 
 #define WDC_GEMM_LOAD(buf, kt)                                                                     \
   {                                                                                                \
-    const int kb_ = (kt) * BK * 2;                                                                 \
+    const int kb_ = ((kt) * KG + kg) * BK * 2;                                                     \
     if (wu < NW) {                                                                                 \
       int v_ = va0;                                                                                \
       _Pragma("unroll") for (int i = 0; i < C::A_CHUNKS; ++i) {                                     \
@@ -471,7 +475,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
   }
 
   constexpr int SL = C::A_CHUNKS + C::B_CHUNKS;           // load instructions per loading wave per stage
-  const int nk = (int)(g.k / BK);
+  const int nk = (int)(g.k / (BK * KG));                  // stages of a K group
   // Stages 0 and 1 fill both buffers; stage 0 is complete once no more than
   // stage 1's loads are pending (a wave's memory operations complete in issue
   // order).
@@ -521,12 +525,12 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
 #define WDC_GEMM_LOAD1(lbuf, lkt, l)                                                               \
   {                                                                                                \
     if ((l) < C::A_CHUNKS) {                                                                       \
-      lds_load16(a_desc, sA + (lbuf) * BM * 128 + ((l) * NW + wu) * 1024, va, (lkt) * BK * 2);     \
+      lds_load16(a_desc, sA + (lbuf) * BM * 128 + ((l) * NW + wu) * 1024, va, ((lkt) * KG + kg) * BK * 2);\
       if ((l) + 1 < C::A_CHUNKS) asm volatile("v_add_u32 %0, %0, %1" : "+v"(va) : "s"(a_step));     \
     } else {                                                                                       \
       const int lb_ = (l) - C::A_CHUNKS;                                                           \
       lds_load16(b_desc, sB + (lbuf) * BN * 128 + (lb_ * NW + wu) * 1024, vb,                      \
-                 lb_ * 8 * NW * (int)g.k * 2 + (lkt) * BK * 2);                                    \
+                 lb_ * 8 * NW * (int)g.k * 2 + ((lkt) * KG + kg) * BK * 2);                        \
     }                                                                                              \
   }
   // the loads that belong after MFMA q of LQ since the barrier (the branch holds
@@ -598,6 +602,25 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(GemmArgs g0) {
 #undef WDC_GEMM_READA
 #undef WDC_GEMM_READB
 
+  if constexpr (KG > 1) {
+    static_assert(!STAGE_OUT && (KG - 1) * BM * BN * 4 <= C::LDS_BYTES, "partial sums in LDS");
+    f32x4 *part = (f32x4 *)smem + tid;                    // [group - 1][TM][TN][threads of a group]
+    __syncthreads();                                      // every group is done with its buffers
+    if (kg > 0) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) part[(((kg - 1) * TM + i) * TN + j) * C::NT] = acc[i][j];
+    }
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll
+    for (int u = 0; u + 1 < KG; ++u)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] += part[((u * TM + i) * TN + j) * C::NT];
+  }
   const bf16_t *bias = (const bf16_t *)g.bias;
   const int cb = wn * (BN / WN) + 4 * lg;                 // the lane's columns in the block: cb + 16 j + 0..3
   if constexpr (OUT16 && STAGE_OUT) {
@@ -742,9 +765,9 @@ int rect_chunks(const GemmArgs &g) {
   return chunks >= 64 ? chunks : 0;
 }
 
-template <int BM, int BN, int WM, int WN, int NB = 2>
+template <int BM, int BN, int WM, int WN, int NB = 2, int KG = 1>
 hipError_t launch_mfma(const GemmArgs &g0, hipStream_t s, int max_chunks = 0) {
-  using C = Cfg<BM, BN, WM, WN, NB>;
+  using C = Cfg<BM, BN, WM, WN, NB, KG>;
   GemmArgs g = g0;
   const int m_tiles = (int)((g.m + BM - 1) / BM), n_tiles = (int)(g.n / BN);
   g.rect_n = RECT_N;
@@ -752,38 +775,38 @@ hipError_t launch_mfma(const GemmArgs &g0, hipStream_t s, int max_chunks = 0) {
   g.order = chunks > 0;
   int blocks = m_tiles * n_tiles;
   if (g.order == 1) blocks = ((max_chunks > 0 ? max_chunks : chunks) + 7) / 8 * 256;
-  dim3 grid(blocks, 1, g.batch > 1 ? g.batch : 1), block(C::NT);
+  dim3 grid(blocks, 1, g.batch > 1 ? g.batch : 1), block(C::NT * KG);
   switch (g.epi) {
-    case EPI_STORE: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_STORE, NB>), grid, block, C::LDS_BYTES, s, g); break;
-    case EPI_GELU: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GELU, NB>), grid, block, C::LDS_BYTES, s, g); break;
-    case EPI_GATE_RES: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES, NB>), grid, block, C::LDS_BYTES, s, g); break;
-    case EPI_GATE_RES_NT: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES_NT, NB>), grid, block, C::LDS_BYTES, s, g); break;
+    case EPI_STORE: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_STORE, NB, KG>), grid, block, C::LDS_BYTES, s, g); break;
+    case EPI_GELU: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GELU, NB, KG>), grid, block, C::LDS_BYTES, s, g); break;
+    case EPI_GATE_RES: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES, NB, KG>), grid, block, C::LDS_BYTES, s, g); break;
+    case EPI_GATE_RES_NT: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES_NT, NB, KG>), grid, block, C::LDS_BYTES, s, g); break;
     case EPI_QKV:
       if constexpr (C::QKV) {
-        hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_QKV, NB>), grid, block, C::LDS_BYTES, s, g);
+        hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_QKV, NB, KG>), grid, block, C::LDS_BYTES, s, g);
         break;
       } else {
         return hipErrorInvalidValue;
       }
-    default: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_STORE_F32, NB>), grid, block, C::LDS_BYTES, s, g); break;
+    default: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_STORE_F32, NB, KG>), grid, block, C::LDS_BYTES, s, g); break;
   }
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN, int NB = 2>
+template <int BM, int BN, int WM, int WN, int NB = 2, int KG = 1>
 hipError_t set_lds_limit() {
-  using C = Cfg<BM, BN, WM, WN, NB>;
-  const void *k[5] = {(const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_STORE, NB>,
-                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GELU, NB>,
-                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES, NB>,
-                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES_NT, NB>,
-                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_STORE_F32, NB>};
+  using C = Cfg<BM, BN, WM, WN, NB, KG>;
+  const void *k[5] = {(const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_STORE, NB, KG>,
+                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GELU, NB, KG>,
+                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES, NB, KG>,
+                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES_NT, NB, KG>,
+                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_STORE_F32, NB, KG>};
   for (const void *f : k) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
     if (e != hipSuccess) return e;
   }
   if constexpr (C::QKV)
-    return hipFuncSetAttribute((const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_QKV, NB>,
+    return hipFuncSetAttribute((const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_QKV, NB, KG>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
   return hipSuccess;
 }
@@ -847,7 +870,14 @@ SmallTile pick_small(const GemmArgs &g, bool out16, double *us) {
 hipError_t launch_small(const GemmArgs &g, bool out16, hipStream_t s) {
   double us;
   switch (pick_small(g, out16, &us)) {
-    case T64: return launch_mfma<64, 64, 2, 2, 3>(g, s);
+    case T64:
+      // a lone 64 x 64 block per CU is bound by the latency of its stages: two
+      // groups of waves halve the chain (226 x 3,072, K = 4,096: 20.1 us with one
+      // group, 17.9 with two, 22.2 with four of two buffers each; 256 x 3,072, K =
+      // 12,288: 53.8, 47.5, 61.7; 77 x 1,024, K = 1,024: 6.4 and 5.8)
+      if (g.k_groups && g.k % (2 * BK) == 0 && g.k >= 512 && tile_count(g, 64, 64) <= device_cus())
+        return launch_mfma<64, 64, 2, 2, 3, 2>(g, s);
+      return launch_mfma<64, 64, 2, 2, 3>(g, s);
     case T128_64: return launch_mfma<128, 64, 2, 2>(g, s);
     case T96_128: return launch_mfma<96, 128, 2, 2, 4>(g, s);
     case T128_ONE: return launch_mfma<128, 128, 2, 2, 4>(g, s);
@@ -957,6 +987,7 @@ hipError_t launch_gemm(int dtype, const GemmArgs &g_in, hipStream_t s) {
       if (e == hipSuccess) e = set_lds_limit<128, 128, 2, 2, 4>();
       if (e == hipSuccess) e = set_lds_limit<128, 64, 2, 2>();
       if (e == hipSuccess) e = set_lds_limit<64, 64, 2, 2, 3>();
+      if (e == hipSuccess) e = set_lds_limit<64, 64, 2, 2, 3, 2>();
       if (e != hipSuccess) return e;
     }
     // 256 x 256 block tiles: 8 waves of 128 x 64 (two per SIMD). With the reads

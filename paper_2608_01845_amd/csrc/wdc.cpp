@@ -61,7 +61,7 @@ struct wdc_ctx {
   // (WDC_FUSE_QKV=0: always the separate kernels, for comparison)
   bool fuse_qkv = true;
   // products that would not fill one dispatch round of 256 x 256 tiles run on
-  // 128 x 128 tiles (WDC_FILL_TILES=0: tile size by shape alone, so tests can
+  // smaller ones (WDC_FILL_TILES=0: tile size by shape alone, so tests can
   // reach the 256 x 256 kernels and the fused q/k/v epilogue at small sizes)
   bool fill_tiles = true;
   // key-range split of the attention's last partial dispatch round
@@ -319,7 +319,8 @@ struct Batch {
 };
 
 wdc_status gemm(wdc_ctx *c, const void *a, int64_t lda, const void *w, const void *b, void *out, int64_t ldc,
-                int64_t m, int64_t n, int64_t k, int epi, const float *gate = nullptr, Batch bt = Batch()) {
+                int64_t m, int64_t n, int64_t k, int epi, const float *gate = nullptr, Batch bt = Batch(),
+                bool k_groups = false) {
   if (m <= 0 || bt.n <= 0) return WDC_OK;
   if (!w) {
     set_err(c, "weights not bound");
@@ -342,6 +343,7 @@ wdc_status gemm(wdc_ctx *c, const void *a, int64_t lda, const void *w, const voi
   g.c_bs = bt.c_bs;
   g.gate_bs = bt.gate_bs;
   g.fill_tiles = c->fill_tiles;
+  g.k_groups = k_groups;
   HIPCHK(c, timed(c, WDC_T_GEMM, 2.0 * m * n * k * bt.n, [&] { return launch_gemm(c->d.dtype, g, c->stream); }));
   return WDC_OK;
 }
@@ -662,7 +664,7 @@ wdc_status dit_forward_batch(wdc_ctx *c, int nb, const float *const *z, double t
         return WDC_E_ARG;
       }
       CHK(gemm(c, text[b], d.text_dim, W(c, "text_proj.w"), W(c, "text_proj.b"), c->x + (b * N + NV) * D, D, c->nt,
-               D, d.text_dim, EPI_STORE_F32));
+               D, d.text_dim, EPI_STORE_F32, nullptr, Batch(), true));
     }
   }
   for (int b = 0; b < d.n_seq + d.n_dual + d.n_single; ++b) CHK(block_forward(c, b));
@@ -1653,7 +1655,7 @@ wdc_status wdc_attention_plan(const wdc_ctx *ctx, int64_t n, int32_t *qb_main, i
 wdc_status wdc_linear(wdc_ctx *ctx, const void *d_a, int64_t lda, const void *d_w, const void *d_bias, void *d_c,
                       int64_t ldc, int64_t m, int64_t n, int64_t k) {
   if (!ctx || !d_a || !d_w || !d_c || m < 0 || n <= 0 || k <= 0 || lda < k || ldc < n) return WDC_E_ARG;
-  return gemm(ctx, d_a, lda, d_w, d_bias, d_c, ldc, m, n, k, EPI_STORE);
+  return gemm(ctx, d_a, lda, d_w, d_bias, d_c, ldc, m, n, k, EPI_STORE, nullptr, Batch(), true);
 }
 
 wdc_status wdc_set_timing(wdc_ctx *ctx, int32_t on) {
