@@ -130,7 +130,8 @@ struct GemmArgs {
   int batch;
   int64_t a_bs, c_bs, gate_bs;
   // block-to-tile order of the MFMA kernels, chosen by launch_gemm: 0 groups
-  // of 8 M tiles, 1 one 8 x 4 tile rectangle per XCD per dispatch round
+  // of 8 M tiles, 1 one 8 x 4 tile rectangle per XCD per dispatch round, 2 every
+  // M tile of a column tile on one XCD
   int order;
   int rect_n;        // order 1: N tiles of the rectangle (32 / rect_n M tiles)
   // 1: a product whose 256 x 256 tiles would fill less than one dispatch round

@@ -320,14 +320,15 @@ def test_forward_batch_several_blocks_of_each_kind_match_oracle():
 # 128 with partial last rows; two 128 x 128 blocks per compute unit; narrow outputs on 64 x 64 and 128 x 64;
 # 128 x 128 in place of 256 x 128 where output rows are not 16-byte aligned; 64 x 64
 # in two K groups from K = 512 on, where K has an even number of stages, and with
-# more blocks than compute units in one
+# more blocks than compute units in one; up to 8 M tiles of 64 rows
+# grouped by weight panel, a partial last one among them
 @pytest.mark.parametrize("m,n,k,pad", [
     (1, 64, 64, 0), (65, 192, 128, 0), (63, 128, 192, 8), (130, 320, 256, 0), (1500, 1024, 64, 0), (1409, 1152, 192, 0),
     (1500, 1024, 256, 8), (1300, 896, 320, 0), (3500, 1024, 64, 0), (3489, 1024, 320, 8), (2990, 2048, 256, 0),
     (3072, 2048, 192, 0), (4900, 1536, 64, 0), (4993, 1536, 256, 8), (4993, 1536, 192, 4),
     (2600, 3072, 448, 0), (5001, 64, 128, 0), (49500, 64, 64, 0),
     (1, 64, 512, 0), (65, 192, 640, 8), (77, 128, 576, 0), (256, 512, 1024, 0), (512, 2048, 512, 0),
-    (513, 2048, 512, 4)])
+    (513, 2048, 512, 4), (449, 512, 192, 0), (300, 1536, 128, 0)])
 def test_linear_bf16_small_tiles_match_oracle(m, n, k, pad):
     torch = torch_cuda()
     cfg = synth.get_config("mid")
