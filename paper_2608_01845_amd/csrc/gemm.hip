@@ -8,13 +8,13 @@
 // an XOR swizzle of the 16-byte chunks of each 128-byte row (conflict-free
 // fragment reads). K stages go straight from HBM into LDS (buffer loads with the
 // LDS flag) two stages ahead; each wave reads its fragments one k-step ahead,
-// one read at a time between its MFMAs, and the stage barrier sits before a
-// stage's last k-step so the matrix cores never drain at it. Large single
-// products take an XCD-aware block order, and long-K ones whose last dispatch
-// round would be thin run their last rows as a second launch of smaller tiles;
-// products too small to fill one dispatch round of 256 x 256 tiles run on
-// smaller ones throughout, with three or four LDS buffers where one block per
-// compute unit has to hide its own loads (launch_small).
+// one read at a time between its MFMAs, and the stage barrier sits one fragment
+// row into a stage's last k-step so the matrix cores never drain at it. Large
+// single products take an XCD-aware block order, and products whose last dispatch
+// round would be thin run their last rows as a second launch of smaller tiles
+// (launch_tail); products too small to fill one dispatch round of 256 x 256 tiles
+// run on smaller ones throughout, with three or four LDS buffers where one block
+// per compute unit has to hide its own loads (launch_small).
 // float32 products run on the matrix cores too (gemm_f32.hip). Shapes that
 // neither covers (K not a multiple of 32 or 64, unaligned operands): a plain
 // LDS-tiled FMA kernel.
