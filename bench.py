@@ -32,7 +32,7 @@ PEAK_HBM_GBS = 8000.0
 # 1 GiB device copy; profiles/attention_13b_hbm_traffic.md): the attention
 # kernel plus the combine launch of its split last round. Valid only for the
 # kernel version named here; set to None whenever that kernel changes.
-MEASURED_TRAFFIC = {"k_attn_bf16_ppr3<128>": None}
+MEASURED_TRAFFIC = {"k_attn_bf16_ppr3<128>": 9.378e9}
 ATTN_KERNEL = {128: "k_attn_bf16_ppr3<128>", 64: "k_attn_bf16_ppr3<64>"}   # default bf16 kernel by head size
 METRIC = "DiT fwd TFLOP/s (% bf16 MFMA peak) + denoising steps/s at 13B shape"
 # Risk thresholds (Eq. (10)) of the measured rollouts, one per workload, for the
