@@ -122,8 +122,11 @@ __global__ __launch_bounds__(256, 1) void k_attn_f32(AttnArgs a, int qblocks) {
 #pragma unroll
     for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[e]);
     const float mn = fmaxf(m, fmaxf(mx, __shfl_xor(mx, 32, 64)));
+    // a wave whose keys so far all score -inf has no maximum yet: its weights are
+    // taken against 0, so they and its sum are 0 and not NaN
+    const float ref = mn == -INFINITY ? 0.f : mn;
     if (__any(mn > m)) {
-      const float al = expf(m - mn);
+      const float al = expf(m - ref);
       m = mn;
       l *= al;
 #pragma unroll
@@ -133,7 +136,7 @@ __global__ __launch_bounds__(256, 1) void k_attn_f32(AttnArgs a, int qblocks) {
     }
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      s[e] = expf(s[e] - m);
+      s[e] = expf(s[e] - ref);
       l += s[e];
     }
 #pragma unroll

@@ -66,6 +66,55 @@ def test_attention_f32_matches_oracle(head_dim, heads, n, spread):
     assert (got[:, heads * head_dim:] == 7.0).all()
 
 
+@pytest.mark.parametrize("head_dim,heads,n", [(64, 4, 100), (64, 8, 449), (128, 2, 160)])
+def test_attention_f32_infinite_and_nan_scores(head_dim, heads, n):
+    """Keys 32..95, whole tiles of two waves, score -inf for every query: weight 0. A NaN
+    query row stays NaN by itself; a +inf score makes its row NaN."""
+    torch = torch_cuda()
+    ctx = context(small_cfg("f32", head_dim=head_dim, hidden=heads * head_dim, heads=heads), weights=False)
+    rng = np.random.default_rng(n)
+    q, k, v = (rng.standard_normal((heads, n, head_dim)).astype(np.float32) for _ in range(3))
+    q[:, :, 0] = np.abs(q[:, :, 0]) + 0.1
+    k[:, 32:96, 0] = -np.inf
+    q[:, 7, 3] = np.nan
+    k[:, n - 1, 5], q[:, :, 5] = np.inf, -np.abs(q[:, :, 5]) - 0.1
+    q[:, 40, 5] = 0.5                          # +inf against the last key
+    npad, ldo = ctx.attn_pad(n), heads * head_dim
+    dev = []
+    for x in (q, k, v):
+        p = np.zeros((heads, npad, head_dim), np.float32)
+        p[:, :n] = x
+        dev.append(ctx.to_device(p))
+    out = torch.full((n, ldo), 7.0, device="cuda")
+    ctx.attention(*dev, n, out, ldo)
+    got = out.cpu().numpy()
+    assert np.isnan(got[[7, 40]]).all()
+    rows = [r for r in range(n) if r not in (7, 40)]
+    keys = [j for j in range(n - 1) if not 32 <= j < 96]
+    ref = dit.attention(q[:, rows].astype(np.float64), *(x[:, keys].astype(np.float64) for x in (k, v)))
+    err = rel_l2(got[rows], ref.transpose(1, 0, 2).reshape(len(rows), -1))
+    print(f"hd {head_dim} n {n}: rel_l2 {err:.2e}")
+    assert err <= 2e-6
+
+
+@pytest.mark.parametrize("m,n,k", [(17, 33, 96), (250, 1000, 160), (705, 1000, 64), (1921, 1024, 96)])
+def test_linear_f32_infinities_and_nan_stay_in_their_rows_and_columns(m, n, k):
+    """Every tile form: a NaN in the last row of A and an infinity in the last row of W touch only
+    that output row and column."""
+    torch = torch_cuda()
+    ctx = context(synth.get_config("tiny"), weights=False)
+    rng = np.random.default_rng(m)
+    a, w, b = (rng.standard_normal(s).astype(np.float32) for s in ((m, k), (n, k), (n,)))
+    a[:, 1] = np.abs(a[:, 1]) + 0.1
+    a[m - 1, 2], w[n - 1, 1] = np.nan, np.inf
+    out = torch.zeros((m, n), device="cuda")
+    ctx.linear(ctx.to_device(a), ctx.to_device(w), ctx.to_device(b), out, m, n, k)
+    got = out.cpu().numpy()
+    assert np.isnan(got[m - 1]).all() and np.isposinf(got[:m - 1, n - 1]).all()
+    ref = dit.linear({"l.w": w[:n - 1], "l.b": b[:n - 1]}, "l", a[:m - 1].astype(np.float64))
+    assert rel_l2(got[:m - 1, :n - 1], ref) <= max(4, np.sqrt(k)) * 4 * 2.0 ** -24
+
+
 def test_block_f32_gated_residual_on_tiles():
     """728 tokens, D = 1,024: every product of the block runs on the 64 x 64 or 128 x 64 tiles."""
     torch = torch_cuda()
