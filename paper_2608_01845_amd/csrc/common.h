@@ -138,10 +138,6 @@ struct GemmArgs {
   // (fewer tiles than compute units) runs on smaller tiles; 0: the tile size
   // follows the shape alone
   int fill_tiles;
-  // 1: K may be summed in two interleaved groups where that is faster. Not for
-  // products whose rows are one sample's in some calls and several samples' in
-  // others: the sample's result would depend on its company.
-  int k_groups;
   QkvOut qkv;        // EPI_QKV only
 };
 

@@ -14,7 +14,8 @@
 // round would be thin run their last rows as a second launch of smaller tiles
 // (launch_tail); products too small to fill one dispatch round of 256 x 256 tiles
 // run on smaller ones throughout, with three or four LDS buffers where one block
-// per compute unit has to hide its own loads (launch_small).
+// per compute unit has to hide its own loads, and loading waves of their own
+// where that block is 64 x 64 (launch_small).
 // float32 products run on the matrix cores too (gemm_f32.hip). Shapes that
 // neither covers (K not a multiple of 32 or 64, unaligned operands): a plain
 // LDS-tiled FMA kernel.
@@ -124,9 +125,9 @@ __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, char *lds, 
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)lds, 16, voff, soff, 0, 0);
 }
 
-template <int BM, int BN, int WM, int WN, int NB = 2, int KG = 1>
+template <int BM, int BN, int WM, int WN, int NB = 2>
 struct Cfg {
-  static constexpr int NT = 64 * WM * WN;       // threads of one K group
+  static constexpr int NT = 64 * WM * WN;       // threads
   static constexpr int TM = BM / WM / 16;       // 16x16 tiles per wave along M
   static constexpr int TN = BN / WN / 16;       // along N
   // the first LW waves (one per SIMD) issue the tile loads: with all 16 waves
@@ -134,7 +135,7 @@ struct Cfg {
   static constexpr int LW = NT / 64 >= 4 ? 4 : NT / 64;
   static constexpr int A_CHUNKS = BM * 8 / (64 * LW);  // 1 KB stripes per loading wave per stage
   static constexpr int B_CHUNKS = BN * 8 / (64 * LW);
-  static constexpr int LDS_BYTES = KG * NB * (BM + BN) * BK * 2;
+  static constexpr int LDS_BYTES = NB * (BM + BN) * BK * 2;
   static constexpr bool QKV = BN % 128 == 0 && BN / WN == 64;   // tiles that take EPI_QKV
 };
 
@@ -355,12 +356,11 @@ __device__ __forceinline__ void v_scatter(const GemmArgs &g, const char *smem, i
   }
 }
 
-// KG > 1: the block holds KG groups of WM x WN waves, group kg taking the K
-// stages kg, kg + KG, ... in LDS buffers of its own; the groups' sums are added
-// in group order before the epilogue.
-template <int BM, int BN, int WM, int WN, int EPI, int NB = 2, int KG = 1>
-__global__ __launch_bounds__(64 * WM * WN * KG) void k_gemm_mfma(GemmArgs g0) {
-  using C = Cfg<BM, BN, WM, WN, NB, KG>;
+// S > 0: the form for lone blocks, with as many loading waves again and S stages
+// per barrier (see below).
+template <int BM, int BN, int WM, int WN, int EPI, int NB = 2, int S = 0>
+__global__ __launch_bounds__(64 * WM * WN * (S > 0 ? 2 : 1)) void k_gemm_mfma(GemmArgs g0) {
+  using C = Cfg<BM, BN, WM, WN, NB>;
   // C^T tiles (weight fragment as the MFMA A operand): a lane holds 4 consecutive
   // columns of one row, 8 bytes of a bf16 output, 16 of a float32 one
   constexpr bool OUT16 = EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_QKV;
@@ -369,9 +369,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void k_gemm_mfma(GemmArgs g0) {
   constexpr bool STAGE_OUT = BM >= 192 || EPI == EPI_QKV;
   const GemmArgs g = batch_entry<bf16_t>(g0);
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int kg = KG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / C::NT) : 0;
-  char *sA = smem + kg * (C::LDS_BYTES / KG);   // [NB][BM][128 B]
-  char *sB = sA + NB * BM * BK * 2;             // [NB][BN][128 B]
+  char *sA = smem;                    // [NB][BM][128 B]
+  char *sB = smem + NB * BM * BK * 2; // [NB][BN][128 B]
 
   // Tile order: a group of 8 consecutive M tiles walks all N tiles, so blocks
   // running at once share A rows and the weight panel in L2.
@@ -422,7 +421,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void k_gemm_mfma(GemmArgs g0) {
   }
   const int64_t m0 = (int64_t)mt * BM, n0 = (int64_t)nt * BN;
 
-  const int tid = threadIdx.x - kg * C::NT, lane = tid & 63, wid = tid >> 6;
+  const bool loader = S == 0 || threadIdx.x >= C::NT;   // S == 0: the first NW waves load
+  const int tid = S > 0 ? threadIdx.x % C::NT : threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wm = wid / WN, wn = wid % WN;
   const int lr = lane & 15, lg = lane >> 4;
 
@@ -458,8 +458,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void k_gemm_mfma(GemmArgs g0) {
 
 #define WDC_GEMM_LOAD(buf, kt)                                                                     \
   {                                                                                                \
-    const int kb_ = ((kt) * KG + kg) * BK * 2;                                                     \
-    if (wu < NW) {                                                                                 \
+    const int kb_ = (kt) * BK * 2;                                                                 \
+    if (wu < NW && loader) {                                                                       \
       int v_ = va0;                                                                                \
       _Pragma("unroll") for (int i = 0; i < C::A_CHUNKS; ++i) {                                     \
         lds_load16(a_desc, sA + (buf) * BM * 128 + (i * NW + wu) * 1024, v_, kb_);                  \
@@ -484,15 +484,15 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void k_gemm_mfma(GemmArgs g0) {
   }
 
   constexpr int SL = C::A_CHUNKS + C::B_CHUNKS;           // load instructions per loading wave per stage
-  const int nk = (int)(g.k / (BK * KG));                  // stages of a K group
+  const int nk = (int)(g.k / BK);
   // Stages 0 and 1 fill both buffers; stage 0 is complete once no more than
   // stage 1's loads are pending (a wave's memory operations complete in issue
   // order).
 #pragma unroll
   for (int st = 0; st < NB; ++st)
     if (st < nk) WDC_GEMM_LOAD(st, st);
-  if (wu < NW) {
-    if (nk >= NB) __builtin_amdgcn_s_waitcnt(vm_wait((NB - 1) * SL));
+  if (wu < NW && loader) {
+    if (nk >= NB) __builtin_amdgcn_s_waitcnt(vm_wait((NB - (S > 0 ? S : 1)) * SL));
     else __builtin_amdgcn_s_waitcnt(WAIT_VM0);
   }
   WDC_GEMM_BARRIER();
@@ -506,6 +506,67 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void k_gemm_mfma(GemmArgs g0) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
+  if constexpr (S > 0) {
+    // One wave per SIMD and four MFMAs per k-step: a wave that also loads issues
+    // its loads, fragment reads and MFMAs one after the other, and nothing runs
+    // under their latencies. Here waves 4 to 7 issue the loads, and waves 0 to 3
+    // read all fragments of the next S stages at once, then run the MFMAs of the
+    // S they hold. After the barrier the step read last is in registers, so its
+    // buffers take the loads of the step NS ahead, and the next step has landed.
+    // 226 x 3,072, K = 4,096, six buffers: 18.4 us with the loop below (three to
+    // eight buffers), 17.9 with S = 2 and the computing waves loading, 14.5 so
+    // (15.5 with S = 1). The sums are those of the loop below, term by term.
+    static_assert(NB % S == 0 && NB / S >= 2 && NW * 64 == C::NT, "whole steps, as many loading waves as computing ones");
+    constexpr int NS = NB / S;
+    int buf = 0;                                          // first buffer of step kt
+    if (loader) {
+      for (int kt = 0; kt * S < nk; ++kt) {
+        if ((kt + NS) * S <= nk) __builtin_amdgcn_s_waitcnt(vm_wait((NS - 2) * S * SL));
+        else __builtin_amdgcn_s_waitcnt(WAIT_VM0);
+        __builtin_amdgcn_s_barrier();
+#pragma unroll
+        for (int st = 0; st < S; ++st)
+          if ((kt + NS) * S + st < nk) WDC_GEMM_LOAD(buf + st, (kt + NS) * S + st);
+        buf = buf + S == NB ? 0 : buf + S;
+      }
+      return;
+    }
+    bf16x8 fa[2][S][2][TM], fb[2][S][2][TN];
+    auto read = [&](bf16x8 (&a)[S][2][TM], bf16x8 (&b)[S][2][TN], int buf) {
+#pragma unroll
+      for (int st = 0; st < S; ++st)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+#pragma unroll
+          for (int i = 0; i < TM; ++i) a[st][s][i] = *(const bf16x8 *)(sA + (buf + st) * BM * 128 + (ra0 ^ (64 * s)) + i * 16 * 128);
+#pragma unroll
+          for (int j = 0; j < TN; ++j) b[st][s][j] = *(const bf16x8 *)(sB + (buf + st) * BN * 128 + (rb0 ^ (64 * s)) + j * 16 * 128);
+        }
+    };
+    read(fa[0], fb[0], 0);
+    auto step = [&](int kt, bf16x8 (&a)[S][2][TM], bf16x8 (&b)[S][2][TN], bf16x8 (&an)[S][2][TM], bf16x8 (&bn)[S][2][TN]) {
+      buf = buf + S == NB ? 0 : buf + S;
+      WDC_GEMM_BARRIER();
+      if ((kt + 1) * S < nk) read(an, bn, buf);           // stages past the last: stale, not used
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int st = 0; st < S; ++st)
+        if (st == 0 || kt * S + st < nk)
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+              for (int j = 0; j < TN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[st][s][j], a[st][s][i], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int kt = 0; kt * S < nk; kt += 2) {
+      step(kt, fa[0], fb[0], fa[1], fb[1]);
+      if ((kt + 1) * S >= nk) break;
+      step(kt + 1, fa[1], fb[1], fa[0], fb[0]);
+    }
+  } else {
   // Two k-steps of 32 per stage, each TM rows of TN MFMAs (v_mfma_16x16x32: at
   // the power limit a loop of them sustains 2,065 TFLOP/s on random operands
   // with two waves per SIMD where 32x32x16 sustains 1,500, and at 64 x 64 to 128
@@ -534,12 +595,12 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void k_gemm_mfma(GemmArgs g0) {
 #define WDC_GEMM_LOAD1(lbuf, lkt, l)                                                               \
   {                                                                                                \
     if ((l) < C::A_CHUNKS) {                                                                       \
-      lds_load16(a_desc, sA + (lbuf) * BM * 128 + ((l) * NW + wu) * 1024, va, ((lkt) * KG + kg) * BK * 2);\
+      lds_load16(a_desc, sA + (lbuf) * BM * 128 + ((l) * NW + wu) * 1024, va, (lkt) * BK * 2);             \
       if ((l) + 1 < C::A_CHUNKS) asm volatile("v_add_u32 %0, %0, %1" : "+v"(va) : "s"(a_step));     \
     } else {                                                                                       \
       const int lb_ = (l) - C::A_CHUNKS;                                                           \
       lds_load16(b_desc, sB + (lbuf) * BN * 128 + (lb_ * NW + wu) * 1024, vb,                      \
-                 lb_ * 8 * NW * (int)g.k * 2 + ((lkt) * KG + kg) * BK * 2);                        \
+                 lb_ * 8 * NW * (int)g.k * 2 + (lkt) * BK * 2);                                    \
     }                                                                                              \
   }
   // the loads that belong after MFMA q of LQ since the barrier (the branch holds
@@ -606,30 +667,12 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void k_gemm_mfma(GemmArgs g0) {
     prv = buf;
     buf = nxt;
   }
+  }
 #undef WDC_GEMM_LOADS
 #undef WDC_GEMM_LOAD1
 #undef WDC_GEMM_READA
 #undef WDC_GEMM_READB
 
-  if constexpr (KG > 1) {
-    static_assert(!STAGE_OUT && (KG - 1) * BM * BN * 4 <= C::LDS_BYTES, "partial sums in LDS");
-    f32x4 *part = (f32x4 *)smem + tid;                    // [group - 1][TM][TN][threads of a group]
-    __syncthreads();                                      // every group is done with its buffers
-    if (kg > 0) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) part[(((kg - 1) * TM + i) * TN + j) * C::NT] = acc[i][j];
-    }
-    __syncthreads();
-    if (kg > 0) return;
-#pragma unroll
-    for (int u = 0; u + 1 < KG; ++u)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] += part[((u * TM + i) * TN + j) * C::NT];
-  }
   const bf16_t *bias = (const bf16_t *)g.bias;
   const int cb = wn * (BN / WN) + 4 * lg;                 // the lane's columns in the block: cb + 16 j + 0..3
   if constexpr (OUT16 && STAGE_OUT) {
@@ -774,9 +817,9 @@ int rect_chunks(const GemmArgs &g) {
   return chunks >= 64 ? chunks : 0;
 }
 
-template <int BM, int BN, int WM, int WN, int NB = 2, int KG = 1>
+template <int BM, int BN, int WM, int WN, int NB = 2, int S = 0>
 hipError_t launch_mfma(const GemmArgs &g0, hipStream_t s, int max_chunks = 0) {
-  using C = Cfg<BM, BN, WM, WN, NB, KG>;
+  using C = Cfg<BM, BN, WM, WN, NB>;
   GemmArgs g = g0;
   const int m_tiles = (int)((g.m + BM - 1) / BM), n_tiles = (int)(g.n / BN);
   g.rect_n = RECT_N;
@@ -784,38 +827,38 @@ hipError_t launch_mfma(const GemmArgs &g0, hipStream_t s, int max_chunks = 0) {
   g.order = chunks > 0 ? 1 : BM == 64 && m_tiles <= 8 && n_tiles % 8 == 0 && g.batch <= 1 ? 2 : 0;
   int blocks = m_tiles * n_tiles;
   if (g.order == 1) blocks = ((max_chunks > 0 ? max_chunks : chunks) + 7) / 8 * 256;
-  dim3 grid(blocks, 1, g.batch > 1 ? g.batch : 1), block(C::NT * KG);
+  dim3 grid(blocks, 1, g.batch > 1 ? g.batch : 1), block(C::NT * (S > 0 ? 2 : 1));
   switch (g.epi) {
-    case EPI_STORE: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_STORE, NB, KG>), grid, block, C::LDS_BYTES, s, g); break;
-    case EPI_GELU: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GELU, NB, KG>), grid, block, C::LDS_BYTES, s, g); break;
-    case EPI_GATE_RES: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES, NB, KG>), grid, block, C::LDS_BYTES, s, g); break;
-    case EPI_GATE_RES_NT: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES_NT, NB, KG>), grid, block, C::LDS_BYTES, s, g); break;
+    case EPI_STORE: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_STORE, NB, S>), grid, block, C::LDS_BYTES, s, g); break;
+    case EPI_GELU: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GELU, NB, S>), grid, block, C::LDS_BYTES, s, g); break;
+    case EPI_GATE_RES: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES, NB, S>), grid, block, C::LDS_BYTES, s, g); break;
+    case EPI_GATE_RES_NT: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES_NT, NB, S>), grid, block, C::LDS_BYTES, s, g); break;
     case EPI_QKV:
       if constexpr (C::QKV) {
-        hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_QKV, NB, KG>), grid, block, C::LDS_BYTES, s, g);
+        hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_QKV, NB, S>), grid, block, C::LDS_BYTES, s, g);
         break;
       } else {
         return hipErrorInvalidValue;
       }
-    default: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_STORE_F32, NB, KG>), grid, block, C::LDS_BYTES, s, g); break;
+    default: hipLaunchKernelGGL((k_gemm_mfma<BM, BN, WM, WN, EPI_STORE_F32, NB, S>), grid, block, C::LDS_BYTES, s, g); break;
   }
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN, int NB = 2, int KG = 1>
+template <int BM, int BN, int WM, int WN, int NB = 2, int S = 0>
 hipError_t set_lds_limit() {
-  using C = Cfg<BM, BN, WM, WN, NB, KG>;
-  const void *k[5] = {(const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_STORE, NB, KG>,
-                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GELU, NB, KG>,
-                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES, NB, KG>,
-                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES_NT, NB, KG>,
-                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_STORE_F32, NB, KG>};
+  using C = Cfg<BM, BN, WM, WN, NB>;
+  const void *k[5] = {(const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_STORE, NB, S>,
+                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GELU, NB, S>,
+                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES, NB, S>,
+                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_GATE_RES_NT, NB, S>,
+                      (const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_STORE_F32, NB, S>};
   for (const void *f : k) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
     if (e != hipSuccess) return e;
   }
   if constexpr (C::QKV)
-    return hipFuncSetAttribute((const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_QKV, NB, KG>,
+    return hipFuncSetAttribute((const void *)k_gemm_mfma<BM, BN, WM, WN, EPI_QKV, NB, S>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
   return hipSuccess;
 }
@@ -833,13 +876,13 @@ int64_t tile_count(const GemmArgs &g, int bm, int bn) {
 // Tile shape of a product too small for the 256 x 256 tiles (n % 64 == 0).
 // Measured per 64-deep K stage (microseconds a compute unit takes for the
 // blocks it holds), the products alone on the device:
-//   64 x 64, 3 buffers: 0.30 for one block, 0.64 for three
+//   64 x 64, lone (6 buffers, loading waves): 0.19; 3 buffers: 0.64 for three blocks
 //   96 x 128, 4 buffers, one block: 0.43; 128 x 128, one block: 0.53
 //   128 x 128, 2 buffers, two blocks: 0.95
 //   192 x 128 and 256 x 128, 3 buffers, 8 waves, one block: 0.60 and 0.78
 // and a few microseconds of prologue and epilogue per round, which nothing
 // overlaps. So: 64 x 64 while they do not fill the device (226 x 3,072, K = 4,096:
-// 19.5 us against 36.7 on 128 x 64; 256 x 3,072, K = 12,288: 53 against 104), then
+// 14.5 us against 36.7 on 128 x 64; 256 x 3,072, K = 12,288: 59.6 against 104), then
 // the smallest of 96 and 128 x 128 that fits it once (2,688 x 1,024, K = 4,096: 37.5
 // us against 41.6 on 128 x 128 and 45.1 on 128 x 64 with two buffers; 3,000 x
 // 1,536, K = 1,536: 18.8, 21.6 and 24.9), then the cheapest of two 128 x 128 blocks
@@ -853,7 +896,7 @@ SmallTile pick_small(const GemmArgs &g, bool out16, double *us) {
   const double st = (double)(g.k / BK);
   auto rounds = [&](int64_t tiles) { return (double)((tiles + cus - 1) / cus); };
   const int64_t t64 = tile_count(g, 64, 64);
-  *us = 0.30 * st + 2.5;
+  *us = 0.19 * st + 2.5;
   if (t64 <= cus) return T64;
   if (g.n % 128 != 0) {   // narrow outputs (the output head: n = 64 latent values per token)
     *us = (0.30 * st + 2.5) * rounds(t64);
@@ -880,12 +923,11 @@ hipError_t launch_small(const GemmArgs &g, bool out16, hipStream_t s) {
   double us;
   switch (pick_small(g, out16, &us)) {
     case T64:
-      // a lone 64 x 64 block per CU is bound by the latency of its stages: two
-      // groups of waves halve the chain (226 x 3,072, K = 4,096: 20.1 us with one
-      // group, 17.9 with two, 22.2 with four of two buffers each; 256 x 3,072, K =
-      // 12,288: 53.8, 47.5, 61.7; 77 x 1,024, K = 1,024: 6.4 and 5.8)
-      if (g.k_groups && g.k % (2 * BK) == 0 && g.k >= 512 && tile_count(g, 64, 64) <= device_cus())
-        return launch_mfma<64, 64, 2, 2, 3, 2>(g, s);
+      // lone blocks, at most one per compute unit: loading waves of their own, two
+      // stages per barrier (226 x 3,072, K = 4,096: 14.5 us against 18.4; 16 x 4,096,
+      // K = 8,192: 32.0 and 48; 256 x 3,072, K = 12,288: 59.6 and 73; 300 x 1,536, K =
+      // 1,536: 7.1 and 8.5; below K = 512 both are as long as the launch)
+      if (tile_count(g, 64, 64) <= device_cus()) return launch_mfma<64, 64, 2, 2, 6, 2>(g, s);
       return launch_mfma<64, 64, 2, 2, 3>(g, s);
     case T128_64: return launch_mfma<128, 64, 2, 2>(g, s);
     case T96_128: return launch_mfma<96, 128, 2, 2, 4>(g, s);
@@ -996,7 +1038,7 @@ hipError_t launch_gemm(int dtype, const GemmArgs &g_in, hipStream_t s) {
       if (e == hipSuccess) e = set_lds_limit<128, 128, 2, 2, 4>();
       if (e == hipSuccess) e = set_lds_limit<128, 64, 2, 2>();
       if (e == hipSuccess) e = set_lds_limit<64, 64, 2, 2, 3>();
-      if (e == hipSuccess) e = set_lds_limit<64, 64, 2, 2, 3, 2>();
+      if (e == hipSuccess) e = set_lds_limit<64, 64, 2, 2, 6, 2>();
       if (e != hipSuccess) return e;
     }
     // 256 x 256 block tiles: 8 waves of 128 x 64 (two per SIMD). With the reads

@@ -319,8 +319,7 @@ struct Batch {
 };
 
 wdc_status gemm(wdc_ctx *c, const void *a, int64_t lda, const void *w, const void *b, void *out, int64_t ldc,
-                int64_t m, int64_t n, int64_t k, int epi, const float *gate = nullptr, Batch bt = Batch(),
-                bool k_groups = false) {
+                int64_t m, int64_t n, int64_t k, int epi, const float *gate = nullptr, Batch bt = Batch()) {
   if (m <= 0 || bt.n <= 0) return WDC_OK;
   if (!w) {
     set_err(c, "weights not bound");
@@ -343,7 +342,6 @@ wdc_status gemm(wdc_ctx *c, const void *a, int64_t lda, const void *w, const voi
   g.c_bs = bt.c_bs;
   g.gate_bs = bt.gate_bs;
   g.fill_tiles = c->fill_tiles;
-  g.k_groups = k_groups;
   HIPCHK(c, timed(c, WDC_T_GEMM, 2.0 * m * n * k * bt.n, [&] { return launch_gemm(c->d.dtype, g, c->stream); }));
   return WDC_OK;
 }
@@ -664,7 +662,7 @@ wdc_status dit_forward_batch(wdc_ctx *c, int nb, const float *const *z, double t
         return WDC_E_ARG;
       }
       CHK(gemm(c, text[b], d.text_dim, W(c, "text_proj.w"), W(c, "text_proj.b"), c->x + (b * N + NV) * D, D, c->nt,
-               D, d.text_dim, EPI_STORE_F32, nullptr, Batch(), true));
+               D, d.text_dim, EPI_STORE_F32));
     }
   }
   for (int b = 0; b < d.n_seq + d.n_dual + d.n_single; ++b) CHK(block_forward(c, b));
@@ -1655,7 +1653,7 @@ wdc_status wdc_attention_plan(const wdc_ctx *ctx, int64_t n, int32_t *qb_main, i
 wdc_status wdc_linear(wdc_ctx *ctx, const void *d_a, int64_t lda, const void *d_w, const void *d_bias, void *d_c,
                       int64_t ldc, int64_t m, int64_t n, int64_t k) {
   if (!ctx || !d_a || !d_w || !d_c || m < 0 || n <= 0 || k <= 0 || lda < k || ldc < n) return WDC_E_ARG;
-  return gemm(ctx, d_a, lda, d_w, d_bias, d_c, ldc, m, n, k, EPI_STORE, nullptr, Batch(), true);
+  return gemm(ctx, d_a, lda, d_w, d_bias, d_c, ldc, m, n, k, EPI_STORE);
 }
 
 wdc_status wdc_set_timing(wdc_ctx *ctx, int32_t on) {

@@ -318,9 +318,9 @@ def test_forward_batch_several_blocks_of_each_kind_match_oracle():
 # (m, n, k, ldc padding): 64 x 64 tiles with 1, 2, 3 and 4 K stages in three
 # buffers; 96 x 128 and 128 x 128 with 1 to 5 stages in four; 256 x 128 and 192 x
 # 128 with partial last rows; two 128 x 128 blocks per compute unit; narrow outputs on 64 x 64 and 128 x 64;
-# 128 x 128 in place of 256 x 128 where output rows are not 16-byte aligned; 64 x 64
-# in two K groups from K = 512 on, where K has an even number of stages, and with
-# more blocks than compute units in one; up to 8 M tiles of 64 rows
+# 128 x 128 in place of 256 x 128 where output rows are not 16-byte aligned; lone 64 x
+# 64 blocks with fewer stages than their six buffers, odd numbers of them and more;
+# 64 x 64 blocks, more than there are compute units; up to 8 M tiles of 64 rows
 # grouped by weight panel, a partial last one among them
 @pytest.mark.parametrize("m,n,k,pad", [
     (1, 64, 64, 0), (65, 192, 128, 0), (63, 128, 192, 8), (130, 320, 256, 0), (1500, 1024, 64, 0), (1409, 1152, 192, 0),
