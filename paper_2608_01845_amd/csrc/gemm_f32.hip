@@ -33,6 +33,17 @@ __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, char *lds, 
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)lds, 16, voff, soff, 0, 0);
 }
 
+// Every kernel sums K in the same order, so that an output's bits do not depend on
+// the rows it shares its call with (the tile forms are chosen by their number): K
+// is cut into units of 16, unit u belongs to part w while u < units (w + 1) / 4,
+// a part's sum is a chain over its units, k = q, 4 + q, 8 + q, 12 + q for q = 0..3
+// within one, and the parts are added from the first to the last. One
+// v_mfma_f32_16x16x4 takes four terms in order, v_mfma_f32_32x32x2 two. Against one
+// chain over all of K in the tiles: 8,192 x 4,096, K = 4,096 1.98 ms for 1.96, 700 x
+// 2,048, K = 2,048 (64 x 64 tiles) 78.8 us for 76.8, and half the rounding error.
+constexpr int KU = 16;
+__device__ __forceinline__ int part_begin(int units, int w) { return units * w / 4; }
+
 // chunk c (16 bytes) of tile row r lives at c ^ ((r >> 1) & 7) of its 128-byte row
 __device__ __forceinline__ int swz(int row, int chunk) { return (row * 8 + (chunk ^ ((row >> 1) & 7))) * 16; }
 
@@ -92,20 +103,50 @@ __global__ __launch_bounds__(256) void k_gemm_f32_tile(GemmArgs g0) {
     for (int i = 0; i < B_CH; ++i) lds_load16(b_desc, s + BM * 128 + i * 4096, vb + i * b_step, kt * BK * 4);
   };
 
-  f32x16 acc[TM][TN];
+  f32x16 acc[TM][TN], tot[TM][TN];                      // the part in progress, the parts before it
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int e = 0; e < 16; ++e) tot[i][j][e] = 0.f;
 
+  const int ra = swz(wm * (BM / 2) + lr, lg), rb = BM * 128 + swz(wn * (BN / 2) + lr, lg);
+  struct Frag {
+    f32x4 a[2][TM], b[2][TN];
+  };
+  auto read = [&](Frag &f, const char *s, int h) {        // unit h of a stage
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const int s8 = 2 * h + p;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) f.a[p][i] = *(const f32x4 *)(s + (ra ^ (32 * s8)) + i * 32 * 128);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) f.b[p][j] = *(const f32x4 *)(s + BM * 128 + ((rb - BM * 128) ^ (32 * s8)) + j * 32 * 128);
+    }
+  };
+  // lane group lg holds k = 8 p + 4 lg + q of the unit: an MFMA takes k = 8 p + q and 8 p + 4 + q
+  auto mul = [&](const Frag &f) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[p][i][q], f.b[p][j][q], acc[i][j], 0, 0, 0);
+  };
+  auto unit = [&](const char *s, int h) {
+    Frag f;
+    read(f, s, h);
+    mul(f);
+  };
   const int nk = (int)(g.k / BK);
   load(0, 0);
   if (nk > 1) load(1, 1);
-  const int ra = swz(wm * (BM / 2) + lr, lg), rb = BM * 128 + swz(wn * (BN / 2) + lr, lg);
-  int buf = 0;
-  for (int kt = 0; kt < nk; ++kt) {
+  int buf = 0;                                            // of the stage in use
+  auto begin_stage = [&](int kt) {
     // stage kt is in LDS once no more than the next stage's loads are pending;
     // after the barrier every wave is also done with the buffer of stage kt - 1,
     // which takes stage kt + 2
@@ -114,24 +155,51 @@ __global__ __launch_bounds__(256) void k_gemm_f32_tile(GemmArgs g0) {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const int nbuf = buf == 0 ? NBUF - 1 : buf - 1;
     if (kt + 2 < nk) load(nbuf, kt + 2);
-    const char *s = smem + buf * STAGE;
+  };
+  auto end_stage = [&] { buf = buf == NBUF - 1 ? 0 : buf + 1; };
+  // A loop per part, in which only MFMAs touch the accumulators (a test for the
+  // next part inside one loop over the stages made the compiler copy them in and
+  // out in every stage: 8,192 x 4,096, K = 4,096 2.25 ms), and both units' reads in
+  // front of the first MFMA, which needs fragments of both halves of its unit. A part
+  // begins or ends within a stage where K is not a multiple of 128.
+  const int units = (int)(g.k / KU);
+#pragma unroll 1
+  for (int w = 0; w < 4; ++w) {
+    int u = part_begin(units, w);
+    const int ue = part_begin(units, w + 1);
+    if (u == ue) continue;
 #pragma unroll
-    for (int s8 = 0; s8 < 4; ++s8) {
-      f32x4 fa[TM], fb[TN];
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int i = 0; i < TM; ++i) fa[i] = *(const f32x4 *)(s + (ra ^ (32 * s8)) + i * 32 * 128);
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) fb[j] = *(const f32x4 *)(s + BM * 128 + ((rb - BM * 128) ^ (32 * s8)) + j * 32 * 128);
-      // lane group lg holds k = 8 s8 + 4 lg + q for q = 0..3: MFMA q takes k = 8 s8 + q and 8 s8 + 4 + q
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    if (u & 1) {
+      unit(smem + buf * STAGE, 1);
+      end_stage();
+      ++u;
     }
-    buf = buf == NBUF - 1 ? 0 : buf + 1;
+#pragma unroll 1
+    for (; u + 2 <= ue; u += 2) {
+      begin_stage(u >> 1);
+      Frag f[2];
+      read(f[0], smem + buf * STAGE, 0);
+      read(f[1], smem + buf * STAGE, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(f[0]);
+      mul(f[1]);
+      end_stage();
+    }
+    if (u < ue) {
+      begin_stage(u >> 1);
+      unit(smem + buf * STAGE, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) tot[i][j][e] += acc[i][j][e];
   }
 
   // lane: column lr of each 32 x 32 tile, rows 8 (e / 4) + 4 lg + e % 4
@@ -153,7 +221,7 @@ __global__ __launch_bounds__(256) void k_gemm_f32_tile(GemmArgs g0) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int r = 8 * (e / 4) + e % 4;
-        if (rb0 + r < g.m) c[r * g.ldc] = finish<EPI>(acc[i][j][e], bv, gv, x[e]);
+        if (rb0 + r < g.m) c[r * g.ldc] = finish<EPI>(tot[i][j][e], bv, gv, x[e]);
       }
     }
   }
@@ -161,8 +229,8 @@ __global__ __launch_bounds__(256) void k_gemm_f32_tile(GemmArgs g0) {
 
 template <int T, int EPI>
 __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs g0) {
-  constexpr int KU = T == 32 ? 8 : 16;                  // K per 16-byte load pair (64 / T lane groups of 4)
-  constexpr int U = 4;                                  // load pairs in flight per iteration
+  constexpr int NP = T == 32 ? 2 : 1;                   // 16-byte load pairs of a unit (64 / T lane groups of 4)
+  constexpr int U = 4 / NP;                             // units in flight per iteration
   constexpr int NE = T * T / 64;                        // accumulator entries per lane
   const GemmArgs g = batch_entry(g0);
   __shared__ float red[4][T * T];
@@ -173,48 +241,56 @@ __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs g0) {
   // rows past the end read the last row (their outputs are not stored)
   const float *pa = (const float *)g.a + min(m0 + lr, g.m - 1) * g.lda + 4 * lg;
   const float *pw = (const float *)g.w + min(n0 + lr, g.n - 1) * g.k + 4 * lg;
-  const int units = (int)(g.k / KU), u0 = units * wu / 4, u1 = units * (wu + 1) / 4;
+  const int units = (int)(g.k / KU), u0 = part_begin(units, wu), u1 = part_begin(units, wu + 1);
 
   typedef __attribute__((ext_vector_type(NE))) float accv;
   accv acc;
 #pragma unroll
   for (int e = 0; e < NE; ++e) acc[e] = 0.f;
-  auto step = [&](const f32x4 &a, const f32x4 &b) {
+  auto load = [&](f32x4 (&a)[NP], f32x4 (&b)[NP], int u) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if constexpr (T == 32) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b[q], acc, 0, 0, 0);
-      else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[q], acc, 0, 0, 0);
+    for (int p = 0; p < NP; ++p) {
+      a[p] = *(const f32x4 *)(pa + (int64_t)u * KU + 8 * p);
+      b[p] = *(const f32x4 *)(pw + (int64_t)u * KU + 8 * p);
     }
   };
-  // U load pairs ahead: the next U are requested before the current U are used
-  f32x4 fa[U], fb[U];
+  auto step = [&](const f32x4 (&a)[NP], const f32x4 (&b)[NP]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        if constexpr (T == 32) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[p][q], b[p][q], acc, 0, 0, 0);
+        else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[p][q], b[p][q], acc, 0, 0, 0);
+      }
+  };
+  // the next U units are requested before the current U are used
+  f32x4 fa[U][NP], fb[U][NP];
   int u = u0;
   if (u + U <= u1) {
 #pragma unroll
-    for (int i = 0; i < U; ++i) {
-      fa[i] = *(const f32x4 *)(pa + (int64_t)(u + i) * KU);
-      fb[i] = *(const f32x4 *)(pw + (int64_t)(u + i) * KU);
-    }
+    for (int i = 0; i < U; ++i) load(fa[i], fb[i], u + i);
     for (; u + 2 * U <= u1; u += U) {
-      f32x4 na[U], nb[U];
+      f32x4 na[U][NP], nb[U][NP];
 #pragma unroll
-      for (int i = 0; i < U; ++i) {
-        na[i] = *(const f32x4 *)(pa + (int64_t)(u + U + i) * KU);
-        nb[i] = *(const f32x4 *)(pw + (int64_t)(u + U + i) * KU);
-      }
+      for (int i = 0; i < U; ++i) load(na[i], nb[i], u + U + i);
 #pragma unroll
       for (int i = 0; i < U; ++i) step(fa[i], fb[i]);
 #pragma unroll
-      for (int i = 0; i < U; ++i) {
-        fa[i] = na[i];
-        fb[i] = nb[i];
-      }
+      for (int i = 0; i < U; ++i)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+          fa[i][p] = na[i][p];
+          fb[i][p] = nb[i][p];
+        }
     }
 #pragma unroll
     for (int i = 0; i < U; ++i) step(fa[i], fb[i]);
     u += U;
   }
-  for (; u < u1; ++u) step(*(const f32x4 *)(pa + (int64_t)u * KU), *(const f32x4 *)(pw + (int64_t)u * KU));
+  for (; u < u1; ++u) {
+    load(fa[0], fb[0], u);
+    step(fa[0], fb[0]);
+  }
 
   // accumulator entry e: 32 x 32: row 8 (e / 4) + 4 lg + e % 4; 16 x 16: row 4 lg + e; column lr
 #pragma unroll
@@ -225,7 +301,7 @@ __global__ __launch_bounds__(256) void k_gemm_f32_small(GemmArgs g0) {
     const int t = threadIdx.x + 256 * i;
     const int64_t row = m0 + t / T, col = n0 + t % T;
     if (row >= g.m || col >= g.n) continue;
-    const float s = ((red[0][t] + red[1][t]) + red[2][t]) + red[3][t];
+    const float s = (((0.f + red[0][t]) + red[1][t]) + red[2][t]) + red[3][t];   // 0 +: as in the tiles
     float *c = (float *)g.c + row * g.ldc + col;
     *c = finish<EPI>(s, g.bias ? ((const float *)g.bias)[col] : 0.f, EPI == EPI_GATE_RES ? g.gate[col] : 0.f,
                      EPI == EPI_GATE_RES ? *c : 0.f);

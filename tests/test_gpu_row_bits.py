@@ -1,10 +1,9 @@
 """A product's rows do not depend on their company: the same row of A gives the same
 bits whatever the number of rows of the call, on every tile form (GPU)."""
-import numpy as np
 import pytest
 
 import synth
-from tests.gpu_util import context, torch_cuda
+from tests.gpu_util import context, small_cfg, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +43,28 @@ def test_linear_bf16_split_rows_keep_their_bits():
     out = _linear(ctx, a, w, b, 2148)
     assert torch.equal(out[2048:], out[:100])
     assert torch.equal(_linear(ctx, a, w, b, 100), out[:100])
+
+
+# 16 x 16, 32 x 32, 64 x 64 and 128 x 64 tiles; K of one stage, and of parts that start inside a stage
+@pytest.mark.parametrize("n,k", [(1024, 1024), (1000, 32), (256, 544), (72, 96)])
+def test_linear_f32_rows_keep_their_bits(n, k):
+    torch = torch_cuda()
+    ctx, a, w, b = _operands("f32", 6000, n, k, n + k)
+    whole = _linear(ctx, a, w, b, 6000)
+    for m in (1, 17, 64, 226, 300, 700, 1400, 1921, 2688, 5000):
+        assert torch.equal(_linear(ctx, a, w, b, m), whole[:m]), m
+
+
+def test_forward_f32_sample_keeps_its_bits_in_a_batch():
+    """Five samples of a float32 model against each alone: the batched products run on larger tiles."""
+    torch = torch_cuda()
+    import paper_2608_01845_amd as wdc
+    cfg = small_cfg("f32", latent=(16, 5, 14, 18))
+    ctx = wdc.Context(cfg, max_batch=5)
+    ctx.load_weights(synth.gen_weights(cfg))
+    inp = synth.gen_inputs(cfg)
+    zs = [torch.from_numpy(synth.gen_tensor(b, "z", cfg.latent)).cuda() for b in range(5)]
+    one = {key: ctx.to_device(v) for key, v in inp.items() if key != "z_T"}
+    outs = ctx.forward_batch(zs, 0.4, *([one[key]] * 5 for key in ("cond", "text", "cam")))
+    for b in range(5):
+        assert torch.equal(outs[b], ctx.forward(zs[b], 0.4, one["cond"], one["text"], one["cam"])), b
