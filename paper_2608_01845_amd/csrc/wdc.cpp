@@ -1505,7 +1505,6 @@ wdc_status wdc_rollout_batch(wdc_ctx *ctx, wdc_state *const *states, int32_t B, 
     wdc_state *st;
     float *zc, *zh, *zn;
     std::vector<double> pre;  // pass-1 statistics of zc, emitted by the kernel that wrote it
-    bool own;                 // no other sample of the call has the same latent
   };
   std::vector<Sample> sm(B);
   for (int b = 0; b < B; ++b) {
@@ -1520,8 +1519,8 @@ wdc_status wdc_rollout_batch(wdc_ctx *ctx, wdc_state *const *states, int32_t B, 
     }
     state_reset(st, cam.empty() ? nullptr : cam.data());
     // The first step reads the caller's latent where it is; it is written by the
-    // last step only (as the candidate's buffer, or by a copy at the end).
-    sm[b] = Sample{st, d_z[b], st->rz[1], st->rz[2], {}, std::count(d_z, d_z + B, d_z[b]) == 1};
+    // copy at the end only, so that a failure leaves z_T in it.
+    sm[b] = Sample{st, d_z[b], st->rz[1], st->rz[2], {}};
   }
   wdc_step_log tmp;
   std::vector<int> ex;
@@ -1533,7 +1532,6 @@ wdc_status wdc_rollout_batch(wdc_ctx *ctx, wdc_state *const *states, int32_t B, 
     for (int b = 0; b < B; ++b) {
       Sample &q = sm[b];
       wdc_step_log *lg = h_log ? &h_log[(size_t)b * S + k] : &tmp;
-      if (k == S - 1 && q.zc != d_z[b] && q.own) q.zh = d_z[b];
       CHK(surrogate_step(q.st, q.zc, k, S, q.zh, lg, k > 0 ? q.pre.data() : nullptr));
       pre_decision(q.st, k, S, mode, h_forced ? h_forced[(size_t)b * S + k] : 0, lg);
       if (q.st->pend_surrogate) {
@@ -1576,9 +1574,7 @@ wdc_status wdc_rollout_batch(wdc_ctx *ctx, wdc_state *const *states, int32_t B, 
       q.pre.swap(q.st->pre_post);
     }
   }
-  for (int b = 0; b < B; ++b)
-    if (sm[b].zc != d_z[b])
-      HIPCHK(ctx, hipMemcpyAsync(d_z[b], sm[b].zc, bytes, hipMemcpyDeviceToDevice, ctx->stream));
+  for (int b = 0; b < B; ++b) HIPCHK(ctx, hipMemcpyAsync(d_z[b], sm[b].zc, bytes, hipMemcpyDeviceToDevice, ctx->stream));
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   return WDC_OK;
 }

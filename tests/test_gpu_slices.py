@@ -48,3 +48,23 @@ def test_rollout_writes_the_callers_latent_only_at_the_end(steps, forced):
         compare(logs, ref.log)
         assert rel_l2(z.cpu().numpy(), ref.z) <= 1e-5
         ref_z = z.cpu().numpy()
+
+
+@pytest.mark.parametrize("forced", [[0, 1, 0], [0, 1, 1, 0]])
+def test_rollout_leaves_the_callers_latent_alone_until_the_end(forced):
+    """The velocity of the last step lies in the latent's own memory: nothing may be
+    written there while the rollout can still read it, or fail."""
+    torch = torch_cuda()
+    cfg, steps = _cfg(8 * 50 + 2), len(forced)
+    p = P.with_(P.DEFAULTS, theta_q=1.0, theta_sim=-1.0)
+    vel = synth.gen_replay_velocities(cfg, steps)
+    z_T = vel[-1].copy()
+    ctx = context(cfg, weights=False, params=wdc_params(p))
+    vd = torch.from_numpy(vel).cuda()
+    ref = ro.rollout(ro.replay_denoiser(vel), z_T, steps, p, mode="forced", forced=forced)
+    sched, logs = ctx.rollout(ctx.new_state(), vd[-1], steps, mode=1, forced=forced, replay_v=vd)
+    assert sched == ref.schedule == forced
+    compare(logs, ref.log)
+    err = rel_l2(vd[-1].cpu().numpy(), ref.z)
+    print(forced, err)
+    assert err <= 1e-5
