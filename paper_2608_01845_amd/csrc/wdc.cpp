@@ -1519,8 +1519,12 @@ wdc_status wdc_rollout_batch(wdc_ctx *ctx, wdc_state *const *states, int32_t B, 
     }
     state_reset(st, cam.empty() ? nullptr : cam.data());
     // The first step reads the caller's latent where it is; it is written by the
-    // copy at the end only, so that a failure leaves z_T in it.
-    sm[b] = Sample{st, d_z[b], st->rz[1], st->rz[2], {}};
+    // copy at the end only, so that a failure leaves z_T in it. A latent that is
+    // not 16-byte aligned (the statistics would sum it in another order) is copied
+    // first.
+    const bool in_place = aligned16(d_z[b]);
+    if (!in_place) HIPCHK(ctx, hipMemcpyAsync(st->rz[0], d_z[b], bytes, hipMemcpyDeviceToDevice, ctx->stream));
+    sm[b] = Sample{st, in_place ? d_z[b] : st->rz[0], st->rz[1], st->rz[2], {}};
   }
   wdc_step_log tmp;
   std::vector<int> ex;

@@ -68,3 +68,20 @@ def test_rollout_leaves_the_callers_latent_alone_until_the_end(forced):
     err = rel_l2(vd[-1].cpu().numpy(), ref.z)
     print(forced, err)
     assert err <= 1e-5
+
+
+def test_rollout_of_an_unaligned_latent_has_the_same_bits():
+    torch = torch_cuda()
+    cfg, steps, forced = _cfg(8 * 4096 + 3), 4, [0, 1, 0, 1]
+    ctx = context(cfg, weights=False, params=wdc_params(P.with_(P.DEFAULTS, theta_q=1.0, theta_sim=-1.0)))
+    vd = torch.from_numpy(synth.gen_replay_velocities(cfg, steps)).cuda()
+    z_T = torch.from_numpy(synth.gen_inputs(cfg)["z_T"]).cuda()
+    buf = torch.empty(z_T.numel() + 3, device="cuda")
+    out = []
+    for shift in (0, 1, 3):
+        z = buf[shift:shift + z_T.numel()].view_as(z_T)
+        z.copy_(z_T)
+        logs = ctx.rollout(ctx.new_state(), z, steps, mode=1, forced=forced, replay_v=vd)[1]
+        out.append((z.clone(), [{k: v for k, v in lg.items() if v == v} for lg in logs]))   # (d_cf is NaN at first)
+    for z, logs in out[1:]:
+        assert torch.equal(z, out[0][0]) and logs == out[0][1]
