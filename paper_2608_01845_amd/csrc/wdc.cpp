@@ -151,6 +151,9 @@ thread_local std::string g_create_err;
   } while (0)
 
 bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
+bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+  return a && b && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
 
 double t_at(int k, int S) { return (double)(S - k) / (double)S; }
 
@@ -1520,9 +1523,11 @@ wdc_status wdc_rollout_batch(wdc_ctx *ctx, wdc_state *const *states, int32_t B, 
     state_reset(st, cam.empty() ? nullptr : cam.data());
     // The first step reads the caller's latent where it is; it is written by the
     // copy at the end only, so that a failure leaves z_T in it. A latent that is
-    // not 16-byte aligned (the statistics would sum it in another order) is copied
-    // first.
-    const bool in_place = aligned16(d_z[b]);
+    // not 16-byte aligned (the statistics would sum it in another order) or lies
+    // in memory that the steps write (a state's bank slot) is copied first.
+    bool in_place = aligned16(d_z[b]) && !overlap(d_z[b], bytes, ctx->ws, ctx->ws_bytes);
+    for (int j = 0; j < B; ++j)
+      in_place = in_place && !overlap(d_z[b], bytes, states[j]->anchor[0], wdc_state_bytes(ctx));
     if (!in_place) HIPCHK(ctx, hipMemcpyAsync(st->rz[0], d_z[b], bytes, hipMemcpyDeviceToDevice, ctx->stream));
     sm[b] = Sample{st, in_place ? d_z[b] : st->rz[0], st->rz[1], st->rz[2], {}};
   }

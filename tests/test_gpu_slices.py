@@ -85,3 +85,26 @@ def test_rollout_of_an_unaligned_latent_has_the_same_bits():
         out.append((z.clone(), [{k: v for k, v in lg.items() if v == v} for lg in logs]))   # (d_cf is NaN at first)
     for z, logs in out[1:]:
         assert torch.equal(z, out[0][0]) and logs == out[0][1]
+
+
+def test_rollout_batch_from_another_states_bank_slot():
+    """A latent that lies in the bank slot another sample's first exact step fills."""
+    torch = torch_cuda()
+    import paper_2608_01845_amd as wdc
+    cfg, steps, B = _cfg(8 * 50 + 2), 3, 2
+    p = P.with_(P.DEFAULTS, theta_q=1.0, theta_sim=-1.0)
+    vels = [(b + 1) * synth.gen_replay_velocities(cfg, steps) for b in range(B)]
+    z_T = [(b + 1) * synth.gen_inputs(cfg)["z_T"] for b in range(B)]
+    ctx = wdc.Context(cfg, params=wdc_params(p), allocate_weights=False, max_batch=B)
+    states = [ctx.new_state() for _ in range(B)]
+    off = states[0].bank_slot(0)[0] - states[0].mem.data_ptr()
+    slot = states[0].mem[off:off + 4 * z_T[1].size].view(torch.float32).view(cfg.latent)
+    slot.copy_(torch.from_numpy(z_T[1]))
+    zs = [torch.from_numpy(z_T[0]).cuda(), slot]
+    forced = [[0, 0, 0]] * B
+    scheds, logs = ctx.rollout_batch(states, zs, steps, mode=1, forced=forced,
+                                     replay_vs=[torch.from_numpy(v).cuda() for v in vels])
+    for b in range(B):
+        ref = ro.rollout(ro.replay_denoiser(vels[b]), z_T[b], steps, p, mode="forced", forced=forced[b])
+        compare(logs[b], ref.log)
+        assert rel_l2(zs[b].cpu().numpy(), ref.z) <= 1e-5, b
