@@ -728,11 +728,11 @@ hipError_t launch_f32(const AttnArgs &a, hipStream_t s) {
 template <int HD>
 hipError_t launch_bf16_ppr3(const AttnArgs &a, hipStream_t s) {
   constexpr int LDS = 2 * 4 * KV * HD * 2;     // four K tiles, four V^T tiles
-  static bool seen[64] = {};
-  if (first_on_device(seen)) {
-    const hipError_t e = hipFuncSetAttribute((const void *)k_attn_bf16_ppr3<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-    if (e != hipSuccess) return e;
-  }
+  static DeviceOnce once;
+  const hipError_t lim = once_on_device(once, [] {
+    return hipFuncSetAttribute((const void *)k_attn_bf16_ppr3<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+  });
+  if (lim != hipSuccess) return lim;
   AttnArgs b = a;
   attn_split_plan(b);
   const int nqb = (int)(b.n_pad / 256);

@@ -6,6 +6,8 @@
 #include <stdint.h>
 #include <string>
 
+#include "once.h"
+
 #define WDC_MAXB 17  // most latents one observation combine reads: 2 per bank slot (8) + the current one
 
 namespace wdc {
@@ -154,15 +156,12 @@ bool gemm_qkv_fusable(int dtype, const GemmArgs &g);
 // compute units of the current device (0 if the query fails)
 int device_cus();
 
-// True the first time it is called with this flag array on the current device
-// (kernel attributes such as the dynamic LDS limit are set per device). A
-// device id outside the array, or a failed query, always answers true.
-inline bool first_on_device(bool (&seen)[64]) {
-  int d = 0;
-  if (hipGetDevice(&d) != hipSuccess || d < 0 || d >= 64) return true;
-  if (seen[d]) return false;
-  seen[d] = true;
-  return true;
+// once_per_device on the current device
+template <class F>
+hipError_t once_on_device(DeviceOnce &o, F &&fn) {
+  int d = -1;
+  if (hipGetDevice(&d) != hipSuccess) d = -1;
+  return once_per_device(o, d, fn);
 }
 
 // ------------------------------------------------------------------ attention

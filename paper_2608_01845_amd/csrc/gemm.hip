@@ -27,12 +27,15 @@ namespace wdc {
 
 // compute units of the current device (the rectangle order needs exactly 256)
 int device_cus() {
-  static int cus[64] = {};
+  static std::atomic<int> cus[64] = {};   // 0: not yet known
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-  if (!cus[dev] && hipDeviceGetAttribute(&cus[dev], hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    cus[dev] = 0;
-  return cus[dev];
+  int n = cus[dev].load(std::memory_order_relaxed);
+  if (n == 0) {
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    cus[dev].store(n, std::memory_order_relaxed);
+  }
+  return n;
 }
 
 namespace {
@@ -1028,8 +1031,8 @@ hipError_t launch_gemm(int dtype, const GemmArgs &g_in, hipStream_t s) {
   // the MFMA kernels read 16-byte operand chunks and write 4-column output groups
   const bool aligned = operands_aligned(g);
   if (dtype == 1 && aligned) {
-    static bool seen[64] = {};
-    if (first_on_device(seen)) {
+    static DeviceOnce once;
+    const hipError_t lim = once_on_device(once, [] {
       hipError_t e = set_lds_limit<256, 256, 2, 4>();
       if (e == hipSuccess) e = set_lds_limit<256, 128, 4, 2, 3>();
       if (e == hipSuccess) e = set_lds_limit<192, 128, 4, 2, 3>();
@@ -1039,8 +1042,9 @@ hipError_t launch_gemm(int dtype, const GemmArgs &g_in, hipStream_t s) {
       if (e == hipSuccess) e = set_lds_limit<128, 64, 2, 2>();
       if (e == hipSuccess) e = set_lds_limit<64, 64, 2, 2, 3>();
       if (e == hipSuccess) e = set_lds_limit<64, 64, 2, 2, 6, 2>();
-      if (e != hipSuccess) return e;
-    }
+      return e;
+    });
+    if (lim != hipSuccess) return lim;
     // 256 x 256 block tiles: 8 waves of 128 x 64 (two per SIMD). With the reads
     // and loads interleaved into the MFMA stream they were 0.3-1.5% faster than
     // 16 waves of 64 x 64 on the 13B products and read a quarter fewer LDS

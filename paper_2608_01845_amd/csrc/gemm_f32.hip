@@ -317,12 +317,15 @@ hipError_t launch_tile(const GemmArgs &g, hipStream_t s) {
   constexpr int LDS = NBUF * (BM + BN) * 128;
   const void *k[3] = {(const void *)k_gemm_f32_tile<BM, BN, EPI_STORE>, (const void *)k_gemm_f32_tile<BM, BN, EPI_GELU>,
                       (const void *)k_gemm_f32_tile<BM, BN, EPI_GATE_RES>};
-  static bool seen[64] = {};
-  if (first_on_device(seen))
+  static DeviceOnce once;
+  const hipError_t lim = once_on_device(once, [&] {
     for (const void *f : k) {
       const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
       if (e != hipSuccess) return e;
     }
+    return hipSuccess;
+  });
+  if (lim != hipSuccess) return lim;
   const dim3 grid((unsigned)((g.m + BM - 1) / BM * ((g.n + BN - 1) / BN)), 1, g.batch > 1 ? g.batch : 1), block(256);
   if (g.epi == EPI_GELU) hipLaunchKernelGGL((k_gemm_f32_tile<BM, BN, EPI_GELU>), grid, block, LDS, s, g);
   else if (g.epi == EPI_GATE_RES) hipLaunchKernelGGL((k_gemm_f32_tile<BM, BN, EPI_GATE_RES>), grid, block, LDS, s, g);

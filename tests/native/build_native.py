@@ -22,6 +22,7 @@ ROOT = os.path.dirname(os.path.dirname(HERE))
 OUT = os.path.join(HERE, "_out")
 LIB = os.path.join(OUT, "libwdc_hostsan.so")
 DRIVER = os.path.join(OUT, "abi_driver")
+ONCE = os.path.join(OUT, "once_test")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 CLANG = os.path.join(ROCM, "llvm", "bin", "clang")
 
@@ -57,6 +58,10 @@ def build(verbose: bool = False) -> str:
           f"-L{OUT}", "-lwdc_hostsan", f"-L{ROCM}/lib", "-lamdhip64", "-lm",
           "-Wl,-rpath,$ORIGIN", f"-Wl,-rpath,{ROCM}/lib"])
     os.replace(DRIVER + ".tmp", DRIVER)
+    # host code alone: one-time work under several threads
+    _run([clang, "-x", "c++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-pthread",
+          os.path.join(HERE, "once_test.cpp"), "-o", ONCE + ".tmp", "-lstdc++"])
+    os.replace(ONCE + ".tmp", ONCE)
     if verbose:
         print("built", LIB, "and", DRIVER)
     return DRIVER
