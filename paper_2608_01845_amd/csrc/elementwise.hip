@@ -309,7 +309,9 @@ __global__ __launch_bounds__(256) void k_qkv_pad(T *q, T *k, T *v, int hd, int64
 // every wave cost more than its weights' loads (a 18,432 x 3,072 modulation
 // 57 us, 2.0 TB/s; 35 us here). Sums run in one fixed order (explicit fused
 // multiply-adds, lane by lane, then the butterfly), so a sample's result does
-// not depend on how many share the launch.
+// not depend on how many share the launch. The 8 (float32: 4) products of a
+// 16-byte load are summed before they meet the lane's sum: one rounding at its
+// size per load and not per product.
 // CH input elements per sample are in LDS at a time; a chunk's weights are
 // requested before the barriers of its staging, so they travel under it.
 
@@ -348,13 +350,16 @@ __device__ __forceinline__ void gv_dot(const T *const (&w)[R], int k, bool vec, 
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           const uint32_t uu[4] = {u[it][r].x, u[it][r].y, u[it][r].z, u[it][r].w};
+          float t[NB];
 #pragma unroll
           for (int e = 0; e < V; ++e) {
             const float wv = sizeof(T) == 4 ? __uint_as_float(uu[e % 4])
                                             : __uint_as_float(e & 1 ? uu[e / 2] & 0xffff0000u : uu[e / 2] << 16);
 #pragma unroll
-            for (int b = 0; b < NB; ++b) acc[r][b] = fmaf(wv, x[b][e], acc[r][b]);
+            for (int b = 0; b < NB; ++b) t[b] = e == 0 ? wv * x[b][0] : fmaf(wv, x[b][e], t[b]);
           }
+#pragma unroll
+          for (int b = 0; b < NB; ++b) acc[r][b] += t[b];
         }
       }
     } else {

@@ -295,6 +295,25 @@ def test_cond_embed_odd_lengths_match_oracle(dtype, hidden, cond, cam):
     assert err <= 2e-6     # float32 sums of up to 5,000 terms
 
 
+@pytest.mark.parametrize("dtype,width", [("bf16", 8), ("f32", 4)])
+def test_cond_embed_sums_a_load_before_it_meets_the_total(dtype, width):
+    """Rows whose partial sum is 2^24, where adding 1 is lost: the ones of a 16-byte load
+    reach it together."""
+    torch = torch_cuda()
+    cfg = small_cfg(dtype, cond_dim=4096, cam_dim=0)
+    ctx = context(cfg)
+    W = {name: np.zeros(shape, np.float32) for name, shape, _ in ctx.weight_table()}
+    cond = np.zeros(4096, np.float32)
+    step, loads = 64 * width, 4096 // (64 * width)
+    cond[0], cond[(loads - 1) * step] = 4096.0, -4096.0
+    W["cond_embed.w"][:, [0, (loads - 1) * step]] = 4096.0
+    for j in range(1, loads - 1):
+        cond[j * step:j * step + width] = W["cond_embed.w"][:, j * step:j * step + width] = 1.0
+    ctx.load_weights(W)
+    got = ctx.cond_embed(0.5, ctx.to_device(cond)).cpu().numpy()
+    assert (got == (loads - 2) * width).all(), got[:4]
+
+
 def test_forward_batch_several_blocks_of_each_kind_match_oracle():
     """Two blocks of every kind, five samples: the modulation vectors of all
     blocks come from one launch, four samples at a time."""
