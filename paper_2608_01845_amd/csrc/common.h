@@ -296,11 +296,11 @@ SegPlan make_seg_plan(int c, int64_t t, int g);
 enum { PRE_NV = 6, OBS_NV = PRE_NV + 1, POST_NV = 10 };
 
 // K8: z, optional anchor za -> per block [sum z, sum d, sum z^2, sum d^2, sum|d|, sum|za|], d = z - za
-hipError_t launch_stats_pre(const SegPlan &pl, const float *z, const float *za, float *partials, hipStream_t s);
+hipError_t launch_stats_pre(const SegPlan &pl, const float *z, const float *za, double *partials, hipStream_t s);
 // K9: zhat = sum_j kappa_j out_j (j < m, slot order); per block the K8 statistics
 // of zhat against za (za may be null) followed by the count of non-finite zhat values
 hipError_t launch_observe(const SegPlan &pl, const float *const *outs, const float *kappa, int m, const float *za,
-                          float *zhat, float *partials, hipStream_t s);
+                          float *zhat, double *partials, hipStream_t s);
 // K7: exact-step epilogue. If v: zn = z + dt*v and zn is written to zn_out; else zn is read from zn_in.
 // Copies zn to bank_slot and z to anchor_out and in_slot (each when non-null). Per block:
 // [sum zn, sum (zn-za), sum (zn-z), sum zn^2, sum (zn-za)^2, sum (zn-z)^2, sum|zn-zhat|, sum|zn|,
@@ -311,9 +311,9 @@ struct PostArgs {
   float *zn_out, *bank_slot, *anchor_out, *in_slot;
   int has_anchor, has_zhat;
 };
-hipError_t launch_exact_post(const SegPlan &pl, const PostArgs &a, float *partials, hipStream_t s);
+hipError_t launch_exact_post(const SegPlan &pl, const PostArgs &a, double *partials, hipStream_t s);
 // host: sum the blocks' partial sums over splits in a fixed order: [nseg, splits, nv] -> [nseg, nv]
-void reduce_partials(const SegPlan &pl, const float *part, int nv, double *out);
+void reduce_partials(const SegPlan &pl, const double *part, int nv, double *out);
 hipError_t launch_psi(const float *z, const float *v, float dt, float *zn, int64_t n, hipStream_t s);
 
 }  // namespace wdc

@@ -5,13 +5,13 @@
 // which is the finest chunking the 256-d summary pools over (coarser chunks
 // nest: floor(4j/T) = floor(floor(8j/T)/2)). Each block streams one slice of
 // one segment, so every per-chunk sum is a plain per-block sum and the grid
-// needs no atomics. The blocks write their partial sums (7 to 10 floats each)
+// needs no atomics. The blocks write their partial sums (6 to 10 doubles each)
 // straight into the state's pinned host memory, and the host, which waits for
 // them anyway, adds the slices of a segment in a fixed order in float64
 // (deterministic, bit-reproducible run to run): no reduction launch and no copy
-// between the kernel and the decision. That needs few blocks: slices are as
-// long as 512 blocks allow (make_seg_plan), with 1,024 threads where a slice
-// would keep 256 threads too long. The candidate step on 16 x 7 x 32 x 48
+// between the kernel and the decision. That needs few blocks: up to four slices of
+// 4,096 elements and 256 threads per segment, then slices of 16,384 elements and 1,024
+// threads, at most 64 (make_seg_plan). The candidate step on 16 x 7 x 32 x 48
 // (two such waits): 51 -> 37 us; a rollout step on 16 x 33 x 90 x 160: 74 -> 56
 // us, the combine of four latents at 6.2 TB/s (the 256 MB cache holds most of them).
 //
@@ -99,9 +99,11 @@ __device__ __forceinline__ void stream_range(const Op &op, SegRange r, bool vec,
   }
 }
 
-// the block's sums, one store by NV neighbouring lanes (part: pinned host memory)
+// The block's sums, one store by NV neighbouring lanes (part: pinned host memory).
+// The wave sums are added in float64, as the host goes on, so that a block of 16
+// waves loses no more than one of 4.
 template <int NV>
-__device__ __forceinline__ void write_partials(float (&v)[NV], float *lds, float *__restrict__ part) {
+__device__ __forceinline__ void write_partials(float (&v)[NV], float *lds, double *__restrict__ part) {
   const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
 #pragma unroll
   for (int i = 0; i < NV; ++i) v[i] = wave_sum_fast(v[i]);
@@ -110,8 +112,8 @@ __device__ __forceinline__ void write_partials(float (&v)[NV], float *lds, float
     for (int i = 0; i < NV; ++i) lds[(threadIdx.x >> 6) * NV + i] = v[i];
   __syncthreads();
   if (threadIdx.x < NV) {
-    float s = 0.f;
-    for (int w = 0; w < nw; ++w) s += lds[w * NV + threadIdx.x];
+    double s = 0.0;
+    for (int w = 0; w < nw; ++w) s += (double)lds[w * NV + threadIdx.x];
     part[(int64_t)blockIdx.x * NV + threadIdx.x] = s;
   }
 }
@@ -142,7 +144,7 @@ struct PreOp {
   }
 };
 
-__global__ __launch_bounds__(kThreads) void k_stats_pre(SegPlan pl, PreOp op, float *__restrict__ part) {
+__global__ __launch_bounds__(kThreads) void k_stats_pre(SegPlan pl, PreOp op, double *__restrict__ part) {
   __shared__ float lds[16 * PRE_NV];
   float v[PRE_NV] = {};
   stream_range<PRE_NV>(op, seg_range(pl.t, pl.g, pl.splits), pl.vec, v);
@@ -194,7 +196,7 @@ struct ObsOp {
 };
 
 template <int M>
-__global__ __launch_bounds__(kThreads) void k_observe(SegPlan pl, ObsOp<M> op, float *__restrict__ part) {
+__global__ __launch_bounds__(kThreads) void k_observe(SegPlan pl, ObsOp<M> op, double *__restrict__ part) {
   __shared__ float lds[16 * OBS_NV];
   float v[OBS_NV] = {};
   stream_range<OBS_NV>(op, seg_range(pl.t, pl.g, pl.splits), pl.vec, v);
@@ -237,7 +239,7 @@ struct PostOp {
   }
 };
 
-__global__ __launch_bounds__(kThreads) void k_exact_post(SegPlan pl, PostOp op, float *__restrict__ part) {
+__global__ __launch_bounds__(kThreads) void k_exact_post(SegPlan pl, PostOp op, double *__restrict__ part) {
   __shared__ float lds[16 * POST_NV];
   float v[POST_NV] = {};
   stream_range<POST_NV>(op, seg_range(pl.t, pl.g, pl.splits), pl.vec, v);
@@ -264,9 +266,9 @@ __global__ __launch_bounds__(256) void k_psi(const float *__restrict__ z, const 
 bool al16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 }  // namespace
 
-// Slices of about 4,096 elements and 256 threads while at most 4 of them make a
-// segment (512 blocks in all); longer segments in slices of 16,384 elements and
-// 1,024 threads: as many threads in flight, a quarter of the partial sums (16 x
+// Slices of at most 4,096 elements and 256 threads while at most 4 of them make a
+// segment; longer segments in slices of at most 16,384 elements and 1,024 threads
+// (longer ones from 64 slices on, 1,048,576 elements): as many threads in flight, a quarter of the partial sums (16 x
 // 33 x 90 x 160, exact-step epilogue 44 -> 36 us with the wave sums by lane moves).
 SegPlan make_seg_plan(int c, int64_t t, int g) {
   SegPlan p;
@@ -285,17 +287,17 @@ SegPlan make_seg_plan(int c, int64_t t, int g) {
   return p;
 }
 
-void reduce_partials(const SegPlan &pl, const float *part, int nv, double *out) {
+void reduce_partials(const SegPlan &pl, const double *part, int nv, double *out) {
   const int nseg = pl.nseg();
   for (int seg = 0; seg < nseg; ++seg) {
     double *o = out + (size_t)seg * nv;
     for (int v = 0; v < nv; ++v) o[v] = 0.0;
     for (int sp = 0; sp < pl.splits; ++sp, part += nv)
-      for (int v = 0; v < nv; ++v) o[v] += (double)part[v];
+      for (int v = 0; v < nv; ++v) o[v] += part[v];
   }
 }
 
-hipError_t launch_stats_pre(const SegPlan &pl, const float *z, const float *za, float *partials, hipStream_t s) {
+hipError_t launch_stats_pre(const SegPlan &pl, const float *z, const float *za, double *partials, hipStream_t s) {
   SegPlan p = pl;
   p.vec = al16(z) && al16(za);
   hipLaunchKernelGGL(k_stats_pre, dim3(p.nblocks()), dim3(p.threads), 0, s, p, PreOp{z, za}, partials);
@@ -304,7 +306,7 @@ hipError_t launch_stats_pre(const SegPlan &pl, const float *z, const float *za, 
 
 namespace {
 template <int M>
-hipError_t run_observe(const SegPlan &p, const ObsOp<0> &o, float *partials, hipStream_t s) {
+hipError_t run_observe(const SegPlan &p, const ObsOp<0> &o, double *partials, hipStream_t s) {
   ObsOp<M> op;
   for (int j = 0; j < WDC_MAXB; ++j) {
     op.outs[j] = o.outs[j];
@@ -319,7 +321,7 @@ hipError_t run_observe(const SegPlan &p, const ObsOp<0> &o, float *partials, hip
 }  // namespace
 
 hipError_t launch_observe(const SegPlan &pl, const float *const *outs, const float *kappa, int m, const float *za,
-                          float *zhat, float *partials, hipStream_t s) {
+                          float *zhat, double *partials, hipStream_t s) {
   if (m < 1 || m > WDC_MAXB) return hipErrorInvalidValue;
   ObsOp<0> op;
   bool vec = al16(zhat) && al16(za);
@@ -343,7 +345,7 @@ hipError_t launch_observe(const SegPlan &pl, const float *const *outs, const flo
   }
 }
 
-hipError_t launch_exact_post(const SegPlan &pl, const PostArgs &a, float *partials, hipStream_t s) {
+hipError_t launch_exact_post(const SegPlan &pl, const PostArgs &a, double *partials, hipStream_t s) {
   SegPlan p = pl;
   p.vec = al16(a.z) && al16(a.v) && al16(a.zn_in) && al16(a.za) && al16(a.zhat) && al16(a.zn_out) &&
           al16(a.bank_slot) && al16(a.anchor_out) && al16(a.in_slot);

@@ -102,8 +102,8 @@ struct wdc_state {
   double R = 0, eta = 1;
   int n_s = 0;
   float *rz[3] = {nullptr, nullptr, nullptr};  // current latent, candidate, next exact latent of a rollout
-  float *h_part = nullptr;    // pinned host: the blocks' partial sums of the last statistics kernel
-  float *partials = nullptr;  // its device address
+  double *h_part = nullptr;   // pinned host: the blocks' partial sums of the last statistics kernel
+  double *partials = nullptr; // its device address
   std::vector<double> red;    // their sums per segment
   std::vector<double> n8;   // element count of each fine segment [C*8]
   // pass-1 statistics [nseg, PRE_NV] of the latent the next step starts from,
@@ -1353,7 +1353,7 @@ wdc_status wdc_state_create(wdc_ctx *ctx, void *d_mem, size_t bytes, wdc_state *
       st->bank_in[i] = (float *)(b + lat * (2 + ctx->p.bank_capacity + i));
   for (int i = 0; i < 3; ++i) st->rz[i] = (float *)(b + lat * (n_latents(ctx) + i));
   st->red.resize((size_t)st->plan.nseg() * POST_NV);
-  hipError_t e = hipHostMalloc((void **)&st->h_part, sizeof(float) * st->plan.nblocks() * POST_NV, hipHostMallocDefault);
+  hipError_t e = hipHostMalloc((void **)&st->h_part, sizeof(double) * st->plan.nblocks() * POST_NV, hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&st->partials, st->h_part, 0);
   if (e != hipSuccess) {
     set_err(ctx, "pinned host memory for the statistics: %s", hipGetErrorString(e));

@@ -28,6 +28,23 @@ def test_replay_rollout_at_slice_edges(t, overrides):
     run_variant(_cfg(t), 10, {"period": 3, **overrides}, "periodic")
 
 
+def test_wave_sums_of_a_long_slice_are_added_without_loss():
+    """One 1,024-thread slice per segment: the first wave's sum of |z| is 2^24, where adding
+    the 1 of each of the other 15 waves would be lost in float32."""
+    torch = torch_cuda()
+    cfg = _cfg(8 * 16384 + 8)
+    z_T, vel = np.zeros(cfg.latent, np.float32), np.zeros((2,) + cfg.latent, np.float32)
+    z_T[0, 0, 0, 256 * np.arange(16)] = 1.0
+    z_T[0, 0, 0, 0] = 2.0 ** 24
+    vel[0, 0, 0, 0, 100] = 2.0 ** 20
+    p = P.with_(P.DEFAULTS, theta_q=1.0, theta_sim=-1.0)
+    ctx = context(cfg, weights=False, params=wdc_params(p))
+    logs = ctx.rollout(ctx.new_state(), torch.from_numpy(z_T).cuda(), 2, mode=1, forced=[0, 0],
+                       replay_v=torch.from_numpy(vel).cuda())[1]
+    want = 0.5 * 2.0 ** 20 / (2.0 ** 24 + 15 + p.eps)     # mean |z_1 - z_0| over mean |z_0| (Eq. (6))
+    assert abs(logs[1]["d_z"] - want) <= 1e-9 * want, (logs[1]["d_z"], want)
+
+
 @pytest.mark.parametrize("steps,forced", [
     (1, [0]), (2, [0, 0]), (2, [0, 1]), (3, [0, 1, 1]), (5, [0, 0, 1, 1, 0]), (6, [0, 1, 0, 1, 0, 1])])
 def test_rollout_writes_the_callers_latent_only_at_the_end(steps, forced):
