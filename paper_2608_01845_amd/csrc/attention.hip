@@ -289,7 +289,7 @@ __device__ __forceinline__ void ppr_qk(f32x4 (&S)[4][2], const char *k, const bf
 // key of the lane's entry e of key tile kt within the 64-key tile
 __device__ __forceinline__ int ppr_key(int kt, int lg, int e) { return 32 * (kt >> 1) + krow(4 * lg, kt & 1) + e; }
 
-// max and sum over the four lanes of a query
+// max over the four lanes of a query
 __device__ __forceinline__ float quad_max(float v) {
   auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
@@ -393,9 +393,13 @@ __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
 // sustains 2,065 TFLOP/s with two waves per SIMD, one of 32x32x16 1,500. Same-box
 // against the 32x32x16 form with the same tiles, reads and schedule: hd 128, 24
 // heads, 33,000 tokens 9.93 -> 9.04 ms (1,479 TFLOP/s), 9,001 tokens 824 -> 761
-// us; hd 64, 48 heads, 17,776 tokens 3.36 -> 3.27 ms (1,185). Between a pair's two
-// MFMAs one exponential fits (hd 128: 9.45 ms with it after both; hd 64, two per
-// pair: 3.27 ms after both, 3.33 between them).
+// us; hd 64, 48 heads, 17,776 tokens 3.38 -> 3.26 ms (1,190). Between a pair's two
+// MFMAs one exponential fits (hd 128: 9.45 ms with it after both). hd 64 has two per
+// pair and they go in front of it: 16 heads, 2,688 tokens 40.1 us (41.4 behind the
+// pair, 40.7 between), 1,500 tokens 25.2 (25.8, 25.6), 48 heads, 17,776 tokens 3.25 ms
+// (3.26, 3.24). Launches that fill the device at most once, where no power limit
+// binds, were still 1 to 2% faster in the 32x32x16 form (39.2 and 24.8 us; 5% with 8
+// heads, 88 blocks: 37.5 against 35.6), longer ones 2 to 4% slower.
 // 8 wavefronts per block (two per SIMD), 32 queries each
 // (256 per block); K tiles of 64 keys and V^T tiles reach four K and four V^T
 // LDS slots by direct buffer loads issued by waves 0-3; one block barrier per
@@ -622,8 +626,15 @@ __global__ __launch_bounds__(512, 1) void k_attn_bf16_ppr3(AttnArgs a) {
     const char *vn_ = smem + (((P) + 1) % NB) * K_BYTES;   /* V^T slot of tile t + 1 */          \
     float ls[2] = {0.f, 0.f}, ex_[2];                                                           \
     _Pragma("unroll") for (int q_ = 0; q_ < NMF; ++q_) {                                         \
-      /* hd 128: MFMA, exponential, MFMA, read, every second time the pair; hd 64: MFMAs, */      \
-      /* read, both exponentials and the pair */                                                 \
+      /* hd 128: MFMA, exponential, MFMA, read, every second time the pair; hd 64: both */        \
+      /* exponentials, MFMAs, read, the pair */                                                  \
+      if constexpr (EPM == 2) {                                                                  \
+        const int ei_ = 2 * q_, kt_ = ei_ / 8, t_ = (ei_ / 4) % 2, e_ = ei_ % 4;                 \
+        ex_[0] = __builtin_amdgcn_exp2f(S[c][kt_][t_][e_]);                                      \
+        ex_[1] = __builtin_amdgcn_exp2f(S[c][kt_][t_][e_ + 1]);                                  \
+        asm volatile("" : "+v"(ex_[0]), "+v"(ex_[1]));                                           \
+        __builtin_amdgcn_sched_barrier(0);                                                       \
+      }                                                                                          \
       WDC_PPR3_MFMA(0)                                                                           \
       if constexpr (EPM == 1) {                                                                  \
         const int kt_ = q_ / 8, t_ = (q_ / 4) % 2, e_ = q_ % 4;                                  \
@@ -639,10 +650,6 @@ __global__ __launch_bounds__(512, 1) void k_attn_bf16_ppr3(AttnArgs a) {
       __builtin_amdgcn_sched_barrier(0);                                                         \
       if (EPM == 2 || (q_ & 1)) {                                                                \
         const int ei_ = EPM == 2 ? 2 * q_ : q_ - 1, kt_ = ei_ / 8, t_ = (ei_ / 4) % 2, e_ = ei_ % 4;\
-        if constexpr (EPM == 2) {                                                                \
-          ex_[0] = __builtin_amdgcn_exp2f(S[c][kt_][t_][e_]);                                    \
-          ex_[1] = __builtin_amdgcn_exp2f(S[c][kt_][t_][e_ + 1]);                                \
-        }                                                                                        \
         const bf16x2_t pr_ = {(__bf16)ex_[0], (__bf16)ex_[1]};                                   \
         uint32_t u_ = __builtin_bit_cast(uint32_t, pr_);                                         \
         asm volatile("" : "+v"(u_));                                                             \
