@@ -19,8 +19,8 @@ pytestmark = pytest.mark.gpu
 def _pair(cfg, max_batch=1):
     """(fused, separate) contexts sharing one weight blob. These products are
     too small to fill a dispatch round of 256 x 256 tiles, which would send
-    them to the 128 x 128 tiles and the separate kernels: the fused context
-    keeps the tile size the shape selects (WDC_FILL_TILES=0)."""
+    them to smaller tiles: the fused context keeps the tile size the shape
+    selects (WDC_FILL_TILES=0)."""
     import paper_2608_01845_amd as wdc
     os.environ["WDC_FILL_TILES"] = "0"
     try:
@@ -83,11 +83,11 @@ def test_fused_qkv_batched_forward_equals_separate_preparation():
 
 
 def test_fill_tiles_mid_forward_bitwise_equal():
-    """The mid-size forward (2,688 tokens, D = 1,024) with its products on 128 x
-    128 tiles and the separate q/k/v preparation (the default: no product fills
-    a dispatch round of 256 x 256 tiles) against the 256 x 256 tiles and the
-    fused epilogue: both sum every output over K in the same order and apply
-    the same float32 arithmetic afterwards, so the velocities agree bit for bit."""
+    """The mid-size forward (2,688 tokens, D = 1,024) with its products, the fused
+    q/k/v projection among them, on smaller tiles (the default: no product fills
+    a dispatch round of 256 x 256 tiles) against the 256 x 256 tiles: both sum
+    every output over K in the same order and apply the same float32 arithmetic
+    afterwards, so the velocities agree bit for bit."""
     torch = torch_cuda()
     import paper_2608_01845_amd as wdc
     cfg = synth.get_config("mid")
@@ -104,7 +104,7 @@ def test_fill_tiles_mid_forward_bitwise_equal():
     cond = fill.to_device(inp["cond"])
     a = fill.forward(z, 0.7, cond)
     b = shape.forward(z, 0.7, cond)
-    print("mid forward: 128 x 128 + separate vs 256 x 256 + fused max |diff|", float((a - b).abs().max()))
+    print("mid forward: smaller tiles vs 256 x 256 max |diff|", float((a - b).abs().max()))
     assert torch.isfinite(a).all() and torch.equal(a, b)
 
 
@@ -136,3 +136,37 @@ def test_fused_qkv_on_small_tiles_equals_separate_preparation(hidden, head_dim, 
     vs = sep.forward_batch(zs, 0.4, inp["cond"], inp["text"], inp["cam"])
     for a, b in zip(vf, vs):
         assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+# tokens per sample are no multiple of 16, so a part of a product starts inside a sample. 4 x
+# 4,125 rows: the last 116 run apart, on 128 x 128 tiles (q/k/v) and 64 x 64 ones; 4 x 4,421
+# rows: 1,300 apart; 10 x 4,421: the last two chunks of the rectangle order apart, columns too.
+# The gated products run as a batch of one per sample, with rows of each sample apart.
+@pytest.mark.parametrize("latent,batch,head_dim", [
+    ((16, 6, 36, 76), 4, 64), ((16, 11, 40, 40), 4, 128), ((16, 11, 40, 40), 10, 64)])
+def test_split_last_rounds_of_a_batch_bitwise_equal(latent, batch, head_dim):
+    """A batched forward whose large products run their last rows as a second launch: with the
+    fused q/k/v epilogue against the separate kernels, and each sample against its forward
+    alone (attention without key ranges, whose plan follows the number of heads)."""
+    torch = torch_cuda()
+    import paper_2608_01845_amd as wdc
+    cfg = small_cfg("bf16", head_dim=head_dim, hidden=1024, heads=1024 // head_dim, latent=latent)
+    os.environ["WDC_ATTN_SPLITS"] = "1"
+    try:
+        fused = wdc.Context(cfg, max_batch=batch)
+        os.environ["WDC_FUSE_QKV"] = "0"
+        sep = wdc.Context(cfg, max_batch=batch, allocate_weights=False)
+    finally:
+        del os.environ["WDC_ATTN_SPLITS"]
+        os.environ.pop("WDC_FUSE_QKV", None)
+    fused.init_random_weights(seed=5, std=0.02)
+    sep.bind_weights(fused.weights)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(batch)
+    zs = [torch.randn(latent, generator=g, device="cuda") for _ in range(batch)]
+    one = {k: fused.to_device(v) for k, v in synth.gen_inputs(cfg).items() if k != "z_T"}
+    many = [[one[k]] * batch for k in ("cond", "text", "cam")]
+    vf, vs = fused.forward_batch(zs, 0.4, *many), sep.forward_batch(zs, 0.4, *many)
+    for b in range(batch):
+        assert torch.isfinite(vf[b]).all() and torch.equal(vf[b], vs[b]), b
+        assert torch.equal(vf[b], fused.forward(zs[b], 0.4, one["cond"], one["text"], one["cam"])), b
