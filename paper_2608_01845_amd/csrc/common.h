@@ -49,11 +49,6 @@ __device__ __forceinline__ float warp_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
-__device__ __forceinline__ double warp_sum_d(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 // Sum over each aligned group of G consecutive lanes (G = 8 or 16) with DPP
 // lane moves, no LDS round trip: lane pairs (quad permutation 1 0 3 2), pairs
 // of pairs (2 3 0 1), quads (mirror within 8 lanes), halves of 16 (mirror
@@ -72,12 +67,6 @@ __device__ __forceinline__ float group_sum(float v) {
   if (G == 16) v += dpp_move<0x140>(v);  // row_mirror
   return v;
 }
-__device__ __forceinline__ float warp_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
 // Sum over the wave, in every lane: within rows of 16 lanes by DPP moves, then
 // across rows by the gfx950 lane swaps (no LDS round trips).
 __device__ __forceinline__ float wave_sum_fast(float v) {
@@ -149,8 +138,9 @@ hipError_t launch_gemm(int dtype, const GemmArgs &g, hipStream_t s);
 // it, and the launch (any epilogue but EPI_QKV)
 bool gemm_f32_mfma(const GemmArgs &g);
 hipError_t launch_gemm_f32(const GemmArgs &g, hipStream_t s);
-// Whether launch_gemm runs this product (epi EPI_STORE shape) on the 256 x 256
-// kernels, the only ones with the EPI_QKV epilogue.
+// Whether launch_gemm can run this product with EPI_QKV: bf16, on tiles of whole
+// heads (256, 192, 128 or 96 rows, 256 or 128 columns; not the 64 x 64 ones that a
+// product of few tiles would take).
 bool gemm_qkv_fusable(int dtype, const GemmArgs &g);
 
 // compute units of the current device (0 if the query fails)
@@ -273,8 +263,6 @@ hipError_t launch_unpatchify(const float *tok, const SamplePtrs &v, int nb, int 
                              int pw, hipStream_t s);
 hipError_t launch_fill_normal(int dtype, void *dst, int64_t n, uint64_t seed, uint64_t offset, float std,
                               hipStream_t s);
-hipError_t launch_copy_rows_f32(const float *src, int64_t lds, float *dst, int64_t ldd, int64_t rows, int64_t cols,
-                                hipStream_t s);
 
 // ------------------------------------------------------------------ surrogate / risk kernels
 // A latent [C, T] (T = F*H*W) is split into C*G8 segments: segment (c, g) is

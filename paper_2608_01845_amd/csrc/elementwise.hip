@@ -530,13 +530,6 @@ __global__ void k_fill_normal(T *dst, int64_t n, uint64_t seed, uint64_t offset,
   }
 }
 
-__global__ void k_copy_rows(const float *src, int64_t lds, float *dst, int64_t ldd, int64_t rows, int64_t cols) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows * cols) return;
-  int64_t r = i / cols, c = i % cols;
-  dst[r * ldd + c] = src[r * lds + c];
-}
-
 inline unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 }  // namespace
 
@@ -774,13 +767,6 @@ hipError_t launch_fill_normal(int dtype, void *dst, int64_t n, uint64_t seed, ui
     hipLaunchKernelGGL((k_fill_normal<bf16_t>), dim3(g), dim3(256), 0, s, (bf16_t *)dst, n, seed, offset, std);
   else
     hipLaunchKernelGGL((k_fill_normal<float>), dim3(g), dim3(256), 0, s, (float *)dst, n, seed, offset, std);
-  return hipGetLastError();
-}
-
-hipError_t launch_copy_rows_f32(const float *src, int64_t lds, float *dst, int64_t ldd, int64_t rows, int64_t cols,
-                                hipStream_t s) {
-  if (rows * cols <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_copy_rows, dim3(nblk(rows * cols, 256)), dim3(256), 0, s, src, lds, dst, ldd, rows, cols);
   return hipGetLastError();
 }
 

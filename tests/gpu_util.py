@@ -67,7 +67,7 @@ def wdc_params(p):
 def context(cfg, weights=True, params=None, fill_tiles=True):
     """A context on cuda:0. fill_tiles=False: GEMM tile size by shape alone
     (products too small to fill one dispatch round of 256 x 256 tiles keep
-    those tiles instead of moving to 128 x 128 ones)."""
+    those tiles instead of moving to smaller ones)."""
     torch = torch_cuda()
     import paper_2608_01845_amd as wdc
     if not fill_tiles:

@@ -41,7 +41,7 @@ def test_scheduler_step_matches_closed_form():
     ("f32", 300, 320, 96), ("f32", 5, 64, 256)])
 def test_linear_matches_oracle(dtype, m, n, k, fill_tiles):
     """fill_tiles=True: these products fill less than one dispatch round of
-    256 x 256 tiles, so those with N % 128 == 0 run on 128 x 128 tiles; False:
+    256 x 256 tiles, so those with N % 128 == 0 run on smaller tiles; False:
     the same products on the tiles their shape alone selects (256 x 256 where
     N % 256 == 0 and M >= 512), so both kernels meet ragged M tails."""
     torch = torch_cuda()
@@ -65,8 +65,8 @@ def test_linear_matches_oracle(dtype, m, n, k, fill_tiles):
 def test_linear_output_rows_not_16_byte_aligned():
     """bf16 output rows 8-byte but not 16-byte aligned (ldc = n + 4): the
     product would take the 256 x 256 kernels (tile size by shape alone), whose
-    staged epilogue stores 16-byte chunks, so it must run on the 128 x 128
-    kernels instead. Columns past n stay untouched."""
+    staged epilogue stores 16-byte chunks, so it must run on smaller tiles,
+    whose epilogue stores 8-byte groups, instead. Columns past n stay untouched."""
     torch = torch_cuda()
     cfg = synth.get_config("mid")
     ctx = context(cfg, weights=False, fill_tiles=False)
@@ -117,7 +117,7 @@ def test_linear_large_product_rectangle_order(n):
 def test_linear_long_k_tail_split():
     """A long-K product whose last dispatch round would be thin (9 M tiles x 32
     N tiles = 288 tiles, 32 past the last whole round of 256): the first 2,048
-    rows run as 256 x 256 tiles and the last 100 as 128 x 128 tiles (a second
+    rows run as 256 x 256 tiles and the last 100 as 64 x 64 tiles (a second
     launch). Sampled rows of the first part and every row of the second against
     the oracle."""
     torch = torch_cuda()

@@ -36,7 +36,7 @@ def _cached(key, make):
 def test_linear_bf16_any_shape(m, n_blocks, k_blocks, fill, seed):
     """c = a w^T + b for M in [1, 1300], N a multiple of 64 up to 1280 and K a
     multiple of 64 up to 1536, on either tile rule (products below one dispatch
-    round of 256 x 256 tiles on 128 x 128 tiles, or tile size by shape alone)."""
+    round of 256 x 256 tiles on smaller tiles, or tile size by shape alone)."""
     torch = torch_cuda()
     n, k = 64 * n_blocks, 64 * k_blocks
     cfg = synth.get_config("mid")
