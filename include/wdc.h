@@ -257,7 +257,8 @@ wdc_status wdc_risk_update(wdc_ctx *ctx, wdc_state *st, int32_t phase, int32_t k
  * F_theta, or [S, C, F, H, W] float32 velocities used at exact steps in place
  * of F_theta. h_schedule [S] out: 0 = exact, 1 = surrogate; h_log [S] or NULL.
  * The state is reset at the start (camera descriptor from d_cam). d_z is
- * written once, at the end: after a failure it still holds z_T. */
+ * written once, by the copy at the end: after a failure before that it still
+ * holds z_T. */
 wdc_status wdc_rollout(wdc_ctx *ctx, wdc_state *st, float *d_z, int32_t S, const void *d_cond, const void *d_text,
                        const void *d_cam, int32_t mode, const uint8_t *h_forced, const float *d_replay_v,
                        uint8_t *h_schedule, wdc_step_log *h_log);
@@ -308,9 +309,8 @@ wdc_status wdc_attention(wdc_ctx *ctx, const void *d_q, const void *d_k, const v
 wdc_status wdc_attention_plan(const wdc_ctx *ctx, int64_t n, int32_t *qb_main, int32_t *kv_splits);
 
 /* c[m, n] = sum_k a[m, k] * w[n, k] + bias[n] in the model dtype with float32
- * accumulation; a row stride lda, c row stride ldc. The order of a sum depends
- * on k alone where k % 64 == 0 (float32: k % 32 == 0) and the operands are
- * 16-byte aligned: a row then has the same bits whatever rows share its call. */
+ * accumulation; a row stride lda, c row stride ldc. The order of a sum does not
+ * depend on m: a row has the same bits whatever rows share its call. */
 wdc_status wdc_linear(wdc_ctx *ctx, const void *d_a, int64_t lda, const void *d_w, const void *d_bias, void *d_c,
                       int64_t ldc, int64_t m, int64_t n, int64_t k);
 

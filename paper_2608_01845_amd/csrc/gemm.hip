@@ -400,8 +400,9 @@ __global__ __launch_bounds__(64 * WM * WN * (S > 0 ? 2 : 1)) void k_gemm_mfma(Ge
     if (mt >= m_tiles) return;
   } else if (BM == 64 && g.order == 2) {
     // few M tiles: those of one weight panel on one XCD (block id % 8), which
-    // then fetches the panel once into its L2 (226 x 3,072, K = 4,096: 18.0 us
-    // without, 15.4 with; 256 x 3,072, K = 12,288: 47.5 and 37.8; none slower).
+    // then fetches the panel once into its L2 (226 x 3,072, K = 4,096: 17.9 us
+    // without, 14.2 with; 256 x 3,072, K = 12,288: 47.0 and 38.1; none slower; weights
+    // in the last-level cache).
     // On 64-row tiles only: the branch alone cost the 96-row ones 4 to 8% and the
     // blocks of the large models 0.4%.
     const int l = bid / 8;
@@ -929,7 +930,7 @@ hipError_t launch_small(const GemmArgs &g, bool out16, hipStream_t s) {
       // lone blocks, at most one per compute unit: loading waves of their own, two
       // stages per barrier (226 x 3,072, K = 4,096: 14.5 us against 18.4; 16 x 4,096,
       // K = 8,192: 32.0 and 48; 256 x 3,072, K = 12,288: 59.6 and 73; 300 x 1,536, K =
-      // 1,536: 7.1 and 8.5; below K = 512 both are as long as the launch)
+      // 1,536: 7.1 and 8.5; below K = 512 both are as long as the launch; weights from HBM)
       if (tile_count(g, 64, 64) <= device_cus()) return launch_mfma<64, 64, 2, 2, 6, 2>(g, s);
       return launch_mfma<64, 64, 2, 2, 3>(g, s);
     case T128_64: return launch_mfma<128, 64, 2, 2>(g, s);
